@@ -48,11 +48,95 @@ __device__ __forceinline__ double u01(uint64_t seed, uint64_t r) {
 }
 
 // ------------------------------------------------------------ reductions
+// Lane exchanges without LDS.  __shfl_xor moves every 32-bit word through the
+// LDS crossbar (ds_bpermute); the 16 wavefronts of an orthogonalisation
+// workgroup summing 8 FP64 columns that way queue for 4.1-5.3 us per launch
+// (stamps of the device clock, n = 3000 to 500 000), against 0.5 us here.
+// Exchanges inside a row of 16 lanes are DPP moves; those between rows are
+// the row and half swaps of gfx950.
+template <int CTRL> __device__ __forceinline__ uint32_t dpp_word(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL> __device__ __forceinline__ float dpp_move(float x) {
+    return __uint_as_float(dpp_word<CTRL>(__float_as_uint(x)));
+}
+template <int CTRL> __device__ __forceinline__ double dpp_move(double x) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint64_t lo = dpp_word<CTRL>((uint32_t)u), hi = dpp_word<CTRL>((uint32_t)(u >> 32));
+    return __longlong_as_double((long long)(lo | (hi << 32)));
+}
+constexpr int DPP_XOR1 = 0xb1, DPP_XOR2 = 0x4e;          // quad_perm [1,0,3,2], [2,3,0,1]
+constexpr int DPP_SHL4 = 0x104;                          // lane i takes lane i + 4 of its row
+constexpr int DPP_ROR4 = 0x124, DPP_ROR8 = 0x128;        // lane i takes lane i - 4, i - 8 of its row, cyclic
+constexpr int DPP_HALF_MIRROR = 0x141;                   // lane i takes lane 7 - i of its half row
+
+// v of lane i plus v of lane i ^ D (D = 16 or 32), in every lane: swapping x
+// with itself leaves the even rows (lower half) in one result and the odd
+// rows (upper half) in the other.
+template <int D> __device__ __forceinline__ void swap_word(uint32_t x, uint32_t& even, uint32_t& odd) {
+    static_assert(D == 16 || D == 32, "row or half exchange");
+    if constexpr (D == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        even = r[0];
+        odd = r[1];
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        even = r[0];
+        odd = r[1];
+    }
+}
+template <int D> __device__ __forceinline__ float add_xor_rows(float x) {
+    uint32_t a, b;
+    swap_word<D>(__float_as_uint(x), a, b);
+    return __uint_as_float(a) + __uint_as_float(b);
+}
+template <int D> __device__ __forceinline__ double add_xor_rows(double x) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    uint32_t al, bl, ah, bh;
+    swap_word<D>((uint32_t)u, al, bl);
+    swap_word<D>((uint32_t)(u >> 32), ah, bh);
+    return __longlong_as_double((long long)((uint64_t)al | ((uint64_t)ah << 32))) +
+           __longlong_as_double((long long)((uint64_t)bl | ((uint64_t)bh << 32)));
+}
+
+// Sum over the wavefront, in every lane: pairs at distance 32, 16, 8, 4, 2, 1.
+// After the first three steps a value depends on the lane mod 8 only, so the
+// rotation by four lanes of a row pairs lane i with i ^ 4.
 template <class T> __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v = add_xor_rows<32>(v);
+    v = add_xor_rows<16>(v);
+    v += dpp_move<DPP_ROR8>(v);
+    v += dpp_move<DPP_ROR4>(v);
+    v += dpp_move<DPP_XOR2>(v);
+    v += dpp_move<DPP_XOR1>(v);
     return v;
 }
+
+// Sum over the lanes i, i + CS, i + 2 CS, ... of the wavefront (pairs at
+// distance CS, 2 CS, ... 32), valid in lanes i < CS.
+template <int CS, class T> __device__ __forceinline__ T strided_wave_sum(T v) {
+    static_assert(CS == 1 || CS == 2 || CS == 4 || CS == 8, "lanes per row group");
+    if constexpr (CS <= 1) v += dpp_move<DPP_XOR1>(v);
+    if constexpr (CS <= 2) v += dpp_move<DPP_XOR2>(v);
+    if constexpr (CS <= 4) v += dpp_move<DPP_SHL4>(v);
+    v += dpp_move<DPP_ROR8>(v);
+    v = add_xor_rows<16>(v);
+    return add_xor_rows<32>(v);
+}
+
+// Sum over the CS adjacent lanes of a row group (pairs at distance 1, 2, 4),
+// in each of them.  After two steps a value is the same in the four lanes of a
+// quad, so the half-row mirror pairs lane i with a lane holding i ^ 4's value.
+template <int CS, class T> __device__ __forceinline__ T group_lane_sum(T v) {
+    static_assert(CS == 1 || CS == 2 || CS == 4 || CS == 8, "lanes per row group");
+    if constexpr (CS >= 2) v += dpp_move<DPP_XOR1>(v);
+    if constexpr (CS >= 4) v += dpp_move<DPP_XOR2>(v);
+    if constexpr (CS >= 8) v += dpp_move<DPP_HALF_MIRROR>(v);
+    return v;
+}
+
+// The value of lane l (the same l in every lane).
+__device__ __forceinline__ int lane_value(int x, int l) { return __builtin_amdgcn_readlane(x, l); }
 
 // Sum over the threads of a workgroup of `nw` waves; every thread gets it.
 template <class T> __device__ __forceinline__ T block_sum(T v, T* sh, int nw = BLOCK / 64) {

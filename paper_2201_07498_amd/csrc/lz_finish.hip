@@ -458,7 +458,7 @@ __global__ __launch_bounds__(BLOCK) void k_spmm(State* st, const double* __restr
             while (mask) {
                 const int L = __builtin_ctzll(mask);
                 mask &= mask - 1;
-                const int bL = __shfl(b, L, 64), eL = __shfl(e, L, 64);
+                const int bL = lane_value(b, L), eL = lane_value(e, L);
                 double zz = act ? gather_dot(scol, sval, bL + g, eL, G, Y, K, k) : 0.0;
                 zz = group_sum(zz, KB2);
                 if (g == L / KB2) z = zz;

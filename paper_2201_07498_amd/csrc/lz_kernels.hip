@@ -166,41 +166,55 @@ __device__ __forceinline__ void v_round_store(uint16_t* v, double (&x)[8], bool 
 constexpr int OWAVES = OBLOCK / 64;
 
 // Wave sums of acc[kk] over the lanes that own the same columns (lane % CS
-// equal); lanes 0..CS-1 write them to red[wave][column].  Then thread k < nc
-// publishes the workgroup sum of column k (wavefronts in order) to
-// part[blockIdx.x*NCMAX + k].
+// equal); lanes 0..CS-1 write them to red[wave][column], and the wave sum of
+// nrm goes to redn[wave].  Then thread k < nc publishes the workgroup sum of
+// column k (wavefronts in order) to part[blockIdx.x*NCMAX + k], and thread NC
+// that of nrm to part2[blockIdx.x].
 template <int NC, int CS, int NCL, class A>
-__device__ __forceinline__ void publish_split(const A (&acc)[NCL], int nc, double* part, A (*red)[NC]) {
-    const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63, cs = ln % CS;
+__device__ __forceinline__ void publish_split(const A (&acc)[NCL], A nrm, int nc, double* part, double* part2,
+                                              A (*red)[NC], A* redn) {
+    const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
+    A v[NCL];
 #pragma unroll
-    for (int kk = 0; kk < NCL; ++kk) {
-        A v = acc[kk];
+    for (int kk = 0; kk < NCL; ++kk) v[kk] = strided_wave_sum<CS>(acc[kk]);
+    nrm = wave_sum(nrm);
+    if (ln < CS)
 #pragma unroll
-        for (int o = CS; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
-        if (ln < CS) red[wv][cs * NCL + kk] = v;
-    }
+        for (int kk = 0; kk < NCL; ++kk) red[wv][ln * NCL + kk] = v[kk];
+    if (ln == 0) redn[wv] = nrm;
     __syncthreads();
-    if ((int)threadIdx.x < nc) {
-        A s = red[0][threadIdx.x];
+    const int t = threadIdx.x;
+    if (t < nc) {
+        A s = red[0][t];
 #pragma unroll
-        for (int q = 1; q < OWAVES; ++q) s += red[q][threadIdx.x];
-        st_dev(&part[(int64_t)blockIdx.x * NCMAX + threadIdx.x], (double)s);
+        for (int q = 1; q < OWAVES; ++q) s += red[q][t];
+        st_dev(&part[(int64_t)blockIdx.x * NCMAX + t], (double)s);
+    } else if (t == NC) {
+        A s = redn[0];
+#pragma unroll
+        for (int q = 1; q < OWAVES; ++q) s += redn[q];
+        st_dev(&part2[blockIdx.x], (double)s);
     }
 }
 
-// Run by the last workgroup: out[k] = mul[k] * sum_b part[b*NCMAX + k] for
-// k < nc over the nb <= OGRID workgroup rows; returns sum_b p2[b].  Thread t
-// owns column t % (NC+1) (column NC stands for p2) in slice t / (NC+1), i.e.
-// rows slice, slice + S, slice + 2S, ... (S slices).  Its loads do not depend
-// on one another and are all issued before the first add, so the workgroup
-// waits for one round of loads.  The S slice sums of a column are then added
-// in slice order: the result depends on nb only, not on scheduling.
-template <int NC, class A>
+// Run by the last workgroup: out[k] = lout[k] = mul[k] * sum_b part[b*NCMAX + k]
+// for k < nc over the nb <= OGRID workgroup rows (out in global memory or
+// null, lout in LDS); returns sum_b p2[b].  Thread t owns column t % (NC+1)
+// (column NC stands for p2) in slice t / (NC+1), i.e. rows slice, slice + S,
+// slice + 2S, ... (S slices).  Its loads do not depend on one another and are
+// all issued before the first add, so the workgroup waits for one round of
+// loads.  The slice sums of a column are then added in slice order (slices
+// past nb hold no rows): the result depends on nb only, not on scheduling.
+// `stage` runs between those loads and the first barrier (LDS writes of values
+// the caller loaded in the same round).
+template <int NC, class A, class Stage>
 __device__ __forceinline__ A reduce_columns(const double* part, const double* p2, int nb, int nc,
-                                            const double* mul, double* out, A* sred, A* sh) {
+                                            const double* mul, double* out, A* lout, A* sred, A* sh,
+                                            Stage&& stage) {
     constexpr int NCC = NC + 1, S = OBLOCK / NCC, RPT = (OGRID + S - 1) / S;
     static_assert(NC <= NCMAX && S >= 1, "column count");
     const int t = threadIdx.x, col = t % NCC, slice = t / NCC;
+    const double mt = t < nc ? mul[t] : 0.0;
     if (slice < S) {
         const double* src = col < NC ? part + col : p2;
         const int64_t stride = col < NC ? NCMAX : 1;
@@ -212,17 +226,22 @@ __device__ __forceinline__ A reduce_columns(const double* part, const double* p2
         for (int i = 0; i < RPT; ++i) s += slice + i * S < nb ? (A)v[i] : A(0);
         sred[t] = s;
     }
+    stage();
     __syncthreads();
     if (t < NCC) {
+        const int used = min(S, nb);
         A s = sred[t];
-        for (int q = 1; q < S; ++q) s += sred[q * NCC + t];
-        if (t < nc) out[t] = (double)((A)mul[t] * s);
+#pragma unroll 8
+        for (int q = 1; q < used; ++q) s += sred[q * NCC + t];
+        if (t < nc) {
+            const A o = (A)mt * s;
+            lout[t] = o;
+            if (out) out[t] = (double)o;
+        }
         if (t == NC) sh[0] = s;
     }
     __syncthreads();
-    const A tot = sh[0];
-    __syncthreads();
-    return tot;
+    return sh[0];
 }
 
 // c = V[:,0..j]^T w (coefficients with respect to the unit basis vectors).
@@ -238,7 +257,8 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_dot(State* st, const typename T
     __shared__ A red[OWAVES][NC];
     __shared__ A sc[NC];
     __shared__ A sg[NC][NC + 1];
-    __shared__ A shd[OWAVES];
+    __shared__ A redn[OWAVES];
+    __shared__ A s_tot[1];
     __shared__ A sred[OBLOCK];
     __shared__ int s_last;
     const int j = st->j;
@@ -282,37 +302,46 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_dot(State* st, const typename T
             }
         }
     }
-    publish_split<NC, CS, NCL>(acc, nc, part, red);
-    nrm = block_sum(nrm, shd, OWAVES);
-    if (threadIdx.x == 0) st_dev(&part2[blockIdx.x], (double)nrm);
+    publish_split<NC, CS, NCL>(acc, nrm, nc, part, part2, red, redn);
     if (last_block(&st->ticket[TK_DOT], gridDim.x, &s_last)) {
-        // The Gram rows the correction needs are loaded in the same round of
-        // requests as the partials (nc^2 <= 4 * OBLOCK entries).
+        // Everything the tail needs beside the partials (the Gram rows of the
+        // correction, nc^2 <= 4 * OBLOCK entries, and the scalars of alpha) is
+        // loaded in the same round of requests as the partials.
         const bool gram = gram_mode(st);
+        const int mode = st->mode, reorth = st->reorth;
+        const double u_s = st->u_s;
         A gv[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int idx = threadIdx.x + q * OBLOCK;
             gv[q] = (gram && idx < nc * nc) ? (A)gm[(idx / nc) * NCMAX + idx % nc] : A(0);
         }
-        const A wn = reduce_columns<NC>(part, part2, gridDim.x, nc, st->scale, st->c, sred, shd);
-        if (gram) {
+        A bterm = A(0);
+        if (gram && threadIdx.x == 0 && j > 0) bterm = (A)st->beta[j] * (A)gm[j * NCMAX + (j - 1)];
+        const A wn = reduce_columns<NC>(part, part2, gridDim.x, nc, st->scale, st->c, sc, sred, s_tot, [&] {
+            if (gram)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int idx = threadIdx.x + q * OBLOCK;
-                if (idx < nc * nc) sg[idx / nc][idx % nc] = gv[q];
-            }
+                for (int q = 0; q < 4; ++q) {
+                    const int idx = threadIdx.x + q * OBLOCK;
+                    if (idx < nc * nc) sg[idx / nc][idx % nc] = gv[q];
+                }
+        });
+        // nc <= 64: one wavefront holds every coefficient.
+        if (threadIdx.x >= 64) return;
+        const int k = threadIdx.x;
+        const bool live = k < nc;
+        const A ck = live ? sc[k] : A(0);
+        if (gram) {
             // Second coefficients of classical Gram-Schmidt without a second
             // pass: V^T (w - V c) = c - G c, G the Gram matrix of the unit
             // stored basis.  The update then subtracts V (c + c2) at once, in
             // registers, so no rounded intermediate w' exists.
-            for (int k = threadIdx.x; k < nc; k += OBLOCK) sc[k] = (A)st->c[k];
-            __syncthreads();
             A c2 = A(0);
-            if ((int)threadIdx.x < nc) {
+            if (live) {
                 A gc = A(0);
-                for (int l = 0; l < nc; ++l) gc += sg[threadIdx.x][l] * sc[l];
-                c2 = sc[threadIdx.x] - gc;
+#pragma unroll 8
+                for (int l = 0; l < nc; ++l) gc += sg[k][l] * sc[l];
+                c2 = ck - gc;
             }
             // c2 = c - G c corrects for G != I but not for the rounding of c
             // itself (about u_A ||w|| per coefficient, u_A the unit roundoff
@@ -328,42 +357,39 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_dot(State* st, const typename T
             // until ||w - V c|| is far under the breakdown threshold, so the
             // iteration launcher leaves the re-measuring kernel out there.
             const A ua = sizeof(A) == 8 ? A(1.1102230246251565e-16) : A(5.9604644775390625e-08);
-            const bool can_remeasure = (double)ua >= st->u_s;
-            const bool selective = st->reorth == 3 && st->mode != MODE_RESTART;
+            const bool can_remeasure = (double)ua >= u_s;
+            const bool selective = reorth == 3 && mode != MODE_RESTART;
             // ||w - V c||^2 = ||w||^2 - 2 c.c + c.(G c) tells how much the
             // first pass cancelled.
             A sel[3] = {A(0), A(0), A(0)};
             if (can_remeasure || selective) {
-                sel[0] = (int)threadIdx.x < nc ? c2 * c2 : A(0);
-                sel[1] = (int)threadIdx.x < nc ? sc[threadIdx.x] * sc[threadIdx.x] : A(0);
-                sel[2] = (int)threadIdx.x < nc ? sc[threadIdx.x] * (sc[threadIdx.x] - c2) : A(0);
-                for (int q = 0; q < 3; ++q) sel[q] = block_sum(sel[q], shd, OWAVES);
+                sel[0] = wave_sum(live ? c2 * c2 : A(0));
+                sel[1] = wave_sum(live ? ck * ck : A(0));
+                sel[2] = wave_sum(live ? ck * (ck - c2) : A(0));
             }
             const A w1 = fmax(A(0), wn - A(2) * sel[1] + sel[2]);
-            const A lim = ua / (A(100) * (A)st->u_s);
+            const A lim = ua / (A(100) * (A)u_s);
             const bool remeasure = can_remeasure && w1 < lim * lim * wn;
             // Selective: skip the correction when it is below the rounding of
             // the stored vector, ||c2|| <= u_s ||w - V c||.  The two-pass mode
             // and restart vectors always apply it.
             bool corr = true;
             if (selective) {
-                corr = sel[0] > (A)(st->u_s * st->u_s) * w1;
-                if (threadIdx.x == 0) st->wnorm2 = (double)w1;
+                corr = sel[0] > (A)(u_s * u_s) * w1;
+                if (k == 0) st->wnorm2 = (double)w1;
             }
-            if (!remeasure && (int)threadIdx.x < nc)
-                st->c2[threadIdx.x] = (double)(sc[threadIdx.x] + (corr ? c2 : A(0)));
-            if (threadIdx.x == 0) {
+            if (!remeasure && live) st->c2[k] = (double)(ck + (corr ? c2 : A(0)));
+            if (k == 0) {
                 st->second = 1;
                 st->remeasure = remeasure ? 1 : 0;
                 // alpha_j = v_j . A v_j = c_j + beta_j (v_j . v_{j-1}), with
                 // w = A v_j - beta_j v_{j-1}; the SpMV does not reduce it in
                 // these modes.
-                if (st->mode == MODE_NORMAL)
-                    st->alpha[j] = (double)(sc[j] + (j > 0 ? (A)st->beta[j] * (A)gm[j * NCMAX + (j - 1)] : A(0)));
+                if (mode == MODE_NORMAL) st->alpha[j] = (double)(sc[j] + bterm);
             }
         } else if (!upd_dot_active(st)) {  // one pass: the store kernel uses c
-            for (int k = threadIdx.x; k < nc; k += OBLOCK) st->c2[k] = st->c[k];
-            if (threadIdx.x == 0) st->second = 1;
+            if (live) st->c2[k] = (double)ck;
+            if (k == 0) st->second = 1;
         }
     }
 }
@@ -388,9 +414,7 @@ __device__ __forceinline__ void split_update(const typename Ch<P>::T (&ch)[Split
         }
     }
 #pragma unroll
-    for (int o = 1; o < CS; o <<= 1)
-#pragma unroll
-        for (int rr = 0; rr < R; ++rr) u[rr] += __shfl_xor(u[rr], o, 64);
+    for (int rr = 0; rr < R; ++rr) u[rr] = group_lane_sum<CS>(u[rr]);
 }
 
 // w' = w - V c (stored in the working precision), then c2 = V^T w' and ||w'||^2.
@@ -402,7 +426,9 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_dot(State* st, const typena
     constexpr int R = Ch<P>::R, CS = Split<P, NC>::CS, NCL = Split<P, NC>::NCL, GPW = 64 / CS;
     __shared__ A coef[NC];
     __shared__ A red[OWAVES][NC];
-    __shared__ A shd[OWAVES];
+    __shared__ A redn[OWAVES];
+    __shared__ A lout[NC];
+    __shared__ A s_tot[1];
     __shared__ A sred[OBLOCK];
     __shared__ int s_last;
     const int j = st->j;
@@ -455,11 +481,9 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_dot(State* st, const typena
             }
         }
     }
-    publish_split<NC, CS, NCL>(acc, nc, part, red);
-    nrm = block_sum(nrm, shd, OWAVES);
-    if (threadIdx.x == 0) st_dev(&part2[blockIdx.x], (double)nrm);
+    publish_split<NC, CS, NCL>(acc, nrm, nc, part, part2, red, redn);
     if (last_block(&st->ticket[TK_UPD], gridDim.x, &s_last)) {
-        const A wn = reduce_columns<NC>(part, part2, gridDim.x, nc, st->scale, st->c2, sred, shd);
+        const A wn = reduce_columns<NC>(part, part2, gridDim.x, nc, st->scale, st->c2, lout, sred, s_tot, [] {});
         if (threadIdx.x == 0) {
             st->wnorm2 = (double)wn;
             st->second = 1;
@@ -481,9 +505,10 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_store(State* st, typename T
     constexpr int R = Ch<P>::R, CS = Split<P, NC>::CS, NCL = Split<P, NC>::NCL, GPW = 64 / CS;
     __shared__ A coef[NC];
     __shared__ A red[OWAVES][NC];
-    __shared__ double gcol[NC];
-    __shared__ A sha[OWAVES];
+    __shared__ A redn[OWAVES];
+    __shared__ A gcol[NC];
     __shared__ double shd[OWAVES];
+    __shared__ A s_tot[1], s_sn[1];
     __shared__ A sred[OBLOCK];
     __shared__ int s_last, s_accept;
     // The coefficients do not depend on the step index: their loads go out
@@ -557,22 +582,38 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_store(State* st, typename T
 #pragma unroll
             for (int rr = 0; rr < R; ++rr) nrm += x[rr] * x[rr];
     }
-    if (gram) publish_split<NC, CS, NCL>(acc, nc, part, red);
-    nrm = block_sum(nrm, sha, OWAVES);
-    if (threadIdx.x == 0) st_dev(&part2[blockIdx.x], (double)nrm);
+    if constexpr (GRAM) {
+        publish_split<NC, CS, NCL>(acc, nrm, nc, part, part2, red, redn);
+    } else {
+        nrm = block_sum(nrm, redn, OWAVES);
+        if (threadIdx.x == 0) st_dev(&part2[blockIdx.x], (double)nrm);
+    }
     if (last_block(&st->ticket[TK_STORE], gridDim.x, &s_last)) {
-        const A tot = gram ? reduce_columns<NC>(part, part2, gridDim.x, nc, st->scale, gcol, sred, sha)
-                           : (A)ordered_sum_dev(part2, gridDim.x, shd);
+        // The scalars of thread 0 are loaded in the same round as the partials.
+        double alpha_j = 0.0, beta_j = 0.0, tnorm = 0.0;
+        int mode = 0;
+        if (threadIdx.x == 0) {
+            alpha_j = st->alpha[j];
+            beta_j = st->beta[j];
+            tnorm = st->tnorm;
+            mode = st->mode;
+        }
+        A tot;
+        if constexpr (GRAM)
+            tot = reduce_columns<NC>(part, part2, gridDim.x, nc, st->scale, nullptr, gcol, sred, s_tot, [] {});
+        else
+            tot = (A)ordered_sum_dev(part2, gridDim.x, shd);
         if (threadIdx.x == 0) {
             const A b = sqrt(tot);
             int accept = 0;
+            double sn = 0.0;
             if (!isfinite(b)) {
                 st->status = -7;               // LZ_ERR_NONFINITE
                 st->j = st->m;
-            } else if (st->mode == MODE_NORMAL) {
-                const double t = fabs(st->alpha[j]) + st->beta[j];
-                if (t > st->tnorm) st->tnorm = t;
-                const double tau = 100.0 * st->u_w * st->tnorm;
+            } else if (mode == MODE_NORMAL) {
+                const double t = fabs(alpha_j) + beta_j;
+                if (t > tnorm) st->tnorm = tnorm = t;
+                const double tau = 100.0 * st->u_w * tnorm;
                 if (!(b > tau) && j + 1 < st->m) {
                     // Breakdown: the Krylov space is invariant.  T gets a zero
                     // coupling and the next iteration draws a restart vector.
@@ -580,8 +621,9 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_store(State* st, typename T
                     st->restarts += 1;
                     st->beta[j + 1] = 0.0;
                 } else {
+                    sn = b > A(0) ? (double)(A(1) / b) : 0.0;
                     st->beta[j + 1] = (double)b;
-                    st->scale[j + 1] = b > A(0) ? (double)(A(1) / b) : 0.0;
+                    st->scale[j + 1] = sn;
                     st->j = j + 1;
                     accept = 1;
                 }
@@ -590,7 +632,8 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_store(State* st, typename T
                     st->status = -8;           // LZ_ERR_BREAKDOWN
                     st->j = st->m;
                 } else {
-                    st->scale[j + 1] = (double)(A(1) / b);
+                    sn = (double)(A(1) / b);
+                    st->scale[j + 1] = sn;
                     st->beta[j + 1] = 0.0;
                     st->mode = MODE_NORMAL;
                     st->j = j + 1;
@@ -598,18 +641,21 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_store(State* st, typename T
                 }
             }
             s_accept = accept;
+            s_sn[0] = (A)sn;
         }
-        __syncthreads();
-        if (gram && s_accept) {
-            // Gram entries of the unit stored vectors: column j+1 against 0..j
-            // (gcol already carries scale_k) and its own squared norm.
-            const A sn = (A)st->scale[j + 1];
-            for (int k = threadIdx.x; k < nc; k += OBLOCK) {
-                const double g = (double)((A)gcol[k] * sn);
-                gm[k * NCMAX + (j + 1)] = g;
-                gm[(j + 1) * NCMAX + k] = g;
+        if constexpr (GRAM) {
+            __syncthreads();
+            if (s_accept) {
+                // Gram entries of the unit stored vectors: column j+1 against
+                // 0..j (gcol already carries scale_k) and its own squared norm.
+                const A sn = s_sn[0];
+                for (int k = threadIdx.x; k < nc; k += OBLOCK) {
+                    const double g = (double)(gcol[k] * sn);
+                    gm[k * NCMAX + (j + 1)] = g;
+                    gm[(j + 1) * NCMAX + k] = g;
+                }
+                if (threadIdx.x == 0) gm[(j + 1) * NCMAX + (j + 1)] = (double)(tot * sn * sn);
             }
-            if (threadIdx.x == 0) gm[(j + 1) * NCMAX + (j + 1)] = (double)(tot * sn * sn);
         }
     }
 }

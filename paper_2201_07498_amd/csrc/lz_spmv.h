@@ -56,7 +56,7 @@ __device__ __forceinline__ bool last_wave(uint32_t* ticket, uint32_t count) {
         __builtin_amdgcn_s_waitcnt(0);
         t = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    t = __shfl(t, 0, 64);
+    t = (uint32_t)lane_value((int)t, 0);
     const bool last = t == count - 1u;
     if (last && (threadIdx.x & 63) == 0) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return last;
@@ -271,7 +271,7 @@ __device__ __forceinline__ void tile_sums(const TileRows& q, const AT* pw, const
         while (mask) {
             const int L = __builtin_ctzll(mask);
             mask &= mask - 1;
-            const AT ss = lds_wave_sum(pw, __shfl(b, L, 64), __shfl(e, L, 64), lane);
+            const AT ss = lds_wave_sum(pw, lane_value(b, L), lane_value(e, L), lane);
             if (lane == L) s = ss;
         }
         if (valid) {
