@@ -112,6 +112,13 @@ template <class T> __device__ __forceinline__ T wave_sum(T v) {
     return v;
 }
 
+// Largest value of the wavefront, in every lane (NaN if only NaN).
+__device__ __forceinline__ double wave_max(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+    return v;
+}
+
 // Sum over the lanes i, i + CS, i + 2 CS, ... of the wavefront (pairs at
 // distance CS, 2 CS, ... 32), valid in lanes i < CS.
 template <int CS, class T> __device__ __forceinline__ T strided_wave_sum(T v) {

@@ -14,172 +14,315 @@ constexpr int JMAX_SWEEPS = 60;
 constexpr int JBLOCK = 1024;      // Jacobi workgroup: one round is a single parallel step
 
 // ---------------------------------------------------------------- Jacobi
-// Parallel cyclic Jacobi in LDS.  Each round applies me/2 disjoint
+// Parallel cyclic Jacobi on one CU.  Each round applies half = me/2 disjoint
 // rotations chosen by the round-robin tournament ordering (me = m rounded up
-// to even; an odd m gets a zero dummy row and column that is never
-// rotated); me-1 rounds make a sweep.  Rotation (Rutishauser):
-// zeta = (t_qq - t_pp)/(2 t_pq), t = sgn(zeta)/(|zeta| + sqrt(1+zeta^2)),
-// c = 1/sqrt(1+t^2), s = t c.  A rotation is skipped when |t_pq| is
-// negligible (<= eps sqrt|t_pp t_qq| or <= eps^2 ||T||_F); the method stops
-// at a sweep without rotations (counted, not run).
+// to even; an odd m gets a zero dummy row and column that is never rotated);
+// me-1 rounds make a sweep.  Rotation (Rutishauser): zeta = (t_qq - t_pp) /
+// (2 t_pq), t = sgn(zeta)/(|zeta| + sqrt(1+zeta^2)), c = 1/sqrt(1+t^2),
+// s = t c.  A rotation is skipped when |t_pq| is negligible (<= eps
+// sqrt|t_pp t_qq| or <= eps^2 ||T||_F); the method stops at a sweep without
+// rotations (counted, not run).
 //
-// Disjoint rotations commute, so a round is one parallel step: T' = J^T T J
-// is updated as independent 2x2 blocks (rows of pair a, columns of pair b),
-// upper blocks computed and mirrored so T stays exactly symmetric, and S' = S J.
-__device__ void jacobi_core(int m, double (*T)[MMAX + 1], double (*S)[MMAX + 1], double fro, int* sweeps_out,
-                            int* rot_flag) {
-    __shared__ double rc[MMAX / 2], rs[MMAX / 2];
-    __shared__ int rp_[MMAX / 2], rq_[MMAX / 2], rr_[MMAX / 2];
-    __shared__ uint8_t pair_p[MMAX - 1][MMAX / 2], pair_q[MMAX - 1][MMAX / 2];
-    __shared__ uint8_t blk_a[MMAX / 2 * (MMAX / 2 + 1) / 2], blk_b[MMAX / 2 * (MMAX / 2 + 1) / 2];
-    const double eps = 1.1102230246251565e-16;
-    const int me = (m + 1) & ~1;
-    const int half = me / 2;
-    const int nt = blockDim.x;
-    const int nblk = half * (half + 1) / 2;
-    // Threads for the T blocks (whole wavefronts, at most half the
-    // workgroup).  Splitting pays while the remaining threads need at most two
-    // S items each (measured: m = 48 faster by 10%, m = 64 slower by 14%);
-    // otherwise 0, and every thread takes both updates in turn.
-    const int split_t = (min(nblk, nt / 2) + 63) & ~63;
-    const int split = (split_t < nt && me * half <= 2 * (nt - split_t)) ? split_t : 0;
-    // Tournament pairs of every round and the upper 2x2 block list, once.
-    for (int idx = threadIdx.x; idx < (me - 1) * half; idx += nt) {
-        const int round = idx / half, i = idx % half;
-        auto pos = [&](int k) { return k == 0 ? 0 : 1 + ((k - 1 + round) % (me - 1)); };
-        const int p = pos(i), q = pos(me - 1 - i);
-        pair_p[round][i] = (uint8_t)min(p, q);
-        pair_q[round][i] = (uint8_t)max(p, q);
+// What bounds it is the chain of me-1 rounds per sweep, each with one FP64
+// rotation, two LDS round trips and barriers; the arithmetic is small.  So a
+// round is arranged around that chain:
+//   * T is stored by tournament slot, not by index: pair i is slots i (top)
+//     and me-1-i (bottom), and after a round the contents of slot k move to
+//     slot k-1 (slot 1 to me-1, slot 0 stays).  A thread owns one 2x2 block of
+//     two pairs a < b for the whole solve: it reads the block and the two
+//     rotations at fixed addresses and writes the four results to fixed
+//     addresses of the other buffer, so no index table is looked up.
+//   * The first wavefront holds the diagonal blocks.  While the others apply
+//     round k it already computes the rotations of round k+1: the next pivot
+//     of a pair is one element of one 2x2 block after round k (four products
+//     of the old block with the two rotations), and the diagonal follows from
+//     t_pp' = t_pp - t t_pq, t_qq' = t_qq + t t_pq.  A round then costs one
+//     barrier.
+//   * S' = S J stays in registers: a half wavefront holds a row, lane i the
+//     columns of pair i, and the tournament's move is a lane shift (DPP).
+//   * The rotation is two reciprocal square roots instead of three divisions
+//     and two square roots: with d = t_qq - t_pp, r = 1/sqrt(d^2 + 4 t_pq^2),
+//     c^2 = (1 + |d| r)/2, s c = |t_pq| r; the skip test compares squares.
+//     Both need operands of bounded size, so T is scaled once by a power of
+//     two (exactly) to a norm in [1, 2).
+// Measured on MI355X, before (index tables, two barriers a round, the rotation
+// in line) -> now: m = 16 96 -> 39 us, m = 48 480 -> 150 us, m = 64 863 -> 223 us
+// (about 0.4 us a round).  One loop over the rounds for all three roles
+// instead of a loop each kept 248 us at m = 48.
+struct JacobiShared {
+    double blk[2][(MMAX / 2) * (MMAX / 2 - 1) / 2 * 4 + 4];   // 2x2 blocks of pairs a < b; the last 4 take dropped writes
+    double2 cs[2][MMAX / 2];       // (c, s) of every pair, top as p and bottom as q
+    double dg[2][MMAX];            // diagonal after the round's rotation: [2i] top, [2i+1] bottom of pair i
+    double dpre[MMAX];             // diagonal before it
+    double theta[MMAX];
+    int pend;
+};
+
+// 1/sqrt(h) to about an ulp: the hardware estimate and one third-order step.
+__device__ __forceinline__ double rsqrt_refined(double h) {
+    const double r = __builtin_amdgcn_rsq(h);
+    const double e = fma(-(h * r), r, 1.0);
+    return fma(r * e, fma(0.375, e, 0.5), r);
+}
+
+// The rotation of a pair (top p, bottom q; `flipped`: the top holds the larger
+// index, which only matters for the sign where t_pp = t_qq).  The matrix is
+// scaled to a norm in [1, 2), so the squares neither overflow nor, for a pivot
+// that is not negligible, underflow.
+__device__ __forceinline__ bool jacobi_negligible(double apq, double dd, double fro) {
+    constexpr double eps = 1.1102230246251565e-16;
+    return apq * apq <= eps * eps * fabs(dd) || fabs(apq) <= eps * eps * fro;
+}
+__device__ __forceinline__ bool jacobi_rotation(double app, double aqq, double apq, bool flipped, double fro,
+                                                double2& cs, double& app2, double& aqq2) {
+    const bool rot = !jacobi_negligible(apq, app * aqq, fro);
+    const double d = aqq - app;
+    const double r = rsqrt_refined(fma(d, d, 4.0 * (apq * apq)));
+    const double c2 = fma(0.5 * fabs(d), r, 0.5);
+    const double ci = rsqrt_refined(c2);
+    const bool neg = d == 0.0 ? flipped != (apq < 0.0) : d < 0.0;
+    const double s = ((neg ? -apq : apq) * r) * ci, t = s * ci;
+    cs = rot ? make_double2(c2 * ci, s) : make_double2(1.0, 0.0);
+    app2 = rot ? fma(-t, apq, app) : app;
+    aqq2 = rot ? fma(t, apq, aqq) : aqq;
+    return rot;
+}
+
+// Shifts by one lane of the wavefront (0 past its ends): lane i takes lane
+// i + 1, lane i - 1.
+__device__ __forceinline__ double lane_next(double x) { return dpp_move<0x130>(x); }
+__device__ __forceinline__ double lane_prev(double x) { return dpp_move<0x138>(x); }
+
+// A sweep of column rotations on the S rows of a wavefront: NS row pairs, lane
+// hl of a half wavefront holding the top and bottom columns of pair hl.
+constexpr int JS_ROWS = 5;           // row pairs per wavefront at most: 32 over at least 7 wavefronts
+template <int NS>
+__device__ __forceinline__ void jacobi_s_rounds(int rounds, int half, int hl, const JacobiShared& sh, int& buf,
+                                                double (&top)[JS_ROWS], double (&bot)[JS_ROWS]) {
+    const bool first = hl == 0, last = hl == half - 1, single = half == 1;
+    const int hc = min(hl, half - 1);
+    for (int round = 0; round < rounds; ++round) {
+        const double2 cs = sh.cs[buf][hc];
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+            const double tp = cs.x * top[q] - cs.y * bot[q], bt = cs.y * top[q] + cs.x * bot[q];
+            // The tournament's move (none for a single pair).
+            const double tn = lane_next(tp), bp = lane_prev(bt);
+            top[q] = first ? tp : (last ? bt : tn);
+            bot[q] = single ? bt : (first ? tn : bp);
+        }
+        buf ^= 1;
+        __syncthreads();
     }
-    for (int a = threadIdx.x; a < half; a += nt) {
-        const int first = a * half - a * (a - 1) / 2;      // blocks (a', b) with a' < a come first
-        for (int b = a; b < half; ++b) {
-            blk_a[first + b - a] = (uint8_t)a;
-            blk_b[first + b - a] = (uint8_t)b;
+}
+
+// Jacobi of the symmetric tridiagonal matrix diag[0..m), off[0..m-1): leaves
+// the diagonal in sh.theta and S in Sout (row-major, stride MMAX); returns the
+// sweep count, -1 past the limit.  Called by JBLOCK threads.
+__device__ __forceinline__ int jacobi_core(int m, const double* diag, const double* off, JacobiShared& sh, double* Sout) {
+    constexpr int DROP = (MMAX / 2) * (MMAX / 2 - 1) / 2 * 4;
+    const int me = (m + 1) & ~1, half = me / 2;
+    const int nblk = half * (half - 1) / 2;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    // Norm and scale, by every wavefront for itself.
+    const double dl = lane < m ? diag[lane] : 0.0, ol = lane + 1 < m ? off[lane] : 0.0;
+    const double big = fmax(fabs(dl), fabs(ol));
+    const int ex0 = __builtin_amdgcn_frexp_exp(wave_max(big));
+    const double ds = ldexp(dl, -ex0), os = ldexp(ol, -ex0);
+    const double fro0 = sqrt(wave_sum(ds * ds + 2.0 * os * os));
+    const int ex = ex0 + __builtin_amdgcn_frexp_exp(fro0) - 1;
+    const double fro = ldexp(fro0, ex0 - ex);
+    auto diag_at = [&](int i) { return i < m ? ldexp(diag[i], -ex) : 0.0; };
+    auto tri = [&](int i, int j) {
+        return i < m && j < m && abs(i - j) == 1 ? ldexp(off[min(i, j)], -ex) : 0.0;
+    };
+    auto slot = [&](int pair, int e) { return e == 0 ? pair : me - 1 - pair; };
+    auto moved = [&](int k) { return k == 0 ? 0 : (k == 1 ? me - 1 : k - 1); };
+    auto block = [&](int a, int b) { return a * (2 * half - a - 1) / 2 + (b - a - 1); };
+    // Where the element of slots u, v is stored after a round (DROP: in a
+    // diagonal block, which the first wavefront holds).
+    auto target = [&](int u, int v) {
+        const int mu = moved(u), mv = moved(v);
+        const int pu = mu < half ? mu : me - 1 - mu, eu = mu < half ? 0 : 1;
+        const int pv = mv < half ? mv : me - 1 - mv, ev = mv < half ? 0 : 1;
+        if (pu == pv) return DROP;
+        return pu < pv ? block(pu, pv) * 4 + eu * 2 + ev : block(pv, pu) * 4 + ev * 2 + eu;
+    };
+    const int twaves = (nblk + 63) / 64;                   // wavefronts 1 .. twaves: blocks; the rest: rows of S
+    const bool is_rot = wave == 0, is_blk = !is_rot && wave <= twaves;
+    const int sw = wave - 1 - twaves, nsw = JBLOCK / 64 - 1 - twaves;
+
+    // Per-role constants and state.
+    int ba = 0, bb = 0, bi = 0, dst[4] = {DROP, DROP, DROP, DROP};     // block threads
+    bool live = false;
+    int pa = 0, ea = 0, pb = 0, eb = 0, top_src = 0, bot_src = 0, piv_dst = DROP, itop = 0, ibot = 0;   // rotations
+    double app = 0.0, aqq = 0.0, apq = 0.0, pivot_left = 0.0;
+    bool rot = false;
+    double st_[JS_ROWS], sb_[JS_ROWS];                         // S rows: columns of the top and bottom of pair `lane`
+    if (is_blk) {
+        bi = tid - 64;
+        live = bi < nblk;
+        if (live) {
+            int rest = bi;
+            while (rest >= half - 1 - ba) rest -= half - 1 - ba++;
+            bb = ba + 1 + rest;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int u = slot(ba, e >> 1), v = slot(bb, e & 1);
+                dst[e] = target(u, v);
+                sh.blk[0][bi * 4 + e] = tri(u, v);
+            }
         }
     }
+    if (is_rot) {
+        live = lane < half;
+        const int i = live ? lane : 0;
+        if (half > 1) {
+            const bool last = i == half - 1;
+            pa = i == 0 ? 0 : i - 1;
+            ea = i == 0 ? 0 : 1;
+            pb = last ? half - 1 : i + 1;
+            eb = i == 0 || !last ? 0 : 1;
+            top_src = i == 0 ? 0 : (last ? 2 * (half - 1) + 1 : 2 * (i + 1));
+            bot_src = i == 0 ? 2 : 2 * (i - 1) + 1;
+        }
+        piv_dst = live ? target(slot(i, 0), slot(i, 1)) : DROP;
+        itop = i;
+        ibot = me - 1 - i;
+        app = diag_at(itop);
+        aqq = diag_at(ibot);
+        apq = tri(itop, ibot);
+        double2 cs;
+        double a2, q2;
+        rot = jacobi_rotation(app, aqq, apq, itop > ibot, fro, cs, a2, q2);
+        pivot_left = rot ? 0.0 : apq;
+        if (live) {
+            sh.cs[0][lane] = cs;
+            sh.dg[0][2 * lane] = a2;
+            sh.dg[0][2 * lane + 1] = q2;
+            sh.dpre[2 * lane] = app;
+            sh.dpre[2 * lane + 1] = aqq;
+        }
+        if (tid == 0) sh.pend = 0;
+    }
+    const int hl = lane & 31;                              // pair held by a lane of an S row
+#pragma unroll
+    for (int q = 0; q < JS_ROWS; ++q) {
+        const int r = 2 * (sw + q * nsw) + (lane >> 5);
+        st_[q] = r == hl ? 1.0 : 0.0;
+        sb_[q] = r == me - 1 - hl ? 1.0 : 0.0;
+    }
+    const int nsets = sw < 0 ? 0 : (half - sw + nsw - 1) / nsw;   // half = me/2 row pairs in all
+    const int b4 = half > 1 ? block(pa, pb) * 4 : 0;
+    if (is_rot) __builtin_amdgcn_s_setprio(3);
+
+    int buf = 0, sweeps = -1;
     __syncthreads();
-    int sweeps = -1;
     for (int sweep = 1; sweep <= JMAX_SWEEPS; ++sweep) {
         // A sweep rotates nothing exactly when every pair already passes the
         // skip test at its start (T does not change within such a sweep), so
-        // that sweep is detected here instead of being run.
-        if (threadIdx.x == 0) *rot_flag = 0;
-        __syncthreads();
-        for (int idx = threadIdx.x; idx < m * m; idx += nt) {
-            const int p = idx / m, q = idx % m;
-            if (p < q) {
-                const double apq = T[p][q];
-                if (!(fabs(apq) <= eps * sqrt(fabs(T[p][p] * T[q][q])) || fabs(apq) <= eps * eps * fro))
-                    *rot_flag = 1;
+        // that sweep is detected here instead of being run.  The layout at the
+        // start of a sweep is the identity.
+        bool pending = false;
+        if (is_rot) {
+            pending = live && rot;
+        } else if (is_blk && live) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const double dd = sh.dpre[2 * ba + (e >> 1)] * sh.dpre[2 * bb + (e & 1)];
+                pending |= !jacobi_negligible(sh.blk[buf][bi * 4 + e], dd, fro);
             }
         }
+        if (pending) sh.pend = sweep;
         __syncthreads();
-        const int pending = *rot_flag;
-        __syncthreads();
-        if (!pending) {
+        if (sh.pend != sweep) {
             sweeps = sweep;
             break;
         }
-        if (threadIdx.x == 0) *rot_flag = 0;
-        __syncthreads();
-        for (int round = 0; round < me - 1; ++round) {
-            for (int i = threadIdx.x; i < half; i += nt) {
-                const int p = pair_p[round][i], q = pair_q[round][i];
-                double c = 1.0, s = 0.0;
-                int rot = 0;
-                const double apq = T[p][q], app = T[p][p], aqq = T[q][q];
-                if (!(fabs(apq) <= eps * sqrt(fabs(app * aqq)) || fabs(apq) <= eps * eps * fro)) {
-                    const double zeta = (aqq - app) / (2.0 * apq);
-                    double t;
-                    if (fabs(zeta) > 1e150)
-                        t = 0.5 / zeta;
-                    else
-                        t = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-                    c = 1.0 / sqrt(1.0 + t * t);
-                    s = t * c;
-                    rot = 1;
-                    *rot_flag = 1;
+        // Each role runs its own loop over the rounds (the branch is uniform
+        // in a wavefront), so its addresses and registers stay put.
+        const int rounds = me - 1;
+        if (is_rot) {
+            // Next round's rotations from this round's, the old blocks and the
+            // rotated diagonal.
+            for (int round = 0; round < rounds; ++round) {
+                const int nx = buf ^ 1;
+                if (half > 1) {
+                    const double2 ca = sh.cs[buf][pa], cb = sh.cs[buf][pb];
+                    const double2 t0 = *(const double2*)&sh.blk[buf][b4], t1 = *(const double2*)&sh.blk[buf][b4 + 2];
+                    app = sh.dg[buf][top_src];
+                    aqq = sh.dg[buf][bot_src];
+                    if (live) sh.blk[nx][piv_dst] = pivot_left;
+                    const double ra0 = ea == 0 ? ca.x : ca.y, ra1 = ea == 0 ? -ca.y : ca.x;
+                    const double rb0 = eb == 0 ? cb.x : cb.y, rb1 = eb == 0 ? -cb.y : cb.x;
+                    const double u0 = fma(ra0, t0.x, ra1 * t1.x), u1 = fma(ra0, t0.y, ra1 * t1.y);
+                    apq = fma(rb0, u0, rb1 * u1);
+                    itop = itop == 0 ? 0 : (itop == rounds ? 1 : itop + 1);
+                    ibot = ibot == rounds ? 1 : ibot + 1;
+                } else {
+                    app = sh.dg[buf][0];
+                    aqq = sh.dg[buf][1];
+                    apq = pivot_left;
                 }
-                rc[i] = c;
-                rs[i] = s;
-                rp_[i] = p;
-                rq_[i] = q;
-                rr_[i] = rot;
+                double2 cs;
+                double a2, q2;
+                rot = jacobi_rotation(app, aqq, apq, itop > ibot, fro, cs, a2, q2);
+                pivot_left = rot ? 0.0 : apq;
+                if (live) {
+                    sh.cs[nx][lane] = cs;
+                    *(double2*)&sh.dg[nx][2 * lane] = make_double2(a2, q2);
+                    if (round == rounds - 1) *(double2*)&sh.dpre[2 * lane] = make_double2(app, aqq);
+                }
+                buf = nx;
+                __syncthreads();
             }
-            __syncthreads();
-            // Upper 2x2 blocks (a <= b) of J^T T J, mirrored to the lower half.
-            auto t_block = [&](int idx) {
-                const int a = blk_a[idx], b = blk_b[idx];
-                if (!rr_[a] && !rr_[b]) return;
-                const int pa = rp_[a], qa = rq_[a], pb = rp_[b], qb = rq_[b];
-                const double ca = rc[a], sa = rs[a], cb = rc[b], sb = rs[b];
-                const double t00 = T[pa][pb], t01 = T[pa][qb], t10 = T[qa][pb], t11 = T[qa][qb];
-                const double u00 = ca * t00 - sa * t10, u01 = ca * t01 - sa * t11;
-                const double u10 = sa * t00 + ca * t10, u11 = sa * t01 + ca * t11;
-                double v00 = cb * u00 - sb * u01, v01 = sb * u00 + cb * u01;
-                double v10 = cb * u10 - sb * u11, v11 = sb * u10 + cb * u11;
-                if (a == b) {
-                    v01 = 0.0;                  // the annihilated entry
-                    v10 = 0.0;
+        } else if (is_blk) {
+            for (int round = 0; round < rounds; ++round) {
+                const int nx = buf ^ 1;
+                if (live) {
+                    const double2 ca = sh.cs[buf][ba], cb = sh.cs[buf][bb];
+                    const double2 t0 = *(const double2*)&sh.blk[buf][bi * 4],
+                                  t1 = *(const double2*)&sh.blk[buf][bi * 4 + 2];
+                    const double u00 = ca.x * t0.x - ca.y * t1.x, u01 = ca.x * t0.y - ca.y * t1.y;
+                    const double u10 = ca.y * t0.x + ca.x * t1.x, u11 = ca.y * t0.y + ca.x * t1.y;
+                    double* out = sh.blk[nx];
+                    out[dst[0]] = cb.x * u00 - cb.y * u01;
+                    out[dst[1]] = cb.y * u00 + cb.x * u01;
+                    out[dst[2]] = cb.x * u10 - cb.y * u11;
+                    out[dst[3]] = cb.y * u10 + cb.x * u11;
                 }
-                T[pa][pb] = v00;
-                T[pa][qb] = v01;
-                T[qa][pb] = v10;
-                T[qa][qb] = v11;
-                if (a != b) {
-                    T[pb][pa] = v00;
-                    T[qb][pa] = v01;
-                    T[pb][qa] = v10;
-                    T[qb][qa] = v11;
-                }
-            };
-            // S' = S J, row r of the columns of pair b.
-            auto s_item = [&](int idx) {
-                const int r = idx / half, b = idx - r * half;
-                if (!rr_[b]) return;
-                const int pb = rp_[b], qb = rq_[b];
-                const double sp = S[r][pb], sq = S[r][qb];
-                S[r][pb] = rc[b] * sp - rs[b] * sq;
-                S[r][qb] = rs[b] * sp + rc[b] * sq;
-            };
-            // The two updates are independent: with enough wavefronts, the
-            // first `split` threads take the T blocks and the others the S
-            // rows, so the two run side by side.
-            if (split > 0) {
-                if ((int)threadIdx.x < split)
-                    for (int idx = threadIdx.x; idx < nblk; idx += split) t_block(idx);
-                else
-                    for (int idx = threadIdx.x - split; idx < me * half; idx += nt - split) s_item(idx);
-            } else {
-                for (int idx = threadIdx.x; idx < nblk; idx += nt) t_block(idx);
-                for (int idx = threadIdx.x; idx < me * half; idx += nt) s_item(idx);
+                buf = nx;
+                __syncthreads();
             }
-            __syncthreads();
+        } else {
+            switch (nsets) {
+                case 0:
+                    for (int round = 0; round < rounds; ++round) __syncthreads();
+                    buf ^= rounds & 1;
+                    break;
+                case 1: jacobi_s_rounds<1>(rounds, half, hl, sh, buf, st_, sb_); break;
+                case 2: jacobi_s_rounds<2>(rounds, half, hl, sh, buf, st_, sb_); break;
+                case 3: jacobi_s_rounds<3>(rounds, half, hl, sh, buf, st_, sb_); break;
+                case 4: jacobi_s_rounds<4>(rounds, half, hl, sh, buf, st_, sb_); break;
+                default: jacobi_s_rounds<JS_ROWS>(rounds, half, hl, sh, buf, st_, sb_); break;
+            }
         }
     }
-    *sweeps_out = sweeps;
-}
-
-// T (me x me, zero-padded) from a diagonal and an off-diagonal array.
-__device__ void jacobi_load_tridiag(int m, const double* diag, const double* off, int off_shift,
-                                    double (*T)[MMAX + 1], double (*S)[MMAX + 1], double* sh, double* fro) {
-    const int me = (m + 1) & ~1;
-    double f = 0.0;
-    for (int idx = threadIdx.x; idx < me * me; idx += blockDim.x) {
-        const int r = idx / me, c = idx % me;
-        double t = 0.0;
-        if (r < m && c < m) {
-            if (r == c) t = diag[r];
-            else if (c == r + 1) t = off[r + off_shift];
-            else if (r == c + 1) t = off[c + off_shift];
-        }
-        T[r][c] = t;
-        S[r][c] = r == c ? 1.0 : 0.0;
-        f += t * t;
+    __builtin_amdgcn_s_setprio(0);
+    if (is_rot && live) {
+        sh.theta[lane] = ldexp(app, ex);
+        sh.theta[me - 1 - lane] = ldexp(aqq, ex);
     }
-    *fro = sqrt(block_sum(f, sh, blockDim.x / 64));
+#pragma unroll
+    for (int q = 0; q < JS_ROWS; ++q) {
+        const int r = 2 * (sw + q * nsw) + (lane >> 5);
+        if (q < nsets && r < m && hl < half) {
+            Sout[r * MMAX + hl] = st_[q];
+            if (me - 1 - hl < m) Sout[r * MMAX + me - 1 - hl] = sb_[q];
+        }
+    }
     __syncthreads();
+    return sweeps;
 }
 
 // T from alpha_1..alpha_m and beta_2..beta_m, Jacobi, Top-K selection by
@@ -188,10 +331,7 @@ __device__ void jacobi_load_tridiag(int m, const double* diag, const double* off
 // they are enqueued), a solve that completed fewer than m steps because more
 // breakdowns occurred than the budget absorbs ends with LZ_ERR_RESTART_BUDGET.
 __global__ __launch_bounds__(JBLOCK) void k_jacobi_select(State* st, double* out_vals, int strict) {
-    __shared__ double T[MMAX][MMAX + 1];
-    __shared__ double S[MMAX][MMAX + 1];
-    __shared__ double shd[JBLOCK / 64];
-    __shared__ int rot_flag, sweeps;
+    __shared__ JacobiShared sh;
     if (st->status != 0) return;
     if (strict && st->j < st->m) {
         if (threadIdx.x == 0) st->status = -9;     // LZ_ERR_RESTART_BUDGET
@@ -203,17 +343,14 @@ __global__ __launch_bounds__(JBLOCK) void k_jacobi_select(State* st, double* out
         if (threadIdx.x == 0) st->status = -8;
         return;
     }
-    double fro;
-    jacobi_load_tridiag(m, st->alpha, st->beta, 1, T, S, shd, &fro);
-    jacobi_core(m, T, S, fro, &sweeps, &rot_flag);
-    __syncthreads();
-    for (int i = threadIdx.x; i < m; i += blockDim.x) st->theta[i] = T[i][i];
-    for (int idx = threadIdx.x; idx < m * m; idx += blockDim.x) st->S[(idx / m) * MMAX + idx % m] = S[idx / m][idx % m];
+    const int sweeps = jacobi_core(m, st->alpha, st->beta + 1, sh, st->S);
     for (int i = threadIdx.x; i < m; i += blockDim.x) {
-        const double ti = T[i][i];
+        const double ti = sh.theta[i];
+        st->theta[i] = ti;
         int rank = 0;
+#pragma unroll 8
         for (int k = 0; k < m; ++k) {
-            const double tk = T[k][k];
+            const double tk = sh.theta[k];
             rank += fabs(tk) > fabs(ti) || (fabs(tk) == fabs(ti) && (tk > ti || (tk == ti && k < i)));
         }
         if (rank < K) {
@@ -229,16 +366,9 @@ __global__ __launch_bounds__(JBLOCK) void k_jacobi_select(State* st, double* out
 
 // Standalone tridiagonal eigensolve (component entry point).
 __global__ __launch_bounds__(JBLOCK) void k_jacobi_only(const double* alpha, const double* offd, int m, State* st) {
-    __shared__ double T[MMAX][MMAX + 1];
-    __shared__ double S[MMAX][MMAX + 1];
-    __shared__ double shd[JBLOCK / 64];
-    __shared__ int rot_flag, sweeps;
-    double fro;
-    jacobi_load_tridiag(m, alpha, offd, 0, T, S, shd, &fro);
-    jacobi_core(m, T, S, fro, &sweeps, &rot_flag);
-    __syncthreads();
-    for (int i = threadIdx.x; i < m; i += blockDim.x) st->theta[i] = T[i][i];
-    for (int idx = threadIdx.x; idx < m * m; idx += blockDim.x) st->S[(idx / m) * MMAX + idx % m] = S[idx / m][idx % m];
+    __shared__ JacobiShared sh;
+    const int sweeps = jacobi_core(m, alpha, offd, sh, st->S);
+    for (int i = threadIdx.x; i < m; i += blockDim.x) st->theta[i] = sh.theta[i];
     if (threadIdx.x == 0) {
         st->sweeps = sweeps;
         st->status = sweeps < 0 ? -6 : 0;
