@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <utility>
 #include <vector>
 
@@ -130,6 +131,71 @@ Bufs resolve(const Plan& p, void* base) {
     return b;
 }
 
+// Workspaces of calls that bring none.  The device's default memory pool gives
+// every block back to the driver when the stream is next waited for, so each
+// call paid for mapping and unmapping it: 70-420 us per call for 40 MB to 1 GB
+// in a process with little memory, several milliseconds in one holding tens of
+// GB.  Blocks up to POOL_BLOCK_MAX come from a pool of the library's own (one
+// per device, created at first use) that keeps at most POOL_KEEP_BYTES of freed
+// memory and gives the rest back; 35 us per call whatever the size.  Larger
+// blocks, and allocations inside a stream capture (which become graph nodes),
+// use the default pool.  The runtime orders reuse between streams and threads.
+constexpr size_t POOL_KEEP_BYTES = (size_t)2 << 30;
+constexpr size_t POOL_BLOCK_MAX = (size_t)1 << 30;
+constexpr int POOL_MAX_DEVICES = 64;
+
+static hipMemPool_t workspace_pool() {
+    static std::mutex mu;
+    static hipMemPool_t pools[POOL_MAX_DEVICES] = {};
+    static bool tried[POOL_MAX_DEVICES] = {};
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= POOL_MAX_DEVICES) return nullptr;
+    std::lock_guard<std::mutex> lk(mu);
+    if (!tried[dev]) {
+        tried[dev] = true;
+        hipMemPoolProps props;
+        std::memset(&props, 0, sizeof(props));
+        props.allocType = hipMemAllocationTypePinned;
+        props.location.type = hipMemLocationTypeDevice;
+        props.location.id = dev;
+        hipMemPool_t pool = nullptr;
+        uint64_t keep = POOL_KEEP_BYTES;
+        if (hipMemPoolCreate(&pool, &props) != hipSuccess) {
+            (void)hipGetLastError();
+        } else if (hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipMemPoolDestroy(pool);
+        } else {
+            pools[dev] = pool;
+        }
+    }
+    return pools[dev];
+}
+
+// Stream-ordered allocation on s; freed with hipFreeAsync.
+static hipError_t workspace_alloc(void** p, size_t bytes, hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (bytes <= POOL_BLOCK_MAX && hipStreamIsCapturing(s, &cap) == hipSuccess &&
+        cap == hipStreamCaptureStatusNone) {
+        const hipMemPool_t pool = workspace_pool();
+        if (pool) {
+            if (hipMallocFromPoolAsync(p, bytes, pool, s) == hipSuccess) return hipSuccess;
+            (void)hipGetLastError();
+            (void)hipMemPoolTrimTo(pool, 0);      // make room for the default pool
+        }
+    }
+    return hipMallocAsync(p, bytes, s);
+}
+
+// Pinned host copy of the state (one per host thread, kept for the process):
+// pageable copies are staged in many small blits.
+static State* pinned_state() {
+    static thread_local State* pinned = nullptr;
+    if (!pinned && hipHostMalloc((void**)&pinned, sizeof(State), hipHostMallocDefault) != hipSuccess)
+        pinned = nullptr;
+    return pinned;
+}
+
 }  // namespace lz
 
 using namespace lz;
@@ -219,19 +285,15 @@ int run_solve(Plan p, Csr a, const lz_options& o, hipStream_t s, double* out_val
     };
     {
         if (!ws) {
-            if (hipMallocAsync(&ws, p.bytes, s) != hipSuccess) return LZ_ERR_OUT_OF_MEMORY;
+            if (workspace_alloc(&ws, p.bytes, s) != hipSuccess) return LZ_ERR_OUT_OF_MEMORY;
             owned = true;
         }
         const Bufs b = resolve(p, ws);
-        // Pinned host copy of the state (one per host thread, kept for the
-        // process): pageable copies are staged in many small blits.
-        static thread_local State* pinned = nullptr;
-        if (!pinned && hipHostMalloc((void**)&pinned, sizeof(State), hipHostMallocDefault) != hipSuccess) {
-            pinned = nullptr;
+        hst = pinned_state();
+        if (!hst) {
             rc = LZ_ERR_OUT_OF_MEMORY;
             goto done;
         }
-        hst = pinned;
         if (o.profile) {
             for (int i = 0; i < 5; ++i) LZ_HIP(hipEventCreate(&pev[i]));
             LZ_HIP(hipEventRecord(pev[0], s));
@@ -391,7 +453,7 @@ int run_solve_async(Plan p, Csr a, const lz_options& o, int budget, hipStream_t 
     int rc = LZ_OK;
     bool owned = false;
     if (!ws) {
-        if (hipMallocAsync(&ws, p.bytes, s) != hipSuccess) return LZ_ERR_OUT_OF_MEMORY;
+        if (workspace_alloc(&ws, p.bytes, s) != hipSuccess) return LZ_ERR_OUT_OF_MEMORY;
         owned = true;
     }
     {
@@ -615,45 +677,56 @@ int lz_spmv(const int64_t* csr_rowptr, const int32_t* csr_col, const void* csr_v
             int32_t precision, const void* x, void* y, void* stream) {
     if (!csr_rowptr || !csr_col || !csr_val || !x || !y) return LZ_ERR_INVALID_ARG;
     if (n < 1 || n >= (int64_t(1) << 31) || nnz < 0 || precision < 0 || precision > 2) return LZ_ERR_INVALID_ARG;
-    const Plan p = make_plan(n, nnz, 1, 1, precision);
+    // Only the state and the tile tables are needed (no basis, no report).
+    Plan p = make_plan(n, nnz, 1, 1, precision, false);
+    const size_t o_ob = align_up(sizeof(State), 256), o_tk = align_up(o_ob + (size_t)(p.n_tiles + 1) * 4, 256),
+                 o_head = align_up(o_tk + (size_t)p.n_tiles * 4, 256),
+                 o_tail = align_up(o_head + (size_t)p.n_tiles * 8, 256), bytes = o_tail + (size_t)p.n_tiles * 8;
     hipStream_t s = (hipStream_t)stream;
+    State* hst = pinned_state();
     void* ws = nullptr;
     int rc = LZ_OK;
-    State hst;
-    if (hipMalloc(&ws, p.bytes) != hipSuccess) return LZ_ERR_OUT_OF_MEMORY;
+    if (!hst || workspace_alloc(&ws, bytes, s) != hipSuccess) return LZ_ERR_OUT_OF_MEMORY;
     {
-        const Bufs b = resolve(p, ws);
+        char* c = (char*)ws;
+        Bufs b{};
+        b.st = (State*)c;
+        b.ob = (int32_t*)(c + o_ob);
+        b.tk = (uint32_t*)(c + o_tk);
+        b.head = (double*)(c + o_head);
+        b.tail = (double*)(c + o_tail);
         const Csr a{csr_rowptr, csr_col, csr_val, n, nnz};
         LZ_HIP(launch_setup(p, b, a, 0, LZ_REORTH_TWICE, LZ_REORDER_OFF, s));
         LZ_HIP(launch_spmv_plain(p, b, a, x, y, s));
-        LZ_HIP(hipMemcpyAsync(&hst, b.st, sizeof(State), hipMemcpyDeviceToHost, s));
+        LZ_HIP(hipMemcpyAsync(hst, b.st, STATE_HEAD_BYTES, hipMemcpyDeviceToHost, s));
         LZ_HIP(hipStreamSynchronize(s));
-        rc = hst.status;
+        rc = hst->status;
     }
 done:
-    (void)hipStreamSynchronize(s);
-    (void)hipFree(ws);
+    (void)hipFreeAsync(ws, s);
+    if (hipStreamSynchronize(s) != hipSuccess && rc == LZ_OK) rc = LZ_ERR_HIP;
     return rc;
 }
 
 int lz_tridiag_eig(const double* alpha, const double* offdiag, int32_t m, double* theta, double* S, int32_t* sweeps) {
     if (!alpha || !theta || !S || m < 1 || m > LZ_MAX_STEPS || (m > 1 && !offdiag)) return LZ_ERR_INVALID_ARG;
     int rc = LZ_OK;
-    char* d = nullptr;
-    State* hst = new State;
+    void* d = nullptr;
+    const hipStream_t s = nullptr;
     const size_t so = align_up(sizeof(State), 256);
-    if (hipMalloc((void**)&d, so + 2 * 64 * 8) != hipSuccess) {
-        delete hst;
-        return LZ_ERR_OUT_OF_MEMORY;
-    }
+    State* hst = pinned_state();
+    if (!hst || workspace_alloc(&d, so + 2 * 64 * 8, s) != hipSuccess) return LZ_ERR_OUT_OF_MEMORY;
     {
         State* st = (State*)d;
-        double* da = (double*)(d + so);
-        double* dof = da + 64;
-        LZ_HIP(hipMemcpy(da, alpha, m * 8, hipMemcpyHostToDevice));
-        if (m > 1) LZ_HIP(hipMemcpy(dof, offdiag, (m - 1) * 8, hipMemcpyHostToDevice));
-        LZ_HIP(launch_jacobi_only(da, dof, m, st, nullptr));
-        LZ_HIP(hipMemcpy(hst, st, sizeof(State), hipMemcpyDeviceToHost));
+        double* da = (double*)((char*)d + so);
+        // Diagonal and off-diagonal in one copy, through the pinned state.
+        double* h = hst->S;
+        for (int i = 0; i < 64; ++i) h[i] = i < m ? alpha[i] : 0.0;
+        for (int i = 0; i < 64; ++i) h[64 + i] = i + 1 < m ? offdiag[i] : 0.0;
+        LZ_HIP(hipMemcpyAsync(da, h, 2 * 64 * 8, hipMemcpyHostToDevice, s));
+        LZ_HIP(launch_jacobi_only(da, da + 64, m, st, s));
+        LZ_HIP(hipMemcpyAsync(hst, st, sizeof(State), hipMemcpyDeviceToHost, s));
+        LZ_HIP(hipStreamSynchronize(s));
         for (int i = 0; i < m; ++i) theta[i] = hst->theta[i];
         for (int r = 0; r < m; ++r)
             for (int c = 0; c < m; ++c) S[r * m + c] = hst->S[r * MMAX + c];
@@ -661,8 +734,8 @@ int lz_tridiag_eig(const double* alpha, const double* offdiag, int32_t m, double
         rc = hst->status;
     }
 done:
-    (void)hipFree(d);
-    delete hst;
+    (void)hipFreeAsync(d, s);
+    if (hipStreamSynchronize(s) != hipSuccess && rc == LZ_OK) rc = LZ_ERR_HIP;
     return rc;
 }
 
