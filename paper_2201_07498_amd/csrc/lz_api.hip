@@ -22,6 +22,18 @@ static int pow2_ge(int k) {
     return v;
 }
 
+// Placement of the tail columns' tables (off: the scan's block sums, the panel
+// offsets; the counts come first); returns their bytes.
+static size_t sweep_tail_tables(int64_t np, int64_t nb, size_t* off) {
+    const size_t segs = (size_t)(np * nb);
+    const size_t bsum = align_up((segs + 1) * 8, 256), seg = align_up(bsum + (segs / 2048 + 2) * 8, 256);
+    if (off) {
+        off[0] = bsum;
+        off[1] = seg;
+    }
+    return seg + (segs + (size_t)nb) * 4;
+}
+
 Plan make_plan(int64_t n, int64_t nnz, int32_t K, int32_t m, int32_t prec, bool relabel, int sweep) {
     Plan p;
     p.n = n;
@@ -91,6 +103,12 @@ Plan make_plan(int64_t n, int64_t nnz, int32_t K, int32_t m, int32_t prec, bool 
         p.off_swvin = take((size_t)nnz * 4);
         p.off_swtmp = take(p.sw_sort_bytes);
         p.off_swq = take(8 * 4);
+        // Panels of tail columns, where their tables fit the sort's payload.
+        const int64_t tail = n * (int64_t)vb - SW_HEAD_BYTES;
+        const int64_t np = tail > 0 ? std::min<int64_t>(ceil_div(tail, SW_PANEL_BYTES), SW_PANELS_MAX) : 0;
+        if (np > 0 && p.sw_sort_bytes >= (size_t)nnz * vb &&
+            sweep_tail_tables(np, p.sw_nb, nullptr) <= (size_t)nnz * 4)
+            p.sw_np = (int32_t)np;
     }
     p.bytes = o;
     return p;
@@ -98,7 +116,7 @@ Plan make_plan(int64_t n, int64_t nnz, int32_t K, int32_t m, int32_t prec, bool 
 
 Bufs resolve(const Plan& p, void* base) {
     char* c = (char*)base;
-    Bufs b;
+    Bufs b{};
     b.st = (State*)(c + p.off_state);
     b.V = c + p.off_V;
     b.w = c + p.off_w;
@@ -128,6 +146,15 @@ Bufs resolve(const Plan& p, void* base) {
     b.swvin = p.sweep ? (uint32_t*)(c + p.off_swvin) : nullptr;
     b.swtmp = p.sweep ? c + p.off_swtmp : nullptr;
     b.swq = p.sweep ? (uint32_t*)(c + p.off_swq) : nullptr;
+    if (p.sw_np > 0) {
+        size_t off[2];
+        (void)sweep_tail_tables(p.sw_np, p.sw_nb, off);
+        b.swtcol = (uint16_t*)b.swsrc;
+        b.swxg = b.swtmp;
+        b.swpre = (uint64_t*)b.swvin;
+        b.swbsum = (uint64_t*)((char*)b.swvin + off[0]);
+        b.swseg = (uint32_t*)((char*)b.swvin + off[1]);
+    }
     return b;
 }
 

@@ -62,6 +62,12 @@ static_assert((int64_t)SW_W * 4096 <= (int64_t(1) << SW_POSBITS) && (4096 << SW_
 constexpr int64_t SWEEP_AUTO_MIN_N = int64_t(1) << 22;
 constexpr uint64_t SWEEP_AUTO_MIN_X_BYTES = uint64_t(1) << 26;
 
+// Tail columns of the sweep blocks: x past its first SW_HEAD_BYTES, cut into at
+// most SW_PANELS_MAX panels that fit the LDS of a CU (see k_sweep_tail).
+constexpr int64_t SW_HEAD_BYTES = int64_t(4) << 20;
+constexpr int SW_PANEL_BYTES = 128 << 10;
+constexpr int SW_PANELS_MAX = 512;
+
 enum Mode { MODE_NORMAL = 0, MODE_RESTART = 1 };
 
 // Tickets of the "last workgroup reduces" pattern, one per kernel kind.
@@ -132,6 +138,7 @@ struct Plan {
     int64_t sw_nb = 0;          // sweep blocks
     int64_t sw_items = 0;       // items per sweep block (SW_W * sweep_rows)
     size_t sw_sort_bytes = 0;   // scratch of the segmented sort
+    int32_t sw_np = 0;          // panels of tail columns (0: every gather in the sweep itself)
     Ooc* ooc = nullptr;         // non-null: the matrix entries stay in host memory
     int64_t n_tiles = 0;
     size_t off_state = 0, off_V = 0, off_w = 0, off_part = 0, off_part2 = 0, off_scan = 0, off_bsum = 0,
@@ -200,6 +207,16 @@ struct Bufs {
     uint32_t* swsrc;
     uint32_t* swvin;
     void* swtmp;
+    // Arrays of the tail columns (Plan.sw_np > 0), in the place of scratch
+    // that the sort is done with: the tail entries' columns within their panel
+    // (swsrc), their entries of x (swtmp), and in swvin the entry counts of
+    // panels and blocks (scanned; the total after the last), the scan's block
+    // sums and the panels' offsets in the blocks.
+    uint16_t* swtcol;
+    void* swxg;
+    uint64_t* swpre;
+    uint64_t* swbsum;
+    uint32_t* swseg;
     uint32_t* swq;     // per-XCD work counters of the sweep fill (8), zeroed by the block-table kernel
 };
 Bufs resolve(const Plan& p, void* base);
@@ -246,6 +263,9 @@ bool host_relabel_decision(const int64_t* rowptr_host, int64_t n, int64_t nnz, i
 // device chose PACK_SWEEP (the sort then sees empty blocks).
 void launch_sweep_blocks(const Plan& p, const Bufs& b, hipStream_t s);
 hipError_t launch_sweep_sort(const Plan& p, const Bufs& b, hipStream_t s);
+// Exclusive scan of x[0..n) in place if *gate is set (three kernels); bsum
+// holds n / 2048 + 2 sums.
+void launch_scan(const int32_t* gate, uint64_t* x, int64_t n, uint64_t* bsum, hipStream_t s);
 hipError_t launch_finish(const Plan& p, const Bufs& b, const Csr& a, double* out_vals,
                          double* out_vecs, int report, hipStream_t s);
 // Copies the state into a device-resident lz_report (stream-ordered calls).

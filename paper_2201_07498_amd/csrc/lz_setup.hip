@@ -199,7 +199,7 @@ __global__ __launch_bounds__(BLOCK) void k_scan_apply(const int32_t* gate, uint6
         }
 }
 
-static void scan(const int32_t* gate, uint64_t* x, int64_t n, uint64_t* bsum, hipStream_t s) {
+void launch_scan(const int32_t* gate, uint64_t* x, int64_t n, uint64_t* bsum, hipStream_t s) {
     const int64_t nb = std::max<int64_t>(1, (n + SCAN_TILE - 1) / SCAN_TILE);
     hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(BLOCK), 0, s, gate, x, n, bsum);
     hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(BLOCK), 0, s, gate, bsum, nb);
@@ -592,11 +592,11 @@ hipError_t launch_setup(const Plan& p, const Bufs& b, const Csr& a, uint64_t see
     if (reorder != LZ_REORDER_OFF) {
         const int64_t nch = (n + CHR - 1) / CHR;
         hipLaunchKernelGGL(k_rl_hist, dim3((unsigned)nch), dim3(BLOCK), 0, s, b.st, a.rowptr, n, nch, b.scan);
-        scan(gate, b.scan, NKEY * nch, b.bsum, s);
+        launch_scan(gate, b.scan, NKEY * nch, b.bsum, s);
         hipLaunchKernelGGL(k_rl_rank, dim3((unsigned)nch), dim3(BLOCK), 0, s, b.st, a.rowptr, n, nch, b.scan,
                            b.perm, b.iperm);
         hipLaunchKernelGGL(k_rl_rowlen, dim3(g), dim3(BLOCK), 0, s, b.st, a.rowptr, n, b.perm, b.rp2, nnz);
-        scan(gate, (uint64_t*)b.rp2, n, b.bsum, s);
+        launch_scan(gate, (uint64_t*)b.rp2, n, b.bsum, s);
     }
     hipLaunchKernelGGL(k_setup_tiles, dim3(g), dim3(BLOCK), 0, s, b.st, n, p.n_tiles, b.ob, b.tk);
     if (reorder != LZ_REORDER_OFF) {

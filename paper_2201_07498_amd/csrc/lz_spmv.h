@@ -31,6 +31,8 @@
 //   fin(r, s)    a split row's whole sum, from the finalising wavefront.
 #pragma once
 
+#include <type_traits>
+
 #include "lz_device.h"
 
 namespace lz {
@@ -406,27 +408,61 @@ struct SweepArgs {
     const int32_t* ob;    // first owned row of every block (nb + 1)
     const int64_t* e;     // first entry of every block (nb + 1)
     const int32_t* col;   // columns, column order within each block
-    const uint16_t* rl;   // row of each entry relative to ob[b]
-    const void* val;
+    const uint16_t* rl;   // row of each entry relative to ob[b] (at sweep_place)
+    const void* val;      // values (at sweep_place)
     int64_t nb;
+    // Tail columns (np > 0): entries seg[b] .. seg[np * nb + b] - 1 of block b
+    // gather from xg, the tail entries' values of x in the order k_sweep_tail
+    // leaves them, and their column words are positions in xg.
+    const uint32_t* seg;
+    const void* xg;
+    int np;
 };
-// Entries per lane in flight.  R-MAT 26 step SpMV with 8 / 12 / 16: FP64
-// 14.32 / 13.77 / 13.78 ms, FP32 12.49 / 12.40 / 12.45, BF16 9.66 / 9.58 /
-// 9.67 (the LDS of the row sums already limits occupancy to two wavefronts
-// per SIMD, so the extra registers cost nothing).
+// The tail entries panel by panel, block by block: columns within the panel,
+// and the start of panel p at pre[p * nb] (the total at pre[np * nb]).
+struct TailArgs {
+    const uint16_t* col;
+    const uint64_t* pre;
+    int64_t nb;
+    int np;
+};
+// Entries per lane and round.  Measured with 8 / 12 / 16, step SpMV of R-MAT 25
+// FP32: 3.63 / 3.56 / 3.57 ms (the LDS of the row sums limits occupancy to two
+// wavefronts per SIMD, so registers cost nothing).
 constexpr int SW_U = 12;
-// Rows per block, wavefronts per workgroup (their row sums fill the LDS, so
-// one workgroup per CU) and grid, per storage precision.  Measured on
-// MI355X, R-MAT scale 26 step SpMV (rows/wavefronts/grid): FP64 4096/4/1024
-// 14.3 ms, 4096/4/512 15.0, 2048/8/512 16.5; FP32 2048/8/512 12.4 ms,
-// 4096/4/1024 12.6, 4096/4/512 13.0, 2048/4/512 13.2; BF16 2048/8/512
-// 9.7 ms, 2048/4/512 10.3, 4096/4/1024 11.7, 4096/4/512 12.3.
-template <int P> struct SweepShape { static constexpr int ROWS = 2048, WAVES = 8, GRID = 512; };
-template <> struct SweepShape<0> { static constexpr int ROWS = 4096, WAVES = 4, GRID = 1024; };
+// Rows per block and wavefronts per workgroup (their row sums fill the LDS, so
+// one workgroup per CU), per storage precision.  Measured on MI355X, R-MAT
+// scale 26 step SpMV without the tail pass (rows/wavefronts/grid): FP64
+// 4096/4/1024 14.3 ms, 2048/8/512 16.5; FP32 2048/8/512 12.4 ms, 4096/4/1024
+// 12.6, 2048/4/512 13.2; BF16 2048/8/512 9.7 ms, 2048/4/512 10.3, 4096/4/1024
+// 11.7.
+template <int P> struct SweepShape { static constexpr int ROWS = 2048, WAVES = 8; };
+template <> struct SweepShape<0> { static constexpr int ROWS = 4096, WAVES = 4; };
+constexpr int SWEEP_GRID_MAX = 16384;
 static_assert(SweepShape<0>::ROWS == sweep_rows(0) && SweepShape<1>::ROWS == sweep_rows(1) &&
                   SweepShape<2>::ROWS == sweep_rows(2) && SweepShape<0>::ROWS <= SW_ROWS_MAX,
               "sweep block rows");
 
+// Where rows and values of entry k of the block with entries [e0, e1) are
+// stored: a group of 256 entries (k / 256) wholly inside the block holds the
+// four entries i, i + 64, i + 128, i + 192 of a lane side by side, so that a
+// lane reads them with one load; the block's first and last, partial groups
+// are stored in order.
+__device__ __forceinline__ int64_t sweep_place(int64_t k, int64_t e0, int64_t e1) {
+    const int64_t g = k & ~int64_t(255);
+    const int o = (int)(k & 255);
+    return g >= e0 && g + 256 <= e1 ? g + (o & 63) * 4 + (o >> 6) : k;
+}
+
+// What bounds it: beside the streams (10 bytes an entry in FP32), the L1.  In
+// row order every gather of a rarely used column fetched a line of its own
+// from beyond L2; with those columns fetched ahead (k_sweep_tail) the rest of
+// x fits L2, and the L1 is busy or held up by lines in flight for 70 % of the
+// time.  Step SpMV of R-MAT 25 FP32, all gathers in the sweep -> tail columns
+// ahead, rounds pipelined and one block per wavefront: 5.07 -> 3.28 ms (0.39
+// of it k_sweep_tail); a head of 1, 2, 4, 8 MiB gave 3.63, 3.57, 3.60, 3.90 ms
+// on the same grid, a grid of 512, 1024, 2048 workgroups and one per eight
+// blocks 3.56, 3.56, 3.34, 3.28 ms.
 // Wavefront per sweep block, blocks dealt round-robin over all wavefronts
 // of the grid.  A block zeroes its row sums in LDS (owned rows, then the row
 // continuing past it), walks its entries in stored (column) order, 64 * SW_U
@@ -442,11 +478,15 @@ static_assert(SweepShape<0>::ROWS == sweep_rows(0) && SweepShape<1>::ROWS == swe
 // publishes a tail piece, and the last piece to arrive on the owner's ticket
 // adds them in block order.  Each wavefront has its own sums and adds into
 // them in a fixed instruction order, so the result does not depend on timing.
-template <class VT, int NW, int ROWS, class Pre, class Row, class Piece, class Fin>
+template <class VT, int NW, int ROWS, bool TAIL, bool OFF32, class Pre, class Row, class Piece, class Fin>
 __device__ __forceinline__ void spmv_sweep(const SweepArgs& sw, const int64_t* __restrict__ rp,
                                            const VT* __restrict__ x, int64_t n, uint32_t* tk, double* head,
                                            double* tail, Pre&& pre, Row&& row, Piece&& piece, Fin&& fin) {
     constexpr int64_t ITEMS = (int64_t)SW_W * ROWS;
+    constexpr int STEP = 64 * SW_U;
+    static_assert(SW_U % 4 == 0, "whole groups of 256 entries per round");
+    typedef uint16_t us4 __attribute__((ext_vector_type(4)));      // four entries of a lane
+    typedef VT V4 __attribute__((ext_vector_type(4)));
     __shared__ double ys_all[NW][ROWS + 1];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -454,32 +494,110 @@ __device__ __forceinline__ void spmv_sweep(const SweepArgs& sw, const int64_t* _
     const int32_t* __restrict__ col = sw.col;
     const uint16_t* __restrict__ rlv = sw.rl;
     const VT* __restrict__ val = (const VT*)sw.val;
+    const VT* __restrict__ xg = (const VT*)sw.xg;
     const int64_t nw = (int64_t)gridDim.x * NW;
     for (int64_t b = (int64_t)blockIdx.x * NW + w; b < sw.nb; b += nw) {
         const int64_t r0 = sw.ob[b], r1 = sw.ob[b + 1];
         const int64_t e0 = sw.e[b], e1 = sw.e[b + 1];
         const int nown = (int)(r1 - r0);
+        // Entries [et, ft) are tail entries.
+        const int64_t et = TAIL ? e0 + sw.seg[b] : e1, ft = TAIL ? e0 + sw.seg[sw.np * sw.nb + b] : e1;
         for (int i = lane; i <= nown; i += 64) ys[i] = 0.0;
         wave_sync();
-        for (int64_t base = e0; base < e1; base += 64 * SW_U) {
-            int c[SW_U], r[SW_U];
-            VT v[SW_U];
+        // Whole rounds of 64 * SW_U entries, pipelined over three of them:
+        // while the products of one are added, the gathers of the next and the
+        // streams of the one after that are in flight.  The steady loop has no
+        // branch but its exits, and a round takes 18 (FP64 21) stream loads, so
+        // that all of it fits the 63 loads a wavefront can wait on by count.
+        struct Round {
+            int c[SW_U];
+            us4 r[SW_U / 4];
+            V4 v[SW_U / 4];
+            VT g[SW_U];
+        };
+        auto load = [&](Round& t, int64_t at) {
+            const int32_t* cb = col + at;
+            const uint16_t* rb = rlv + at;
+            const VT* vb = val + at;
 #pragma unroll
-            for (int q = 0; q < SW_U; ++q) {
-                const int64_t k = min(base + q * 64 + lane, e1 - 1);
-                c[q] = __builtin_nontemporal_load(col + k);
-                r[q] = (int)__builtin_nontemporal_load(rlv + k);
-                v[q] = __builtin_nontemporal_load(val + k);
+            for (int q = 0; q < SW_U; ++q) t.c[q] = __builtin_nontemporal_load(cb + (uint32_t)(q * 64 + lane));
+#pragma unroll
+            for (int q = 0; q < SW_U / 4; ++q) {
+                t.r[q] = __builtin_nontemporal_load((const us4*)(rb + (uint32_t)(q * 256 + lane * 4)));
+                t.v[q] = __builtin_nontemporal_load((const V4*)(vb + (uint32_t)(q * 256 + lane * 4)));
             }
+        };
+        auto from = [](const VT* base, int c) {
+            return OFF32 ? *(const VT*)((const char*)base + (uint32_t)c * (uint32_t)sizeof(VT)) : base[(uint32_t)c];
+        };
+        auto gather = [&](Round& t, int64_t at) {
+            const int lo = TAIL ? (int)min<int64_t>(et - at, STEP) : 0, hi = TAIL ? (int)min<int64_t>(ft - at, STEP) : 0;
 #pragma unroll
             for (int q = 0; q < SW_U; ++q) {
-                const bool warm = (uint32_t)c[q] < GATHER_WARM_BYTES / (uint32_t)sizeof(VT);
-                const VT xv = warm ? x[c[q]] : __builtin_nontemporal_load(x + c[q]);
-                if (base + q * 64 + lane < e1)
-                    __hip_atomic_fetch_add(ys + min(r[q], nown), to_a(v[q], 0.0) * to_a(xv, 0.0),
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                const int i = q * 64 + lane;
+                t.g[q] = from(TAIL && i >= lo && i < hi ? xg : x, t.c[q]);
+            }
+        };
+        auto add = [&](const Round& t) {
+#pragma unroll
+            for (int q = 0; q < SW_U; ++q)
+                __hip_atomic_fetch_add(ys + min((int)t.r[q / 4][q % 4], nown),
+                                       to_a(VT(t.v[q / 4][q % 4]), 0.0) * to_a(t.g[q], 0.0), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WAVEFRONT);
+        };
+        // Entries [k0, k1) outside whole rounds.
+        auto sweep_part = [&](int64_t k0, int64_t k1) {
+            for (int64_t at = k0; at < k1; at += STEP) {
+                const int left = (int)min<int64_t>(k1 - at, STEP);
+                int c[SW_U], r[SW_U];
+                VT v[SW_U], g[SW_U];
+#pragma unroll
+                for (int q = 0; q < SW_U; ++q) {
+                    const int64_t k = at + min(q * 64 + lane, left - 1), kp = sweep_place(k, e0, e1);
+                    c[q] = __builtin_nontemporal_load(col + k);
+                    r[q] = (int)__builtin_nontemporal_load(rlv + kp);
+                    v[q] = __builtin_nontemporal_load(val + kp);
+                }
+#pragma unroll
+                for (int q = 0; q < SW_U; ++q) {
+                    const int64_t k = at + min(q * 64 + lane, left - 1);
+                    g[q] = from(TAIL && k >= et && k < ft ? xg : x, c[q]);
+                }
+#pragma unroll
+                for (int q = 0; q < SW_U; ++q)
+                    if (q * 64 + lane < left)
+                        __hip_atomic_fetch_add(ys + min(r[q], nown), to_a(v[q], 0.0) * to_a(g[q], 0.0),
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+            }
+        };
+        // Rounds start at multiples of 256 entries, so that no load shares a
+        // cache line with the next: a load that hits a line still in flight
+        // holds up the L1 until the line has come.
+        const int64_t a0 = min((e0 + 255) & ~int64_t(255), e1);
+        const int rounds = (int)((e1 - a0) / STEP);
+        sweep_part(e0, a0);
+        if (rounds > 0) {
+            auto at = [&](int i) { return a0 + (int64_t)min(i, rounds - 1) * STEP; };
+            Round ra, rb, rc;
+            load(ra, at(0));
+            gather(ra, at(0));
+            load(rb, at(1));
+            for (int i = 0;;) {
+                gather(rb, at(i + 1));
+                load(rc, at(i + 2));
+                add(ra);
+                if (++i == rounds) break;
+                gather(rc, at(i + 1));
+                load(ra, at(i + 2));
+                add(rb);
+                if (++i == rounds) break;
+                gather(ra, at(i + 1));
+                load(rb, at(i + 2));
+                add(rc);
+                if (++i == rounds) break;
             }
         }
+        sweep_part(a0 + (int64_t)rounds * STEP, e1);
         wave_sync();
         const bool split_head = nown > 0 && rp[r0] < e0;
         double head_s = 0.0;

@@ -27,6 +27,10 @@ constexpr int XC_BYTES = 64 * 1024;
 template <bool F> struct Epi { using T = double; };
 template <> struct Epi<true> { using T = float; };
 
+// Sweep-block forms of the step: every gather in the sweep, or the tail
+// columns fetched ahead (k_sweep_tail).
+enum SweepForm { SWEEP_NO = 0, SWEEP_PLAIN = 1, SWEEP_TAIL = 2 };
+
 // The solve's matrix is the caller's CSR (rp_a, col_a, val_a) or its
 // relabelled copy (rp_b, ...), as the setup kernels decided.  Both come in as
 // kernel arguments, so the compiler knows them to be global memory and emits
@@ -39,7 +43,7 @@ template <> struct Epi<true> { using T = float; };
 // and the last launch reduces all of them.  A device-resident matrix is one
 // slab of all tiles.  With SWEEP the relabelled matrix is walked in its
 // sweep blocks (sw) instead of tiles.
-template <int P, int NW, bool XCACHE, bool F = false, bool OFF32 = false, bool SWEEP = false>
+template <int P, int NW, bool XCACHE, bool F = false, bool OFF32 = false, int SWEEP = SWEEP_NO>
 __global__ __launch_bounds__(NW * 64) void k_spmv_step(State* st, const typename Tr<P>::V* __restrict__ Vb,
                                                        typename Tr<P>::W* __restrict__ w, int64_t n, int64_t nnz,
                                                        int64_t ld, int64_t n_tiles, const int32_t* __restrict__ ob,
@@ -104,9 +108,9 @@ __global__ __launch_bounds__(NW * 64) void k_spmv_step(State* st, const typename
         __syncthreads();
     }
     const int packing = rl ? st->packed : PACK_NONE;
-    if constexpr (SWEEP) {
+    if constexpr (SWEEP != SWEEP_NO) {
         if (packing != PACK_SWEEP) return;
-        spmv_sweep<VT, NW, SweepShape<P>::ROWS>(sw, rp, x, n, tk, head, tail, pre, row, piece, fin);
+        spmv_sweep<VT, NW, SweepShape<P>::ROWS, SWEEP == SWEEP_TAIL, OFF32>(sw, rp, x, n, tk, head, tail, pre, row, piece, fin);
     } else if (packing == PACK_GROUP) {
         spmv_groups<VT, AT, NW, XCACHE, OFF32>(rp, col, val, x, xs, hn, n, nnz, n_tiles, ob, tk, head, tail, pre,
                                                row, piece, fin);
@@ -129,6 +133,69 @@ __global__ __launch_bounds__(NW * 64) void k_spmv_step(State* st, const typename
                 st->second = 1;
             }
         }
+    }
+}
+
+// The entries of x that the tail entries of the sweep blocks gather, ahead of
+// the sweep: xg[v] = x[tail column of entry v], panel by panel.  A workgroup
+// takes an equal share of the entries in that order and holds the panel of x
+// they fall in in its LDS, so x is read in whole lines and every other access
+// is a stream (2 bytes read, one entry written), which bounds it: R-MAT 25
+// FP32, 215 million tail entries, 0.39 ms (3.3 TB/s).  Gathering them from L2
+// instead, in 4 MiB panels scattered to their stored positions, took 2.1 ms.
+constexpr int SWT_GRID = 256, SWT_THREADS = 1024, SWT_U = 8;
+template <class VT>
+__global__ __launch_bounds__(SWT_THREADS) void k_sweep_tail(const State* st, const VT* __restrict__ Vb, int64_t ld,
+                                                            TailArgs ta, VT* __restrict__ xg) {
+    constexpr int COLS = SW_PANEL_BYTES / (int)sizeof(VT);
+    constexpr int64_t HEAD = SW_HEAD_BYTES / (int64_t)sizeof(VT);
+    __shared__ __align__(16) VT xs[COLS];
+    __shared__ int64_t start[SW_PANELS_MAX + 1];
+    if (st->status != 0 || !st->reordered || st->packed != PACK_SWEEP) return;
+    const int j = st->j;
+    if (j >= st->m || st->mode == MODE_RESTART) return;
+    const VT* __restrict__ x = Vb + (int64_t)j * ld;
+    const int np = ta.np, t = threadIdx.x;
+    for (int i = t; i <= np; i += SWT_THREADS) start[i] = (int64_t)ta.pre[i * ta.nb];
+    __syncthreads();
+    const int64_t total = start[np];
+    // Shares start at multiples of 64 entries.
+    auto share = [&](int64_t i) { return min<int64_t>(total, (total * i / gridDim.x + 63) & ~int64_t(63)); };
+    int64_t v = share(blockIdx.x);
+    const int64_t v1 = (int)blockIdx.x == (int)gridDim.x - 1 ? total : share(blockIdx.x + 1);
+    int p = 0;
+    for (int step = SW_PANELS_MAX / 2; step > 0; step >>= 1)
+        if (p + step < np && start[p + step] <= v) p += step;
+    while (v < v1) {
+        // Panel p: the last that starts at or before v.
+        while (p + 1 < np && start[p + 1] <= v) ++p;
+        const int64_t end = min(start[p + 1], v1);
+        const int64_t c0 = HEAD + (int64_t)p * COLS;
+        __syncthreads();
+        constexpr int PER16 = 16 / (int)sizeof(VT), ROUNDS = COLS / (PER16 * SWT_THREADS);
+        uint4 buf[ROUNDS];
+#pragma unroll
+        for (int q = 0; q < ROUNDS; ++q) {
+            const int64_t c = c0 + (int64_t)(q * SWT_THREADS + t) * PER16;
+            buf[q] = c < ld ? *(const uint4*)(x + c) : make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < ROUNDS; ++q) *(uint4*)&xs[(q * SWT_THREADS + t) * PER16] = buf[q];
+        __syncthreads();
+        for (; v < end; v += SWT_THREADS * SWT_U) {
+            const int cnt = (int)min<int64_t>(end - v, SWT_THREADS * SWT_U);
+            const uint16_t* cb = ta.col + v;
+            VT* gb = xg + v;
+            uint16_t c[SWT_U];
+#pragma unroll
+            for (int q = 0; q < SWT_U; ++q)
+                c[q] = __builtin_nontemporal_load(cb + (uint32_t)min(q * SWT_THREADS + t, cnt - 1));
+#pragma unroll
+            for (int q = 0; q < SWT_U; ++q)
+                if (q * SWT_THREADS + t < cnt)
+                    __builtin_nontemporal_store(xs[c[q]], gb + (uint32_t)(q * SWT_THREADS + t));
+        }
+        v = end;
     }
 }
 
@@ -163,11 +230,27 @@ static void spmv_step_p(const Plan& p, const Bufs& b, const Csr& a, hipStream_t 
         // Relabelled matrix: its sweep blocks; the caller's order takes the
         // tiles below (the x-head variant is not used with sweep blocks).
         using SS = SweepShape<P>;
-        hipLaunchKernelGGL((k_spmv_step<P, SS::WAVES, false, F, false, true>), dim3(SS::GRID), dim3(SS::WAVES * 64),
-                           0, s, b.st,
-                           (const VT*)b.V, (WT*)b.w, a.n, a.nnz, p.ld, p.n_tiles, b.ob, b.tk, b.head, b.tail,
-                           b.part2, a.rowptr, a.col, a.val, b.rp2, b.col2, b.val2, (int64_t)0, p.n_tiles, 0, 1, 1,
-                           SweepArgs{b.swob, b.swe, b.swcol, b.swrl, b.swval, p.sw_nb});
+        const SweepArgs sw{b.swob, b.swe, b.swcol, b.swrl, b.swval, p.sw_nb, b.swseg, b.swxg, p.sw_np};
+        if (p.sw_np > 0)
+            hipLaunchKernelGGL(k_sweep_tail<VT>, dim3(SWT_GRID), dim3(SWT_THREADS), 0, s, b.st, (const VT*)b.V, p.ld,
+                               TailArgs{b.swtcol, b.swpre, p.sw_nb, p.sw_np}, (VT*)b.swxg);
+        // One block per wavefront: the blocks' costs differ (full ones first), and
+        // a workgroup that ends makes room for the next.
+        const int64_t gs = std::min<int64_t>((p.sw_nb + SS::WAVES - 1) / SS::WAVES, SWEEP_GRID_MAX);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)gs), dim3(SS::WAVES * 64), 0, s, b.st, (const VT*)b.V, (WT*)b.w,
+                               a.n, a.nnz, p.ld, p.n_tiles, b.ob, b.tk, b.head, b.tail, b.part2, a.rowptr, a.col,
+                               a.val, b.rp2, b.col2, b.val2, (int64_t)0, p.n_tiles, 0, 1, 1, sw);
+        };
+        const bool tail32 = off32 && (uint64_t)p.nnz * sizeof(VT) <= (uint64_t(1) << 32);
+        if (p.sw_np > 0 && tail32)
+            launch(k_spmv_step<P, SS::WAVES, false, F, true, SWEEP_TAIL>);
+        else if (p.sw_np > 0)
+            launch(k_spmv_step<P, SS::WAVES, false, F, false, SWEEP_TAIL>);
+        else if (off32)
+            launch(k_spmv_step<P, SS::WAVES, false, F, true, SWEEP_PLAIN>);
+        else
+            launch(k_spmv_step<P, SS::WAVES, false, F, false, SWEEP_PLAIN>);
     }
     if constexpr (P != 0) {
         if (p.xcache && !p.sweep) {

@@ -19,6 +19,9 @@
 // those words as values (rocPRIM, one segment per block, keys sorted on the
 // bits above the line offset so that entries of one line keep their row
 // order); then the rows and, gathered by the sorted positions, the values.
+// Entries of x past its first SW_HEAD_BYTES are not gathered by the sweep: a
+// pass before it lays them out in the order of the tables built here (tail
+// columns: panels of x that fit LDS; see k_sweep_tail).
 #include <cstring>
 
 #include <rocprim/device/device_segmented_radix_sort.hpp>
@@ -73,6 +76,76 @@ __global__ __launch_bounds__(BLOCK) void k_sw_blocks(const State* st, const int6
     }
 }
 
+// Panel of a column: -1 in the head of x, 0 .. np - 1, np past the last panel.
+template <class VT> __device__ __forceinline__ int sweep_panel(int32_t c, int np) {
+    constexpr int64_t HEAD = SW_HEAD_BYTES / (int64_t)sizeof(VT), COLS = SW_PANEL_BYTES / (int64_t)sizeof(VT);
+    return c < HEAD ? -1 : (int)min<int64_t>((c - HEAD) / COLS, np);
+}
+
+// Offsets of the tail panels in every block: seg[p * nb + b] = entries of block
+// b before panel p (p <= np).  Columns ascend by panel within a block, so every
+// entry that opens a panel writes the offsets of the panels since the one
+// before it; one workgroup per block.
+template <class VT>
+__global__ __launch_bounds__(BLOCK) void k_sw_panels(const State* st, int64_t nb, const int64_t* __restrict__ e,
+                                                     const int32_t* __restrict__ col, int np,
+                                                     uint32_t* __restrict__ seg) {
+    if (st->status != 0 || !st->reordered || st->packed != PACK_SWEEP) return;
+    for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
+        const int64_t e0 = e[b];
+        const int cnt = (int)(e[b + 1] - e0);
+        const int32_t* c = col + e0;
+        for (int k = threadIdx.x; k < cnt; k += BLOCK) {
+            const int p = sweep_panel<VT>(c[k], np), before = k > 0 ? sweep_panel<VT>(c[k - 1], np) : -1;
+            for (int q = before + 1; q <= p; ++q) seg[q * nb + b] = (uint32_t)k;
+        }
+        const int last = cnt > 0 ? sweep_panel<VT>(c[cnt - 1], np) : -1;
+        for (int q = last + 1 + (int)threadIdx.x; q <= np; q += BLOCK) seg[q * nb + b] = (uint32_t)cnt;
+    }
+}
+
+// Entry counts of the segments (panel p of block b), to be scanned.
+__global__ __launch_bounds__(BLOCK) void k_sw_seg_len(const State* st, int64_t nb, int64_t segs,
+                                                      const uint32_t* __restrict__ seg, uint64_t* __restrict__ pre) {
+    if (st->status != 0 || !st->reordered || st->packed != PACK_SWEEP) return;
+    for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < segs; i += (int64_t)gridDim.x * BLOCK)
+        pre[i] = seg[i + nb] - seg[i];
+}
+
+// The tail entries panel by panel, block by block: their columns within the
+// panel; their stored column words become their positions in that order.
+template <class VT>
+__global__ __launch_bounds__(BLOCK) void k_sw_tail_fill(const State* st, int64_t nb, const int64_t* __restrict__ e,
+                                                        const uint32_t* __restrict__ seg, int np, uint64_t* pre,
+                                                        int32_t* __restrict__ col, uint16_t* __restrict__ tcol) {
+    constexpr int64_t HEAD = SW_HEAD_BYTES / (int64_t)sizeof(VT), COLS = SW_PANEL_BYTES / (int64_t)sizeof(VT);
+    if (st->status != 0 || !st->reordered || st->packed != PACK_SWEEP) return;
+    for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
+        const int64_t e0 = e[b];
+        const int k1 = (int)seg[np * nb + b];
+        for (int k = (int)seg[b] + (int)threadIdx.x; k < k1; k += BLOCK) {
+            const int64_t c = col[e0 + k] - HEAD, p = c / COLS;
+            const int64_t v = (int64_t)pre[p * nb + b] + (k - (int64_t)seg[p * nb + b]);
+            tcol[v] = (uint16_t)(c - p * COLS);
+            col[e0 + k] = (int32_t)(uint32_t)v;
+        }
+        if (b == nb - 1 && threadIdx.x == 0)
+            pre[np * nb] = pre[np * nb - 1] + (seg[np * nb + b] - seg[(np - 1) * nb + b]);
+    }
+}
+
+template <class VT> void launch_sweep_tail_setup(const Plan& p, const Bufs& b, hipStream_t s) {
+    const int64_t segs = (int64_t)p.sw_np * p.sw_nb;
+    const unsigned gb = (unsigned)std::min<int64_t>(p.sw_nb, 16384);
+    hipLaunchKernelGGL(k_sw_panels<VT>, dim3(gb), dim3(BLOCK), 0, s, b.st, p.sw_nb, b.swe, b.swcol, p.sw_np,
+                       b.swseg);
+    hipLaunchKernelGGL(k_sw_seg_len, dim3((unsigned)std::min<int64_t>((segs + BLOCK - 1) / BLOCK, 8192)),
+                       dim3(BLOCK), 0, s, b.st, p.sw_nb, segs, b.swseg, b.swpre);
+    launch_scan(&b.st->reordered, b.swpre, segs, b.swbsum, s);
+    hipLaunchKernelGGL(k_sw_tail_fill<VT>, dim3(gb), dim3(BLOCK), 0, s, b.st, p.sw_nb, b.swe, b.swseg, p.sw_np,
+                       b.swpre, b.swcol, b.swtcol);
+}
+
 // Measured on MI355X, R-MAT 26 FP32 (grid / slices per block / entries per
 // thread in flight -> fill ms): 1024/32/1 22.6, 1024/8/8 17.2, 512/16/8
 // 15.4, 256/16/8 17.2, 512/32/4 22.8, 1024/64/2 36.0, 256/8/16 12.3,
@@ -82,7 +155,7 @@ __global__ __launch_bounds__(BLOCK) void k_sw_blocks(const State* st, const int6
 constexpr int SWF_THREADS = 256;
 constexpr int SWF_GRID = 256;
 constexpr int SWF_SLICES = 8;         // work items per block
-constexpr int SWF_U = 16;             // entries per thread in flight
+constexpr int SWF_G = 4;              // groups of 256 entries a wavefront has in flight (16 entries per lane)
 
 // Rows within the block and values of the column-sorted entries: the sorted
 // payload of entry p of block b holds its row within the block and its
@@ -95,8 +168,9 @@ constexpr int SWF_U = 16;             // entries per thread in flight
 // payload stream and the outputs bypass L2.  Every entry's outputs depend on
 // the entry alone, so the order in which slices are drawn does not matter.
 // A workgroup draws its next slice before working on the current one, and
-// each thread keeps SWF_U entries in flight, so the chain of dependent loads
-// (payload, then value) is paid once per SWF_U entries.
+// each lane keeps 16 entries in flight, so the chain of dependent loads
+// (payload, then value) is paid once per 16 entries.  Outputs go to
+// sweep_place.
 template <class VT>
 __global__ __launch_bounds__(SWF_THREADS) void k_sw_fill(const State* st, const VT* __restrict__ val2, int64_t nb,
                                                          const int64_t* __restrict__ e,
@@ -106,6 +180,9 @@ __global__ __launch_bounds__(SWF_THREADS) void k_sw_fill(const State* st, const 
     __shared__ uint32_t s_item[2];
     if (st->status != 0 || !st->reordered || st->packed != PACK_SWEEP) return;
     constexpr uint32_t POSMASK = (1u << SW_POSBITS) - 1u;
+    typedef uint16_t us4 __attribute__((ext_vector_type(4)));
+    typedef VT V4 __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t xcd = blockIdx.x & 7u;
     const int64_t nbx = (nb - xcd + 7) / 8;      // blocks of this XCD
     const int64_t items = nbx * SWF_SLICES;
@@ -118,22 +195,51 @@ __global__ __launch_bounds__(SWF_THREADS) void k_sw_fill(const State* st, const 
         if (threadIdx.x == 0)
             s_item[it ^ 1] = __hip_atomic_fetch_add(queue + xcd, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const int64_t b = xcd + 8 * (item / SWF_SLICES), slice = item % SWF_SLICES;
-        const int64_t e0 = e[b], cnt = e[b + 1] - e0;
-        const int64_t k0 = cnt * slice / SWF_SLICES, k1 = cnt * (slice + 1) / SWF_SLICES;
-        for (int64_t k = k0 + threadIdx.x; k < k1; k += SWF_THREADS * SWF_U) {
-            uint32_t w[SWF_U];
+        const int64_t e0 = e[b], e1 = e[b + 1];
+        if (e0 < e1) {
+            // Groups of 256 entries that hold entries of the block.
+            const int64_t f = e0 >> 8;
+            const int ng = (int)(((e1 + 255) >> 8) - f);
+            const int g1 = (int)((int64_t)ng * (slice + 1) / SWF_SLICES);
+            for (int g = (int)((int64_t)ng * slice / SWF_SLICES) + wave * SWF_G; g < g1;
+                 g += SWF_G * SWF_THREADS / 64) {
+                uint32_t w[SWF_G][4];
+                VT v[SWF_G][4];
 #pragma unroll
-            for (int q = 0; q < SWF_U; ++q)
-                w[q] = __builtin_nontemporal_load(src + e0 + min<int64_t>(k + q * SWF_THREADS, k1 - 1));
-            VT v[SWF_U];
+                for (int u = 0; u < SWF_G; ++u)
 #pragma unroll
-            for (int q = 0; q < SWF_U; ++q) v[q] = val2[e0 + (w[q] & POSMASK)];
+                    for (int i = 0; i < 4; ++i) {
+                        const int64_t k = ((f + g + u) << 8) + i * 64 + lane;
+                        w[u][i] = __builtin_nontemporal_load(src + min(max(k, e0), e1 - 1));
+                    }
 #pragma unroll
-            for (int q = 0; q < SWF_U; ++q) {
-                const int64_t kq = k + q * SWF_THREADS;
-                if (kq < k1) {
-                    __builtin_nontemporal_store((uint16_t)(w[q] >> SW_POSBITS), rl + e0 + kq);
-                    __builtin_nontemporal_store(v[q], val + e0 + kq);
+                for (int u = 0; u < SWF_G; ++u)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[u][i] = val2[e0 + (w[u][i] & POSMASK)];
+#pragma unroll
+                for (int u = 0; u < SWF_G; ++u) {
+                    const int64_t k = (f + g + u) << 8;
+                    if (g + u >= g1) break;
+                    if (k >= e0 && k + 256 <= e1) {
+                        us4 r4;
+                        V4 v4;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            r4[i] = (uint16_t)(w[u][i] >> SW_POSBITS);
+                            v4[i] = v[u][i];
+                        }
+                        __builtin_nontemporal_store(r4, (us4*)(rl + k + lane * 4));
+                        __builtin_nontemporal_store(v4, (V4*)(val + k + lane * 4));
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const int64_t ki = k + i * 64 + lane;
+                            if (ki >= e0 && ki < e1) {
+                                rl[ki] = (uint16_t)(w[u][i] >> SW_POSBITS);
+                                val[ki] = v[u][i];
+                            }
+                        }
+                    }
                 }
             }
         }
@@ -194,6 +300,14 @@ hipError_t launch_sweep_sort(const Plan& p, const Bufs& b, hipStream_t s) {
                                (const uint16_t*)b.val2, p.sw_nb, b.swe, b.swsrc, b.swrl, (uint16_t*)b.swval,
                                b.swq);
             break;
+    }
+    if (p.sw_np > 0) {
+        if (p.prec == 0)
+            launch_sweep_tail_setup<double>(p, b, s);
+        else if (p.prec == 1)
+            launch_sweep_tail_setup<float>(p, b, s);
+        else
+            launch_sweep_tail_setup<uint16_t>(p, b, s);
     }
     return hipGetLastError();
 }
