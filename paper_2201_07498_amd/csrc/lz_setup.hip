@@ -472,8 +472,9 @@ __global__ __launch_bounds__(FILL_WAVES * 64) void k_rl_fill(const State* st, co
             const int k = e * 64 + lane;
             if (k < cnt) {
                 const uint32_t kv = key[k];
-                col2[t0 + k] = (int32_t)kv;
-                val2[t0 + k] = sv[kv & PACK_SLOTMASK];
+                const int at = sorted_place<VT>(k, cnt);
+                col2[t0 + at] = (int32_t)kv;
+                val2[t0 + at] = sv[kv & PACK_SLOTMASK];
             }
         }
         wave_sync();
@@ -543,8 +544,9 @@ __global__ __launch_bounds__(BLOCK) void k_rl_fill_group(const State* st, const 
         __syncthreads();
         for (int p = tid; p < ne; p += BLOCK) {
             const uint32_t kv = key[p];
-            col2[g0 + p] = (int32_t)kv;
-            val2[g0 + p] = sv[kv & GROUP_SLOTMASK];
+            const int at = sorted_place<VT>(p, ne);
+            col2[g0 + at] = (int32_t)kv;
+            val2[g0 + at] = sv[kv & GROUP_SLOTMASK];
         }
         __syncthreads();
     }
