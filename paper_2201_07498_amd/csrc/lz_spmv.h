@@ -171,83 +171,96 @@ template <class VT> __device__ __forceinline__ int sorted_place(int k, int cnt) 
 }
 
 // The products of one wavefront's share of stored entries [base, base+cnt)
-// in LDS.  The col/val loads of a lane go out together, then the 16 gathers of
-// x.  Lanes past the end re-read the last entries (same cache lines), so every
-// load is unconditional.  Row-ordered storage (slotbits = 0): entry base+k
-// lands in pw[k].  Column-sorted storage: each column word is (col <<
-// slotbits) | slot and the product lands in pw[slot], the entry's position in
-// row order, so the row sums add the same values in the same order as for
+// in LDS, in two halves: tile_load issues the col/val loads of a lane together;
+// tile_gather issues the 16 gathers of x, runs `between` (loads of later work)
+// and writes the products.  Lanes past the end re-read the last entries (same
+// cache lines), so every load is unconditional; with fewer entries than a lane
+// takes (cnt < E) the load is by element.  Row-ordered storage (slotbits = 0):
+// entry base+k lands in pw[k].  Column-sorted storage: each column word is (col
+// << slotbits) | slot and the product lands in pw[slot], the entry's position
+// in row order, so the row sums add the same values in the same order as for
 // row-ordered storage (lanes past the end rewrite the last entries' products).
 // With CACHED, xs holds x[0..hn) in LDS and gathers of those entries read it.
 // With OFF32 (every byte offset into x below 2^32), each load is a
 // wave-uniform base in scalar registers plus a 32-bit per-lane offset; 64-bit
 // per-lane addresses would otherwise take about half of the kernel's vector
 // registers and limit its occupancy.
-template <class VT, class AT, bool CACHED, bool OFF32>
-__device__ __forceinline__ void tile_products(const int32_t* __restrict__ col, const VT* __restrict__ val,
-                                              const VT* __restrict__ x, const VT* xs, int hn, int64_t base, int cnt,
-                                              int slotbits, AT* pw, int lane) {
-    constexpr int E = TileVec<VT>::E, NV = TP / E;
+template <class VT> struct TileEntries {
+    static constexpr int NV = TP / TileVec<VT>::E;
+    typename TileVec<VT>::C ci[NV];
+    typename TileVec<VT>::V vv[NV];
+};
+template <class VT>
+__device__ __forceinline__ void tile_load(TileEntries<VT>& t, const int32_t* __restrict__ col,
+                                          const VT* __restrict__ val, int64_t base, int cnt, int lane) {
+    constexpr int E = TileVec<VT>::E, NV = TileEntries<VT>::NV;
     using C = typename TileVec<VT>::C;
     using V = typename TileVec<VT>::V;
     if (cnt <= 0) return;
-    const uint32_t smask = (1u << slotbits) - 1u;
-    // Entries of x past the first GATHER_WARM_BYTES are gathered
-    // non-temporally: after the hub-first relabelling they are the rarely
-    // used columns, and keeping their lines out of L2 leaves it to the warm
-    // head of x.
-    auto gather = [&](uint32_t c) -> VT {
-        const bool warm = c < GATHER_WARM_BYTES / (uint32_t)sizeof(VT);
-        if constexpr (CACHED) {
-            return (int)c < hn ? xs[c] : (warm ? x[c] : __builtin_nontemporal_load(x + c));
-        } else if constexpr (OFF32) {
-            const VT* px = (const VT*)((const char*)x + c * (uint32_t)sizeof(VT));
-            return warm ? *px : __builtin_nontemporal_load(px);
-        } else {
-            return warm ? x[c] : __builtin_nontemporal_load(x + c);
-        }
-    };
     if (cnt < E) {
-        const int k = min(lane, cnt - 1);
-        const uint32_t w = (uint32_t)col[base + k];
-        pw[slotbits ? (int)(w & smask) : k] = to_a(val[base + k], AT(0)) * to_a(gather(w >> slotbits), AT(0));
+#pragma unroll
+        for (int q = 0; q < NV; ++q)
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                t.ci[q][i] = col[base + min(i, cnt - 1)];
+                t.vv[q][i] = val[base + min(i, cnt - 1)];
+            }
         return;
     }
-    C ci[NV];
-    V vv[NV];
     constexpr bool NT = sizeof(VT) == 8;
     const char* cb = (const char*)(col + base);
     const char* vb = (const char*)(val + base);
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
         const uint32_t o = (uint32_t)min(q * 64 * E + lane * E, cnt - E);
-        ci[q] = stream_load<NT>((const C*)(cb + o * 4u));
-        vv[q] = stream_load<NT>((const V*)(vb + o * (uint32_t)sizeof(VT)));
+        t.ci[q] = stream_load<NT>((const C*)(cb + o * 4u));
+        t.vv[q] = stream_load<NT>((const V*)(vb + o * (uint32_t)sizeof(VT)));
     }
+}
+template <class VT, class AT, bool CACHED, bool OFF32, class Between>
+__device__ __forceinline__ void tile_gather(const TileEntries<VT>& t, const VT* __restrict__ x, const VT* xs, int hn,
+                                            int cnt, int slotbits, AT* pw, int lane, Between&& between) {
+    constexpr int E = TileVec<VT>::E, NV = TileEntries<VT>::NV;
+    if (cnt <= 0) {
+        between();
+        return;
+    }
+    // Entries of x past the first GATHER_WARM_BYTES are gathered
+    // non-temporally: after the hub-first relabelling they are the rarely
+    // used columns, and keeping their lines out of L2 leaves it to the warm
+    // head of x.
+    auto gather = [&](uint32_t c) -> VT {
+        const bool warm = c < GATHER_WARM_BYTES / (uint32_t)sizeof(VT);
+        if (CACHED && (int)c < hn) return xs[c];
+        const VT* px = OFF32 ? (const VT*)((const char*)x + c * (uint32_t)sizeof(VT)) : x + c;
+        return warm ? *px : __builtin_nontemporal_load(px);
+    };
+    const uint32_t smask = (1u << slotbits) - 1u;
     VT xv[TP];
 #pragma unroll
     for (int q = 0; q < NV; ++q)
 #pragma unroll
-        for (int i = 0; i < E; ++i) xv[q * E + i] = gather((uint32_t)ci[q][i] >> slotbits);
+        for (int i = 0; i < E; ++i) xv[q * E + i] = gather((uint32_t)t.ci[q][i] >> slotbits);
+    between();
     if (slotbits) {
 #pragma unroll
         for (int q = 0; q < NV; ++q)
 #pragma unroll
             for (int i = 0; i < E; ++i)
-                pw[(uint32_t)ci[q][i] & smask] = to_a(VT(vv[q][i]), AT(0)) * to_a(xv[q * E + i], AT(0));
+                pw[(uint32_t)t.ci[q][i] & smask] = to_a(VT(t.vv[q][i]), AT(0)) * to_a(xv[q * E + i], AT(0));
     } else {
         typedef AT P __attribute__((ext_vector_type(E)));
 #pragma unroll
         for (int q = 0; q < NV; ++q) {
             P pr;
 #pragma unroll
-            for (int i = 0; i < E; ++i) pr[i] = to_a(VT(vv[q][i]), AT(0)) * to_a(xv[q * E + i], AT(0));
+            for (int i = 0; i < E; ++i) pr[i] = to_a(VT(t.vv[q][i]), AT(0)) * to_a(xv[q * E + i], AT(0));
             if ((q + 1) * 64 * E <= cnt) {               // the whole run is live: one aligned store
                 *(P*)(pw + q * 64 * E + lane * E) = pr;
             } else {
-                const int k = min(q * 64 * E + lane * E, cnt - E);
+                const int k = max(min(q * 64 * E + lane * E, cnt - E), 0);
 #pragma unroll
-                for (int i = 0; i < E; ++i) pw[k + i] = pr[i];
+                for (int i = 0; i < E; ++i) pw[min(k + i, cnt - 1)] = pr[i];
             }
         }
     }
@@ -374,6 +387,45 @@ __device__ __forceinline__ void spmv_tiles(const int64_t* __restrict__ rp, const
     AT* pw = prod_lds<AT, NW>() + (threadIdx.x >> 6) * TILE;
     const TileRange tr = wave_tiles<NW>(tb, te);
     const int64_t items = nnz + n;
+    if constexpr (CACHED && sizeof(VT) == 2) {
+        // One workgroup per CU, so 16 wavefronts and, in BF16, registers to
+        // spare (FP32 would spill): the entries and row bounds of the next tile
+        // are loaded while the gathers of this one are in flight and its rows
+        // are summed.  R-MAT 23 step SpMV 1.146 -> 1.129 ms.
+        auto owned = [&](int64_t t, int64_t& lo, int64_t& hi) {
+            lo = hi = 0;
+            if (t < tr.end) {
+                lo = ob[t];
+                hi = ob[t + 1];
+            }
+        };
+        if (tr.first >= tr.end) return;
+        int64_t r_lo, r_hi, n_lo, n_hi;
+        owned(tr.first, r_lo, r_hi);
+        owned(tr.first + tr.stride, n_lo, n_hi);
+        TileRows q = tile_rows(rp, tr.first, r_lo, r_hi, n, items, lane, pre);
+        TileEntries<VT> en;
+        tile_load(en, col, val, q.t0, q.cnt, lane);
+        for (int64_t t = tr.first; t < tr.end; t += tr.stride) {
+            const int64_t tn = t + tr.stride;
+            TileRows qn{};
+            TileEntries<VT> nx;
+            const TileRows cur = q;
+            tile_gather<VT, AT, CACHED, OFF32>(en, x, xs, hn, cur.cnt, slotbits, pw, lane, [&] {
+                if (tn < tr.end) {
+                    qn = tile_rows(rp, tn, n_lo, n_hi, n, items, lane, pre);
+                    tile_load(nx, col, val, qn.t0, qn.cnt, lane);
+                    owned(tn + tr.stride, n_lo, n_hi);
+                }
+            });
+            wave_sync();
+            tile_sums(cur, pw, rp, n, n_tiles, tk, head, tail, lane, pre, row, piece, fin);
+            wave_sync();
+            q = qn;
+            en = nx;
+        }
+        return;
+    }
     int64_t r_lo = 0, r_hi = 0;
     if (tr.first < tr.end) {
         r_lo = ob[tr.first];
@@ -388,7 +440,9 @@ __device__ __forceinline__ void spmv_tiles(const int64_t* __restrict__ rp, const
             n_hi = ob[tn + 1];
         }
         const TileRows q = tile_rows(rp, t, r_lo, r_hi, n, items, lane, pre);
-        tile_products<VT, AT, CACHED, OFF32>(col, val, x, xs, hn, q.t0, q.cnt, slotbits, pw, lane);
+        TileEntries<VT> en;
+        tile_load(en, col, val, q.t0, q.cnt, lane);
+        tile_gather<VT, AT, CACHED, OFF32>(en, x, xs, hn, q.cnt, slotbits, pw, lane, [] {});
         wave_sync();
         tile_sums(q, pw, rp, n, n_tiles, tk, head, tail, lane, pre, row, piece, fin);
         wave_sync();
@@ -434,8 +488,9 @@ __device__ __forceinline__ void spmv_groups(const int64_t* __restrict__ rp, cons
         TileRows q{};
         if (has) q = tile_rows(rp, t, ob[t], ob[t + 1], n, items, lane, pre);
         const int cw = (int)max<int64_t>(0, min<int64_t>(TILE, gend - g0 - (int64_t)wi * TILE));
-        tile_products<VT, AT, CACHED, OFF32>(col, val, x, xs, hn, g0 + (int64_t)wi * TILE, cw, GROUP_SLOTBITS, pg,
-                                              lane);
+        TileEntries<VT> en;
+        tile_load(en, col, val, g0 + (int64_t)wi * TILE, cw, lane);
+        tile_gather<VT, AT, CACHED, OFF32>(en, x, xs, hn, cw, GROUP_SLOTBITS, pg, lane, [] {});
         __syncthreads();
         if (has) tile_sums(q, pg + (q.t0 - g0), rp, n, n_tiles, tk, head, tail, lane, pre, row, piece, fin);
         __syncthreads();
