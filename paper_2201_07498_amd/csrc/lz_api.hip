@@ -351,31 +351,57 @@ int run_solve(Plan p, Csr a, const lz_options& o, hipStream_t s, double* out_val
             LZ_HIP(hipStreamSynchronize(s));
             p.xcache = want_xcache(p, hst->reordered != 0);
         }
+        p.fold = 1;
         LZ_HIP(launch_init(p, b, s));
         if (o.profile) LZ_HIP(hipEventRecord(pev[1], s));
         for (int t = 0; t < m; ++t) LZ_HIP(launch_iteration(p, b, a, t + 1, o.reorth, s, iter_events(t)));
         if (o.profile) LZ_HIP(hipEventRecord(pev[2], s));
-        // Breakdowns consume iterations without advancing j: run more until
-        // m steps are done (bounded; each round advances j).
-        for (int round = 0; round < 2 * LZ_MAX_STEPS + 2; ++round) {
-            LZ_HIP(hipMemcpyAsync(hst, b.st, STATE_HEAD_BYTES, hipMemcpyDeviceToHost, s));
-            LZ_HIP(hipStreamSynchronize(s));
-            if (hst->status != 0 || hst->j >= m) break;
-            const int extra = m - hst->j;
-            for (int t = 0; t < extra; ++t)
-                LZ_HIP(launch_iteration(p, b, a, m, o.reorth, s, iter_events(launched + t)));
-            launched += extra;
-            if (o.profile) LZ_HIP(hipEventRecord(pev[2], s));
+        // The finish goes out right behind the iterations: nearly every solve
+        // has taken its m steps by then, and the host waits once.  (A
+        // host-resident matrix would stream its slabs for nothing.)
+        auto finish = [&]() -> hipError_t {
+            hipError_t e = o.profile ? hipEventRecord(pev[3], s) : hipSuccess;
+            if (e == hipSuccess) e = launch_finish(p, b, a, out_vals, out_vecs, o.report, s);
+            if (e == hipSuccess && o.profile) e = hipEventRecord(pev[4], s);
+            if (e == hipSuccess) e = hipMemcpyAsync(hst, b.st, STATE_REPORT_BYTES, hipMemcpyDeviceToHost, s);
+            return e == hipSuccess ? hipStreamSynchronize(s) : e;
+        };
+        bool finished = false;
+        if (!hc) {
+            p.strict_m = STRICT_PENDING;
+            LZ_HIP(finish());
+            p.strict_m = STRICT_NO;
+            finished = hst->status != LZ_PENDING;
+            if (!finished) launch_resume(b, s);
         }
-        if (hst->status == 0 && hst->j < m) {
-            rc = LZ_ERR_BREAKDOWN;
-            goto done;
+        if (!finished) {
+            // Breakdowns and second passes consume iterations without advancing
+            // j: run more until m steps are done (bounded; each round advances j).
+            for (int round = 0; round < 2 * LZ_MAX_STEPS + 2; ++round) {
+                LZ_HIP(hipMemcpyAsync(hst, b.st, STATE_HEAD_BYTES, hipMemcpyDeviceToHost, s));
+                LZ_HIP(hipStreamSynchronize(s));
+                if (hst->status != 0 || hst->j >= m) break;
+                const int extra = m - hst->j;
+                for (int t = 0; t < extra; ++t)
+                    LZ_HIP(launch_iteration(p, b, a, m, o.reorth, s, iter_events(launched + t)));
+                launched += extra;
+                if (o.profile) LZ_HIP(hipEventRecord(pev[2], s));
+            }
+            if (hst->status == 0 && hst->j < m) {
+                rc = LZ_ERR_BREAKDOWN;
+                goto done;
+            }
+            if (hst->status == 0) {
+                LZ_HIP(finish());
+            } else {
+                if (o.profile) {
+                    LZ_HIP(hipEventRecord(pev[3], s));
+                    LZ_HIP(hipEventRecord(pev[4], s));
+                }
+                LZ_HIP(hipMemcpyAsync(hst, b.st, STATE_REPORT_BYTES, hipMemcpyDeviceToHost, s));
+                LZ_HIP(hipStreamSynchronize(s));
+            }
         }
-        if (o.profile) LZ_HIP(hipEventRecord(pev[3], s));
-        if (hst->status == 0) LZ_HIP(launch_finish(p, b, a, out_vals, out_vecs, o.report, s));
-        if (o.profile) LZ_HIP(hipEventRecord(pev[4], s));
-        LZ_HIP(hipMemcpyAsync(hst, b.st, STATE_REPORT_BYTES, hipMemcpyDeviceToHost, s));
-        LZ_HIP(hipStreamSynchronize(s));
         rc = hst->status;
         if (report) {
             std::memset(report, 0, sizeof(*report));
@@ -485,7 +511,7 @@ int run_solve_async(Plan p, Csr a, const lz_options& o, int budget, hipStream_t 
     }
     {
         const Bufs b = resolve(p, ws);
-        p.strict_m = 1;
+        p.strict_m = STRICT_BUDGET;
         p.xcache = (o.reorder != LZ_REORDER_OFF && !p.sweep && want_xcache(p, true)) ? XC_GATED : XC_OFF;
         LZ_HIP(launch_setup(p, b, a, o.seed, o.reorth, o.reorder, s));
         LZ_HIP(launch_init(p, b, s));

@@ -327,14 +327,13 @@ __device__ __forceinline__ int jacobi_core(int m, const double* diag, const doub
 
 // T from alpha_1..alpha_m and beta_2..beta_m, Jacobi, Top-K selection by
 // modulus (ties: larger value, then lower index); writes the eigenvalues.
-// With `strict` (stream-ordered calls, whose iteration budget is fixed when
-// they are enqueued), a solve that completed fewer than m steps because more
-// breakdowns occurred than the budget absorbs ends with LZ_ERR_RESTART_BUDGET.
+// A solve that completed fewer than m steps (breakdowns took some of the
+// enqueued iterations) ends as `strict` says (STRICT_*).
 __global__ __launch_bounds__(JBLOCK) void k_jacobi_select(State* st, double* out_vals, int strict) {
     __shared__ JacobiShared sh;
     if (st->status != 0) return;
-    if (strict && st->j < st->m) {
-        if (threadIdx.x == 0) st->status = -9;     // LZ_ERR_RESTART_BUDGET
+    if (strict != STRICT_NO && st->j < st->m) {
+        if (threadIdx.x == 0) st->status = strict == STRICT_PENDING ? 1 : -9;   // LZ_PENDING, LZ_ERR_RESTART_BUDGET
         return;
     }
     const int m = min(st->j, st->m);
@@ -897,6 +896,7 @@ __global__ __launch_bounds__(BLOCK) void k_gram(const State* st, const T* __rest
 // (a fixed order).
 __global__ __launch_bounds__(BLOCK) void k_gram_reduce(const State* st, const double* gpart, int nparts, int which,
                                                        double* G) {
+    if (st->status != 0) return;
     const int c = which == 0 ? min(st->j, st->m) : st->K;
     const int lane = threadIdx.x & 63;
     const int entry = blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6);

@@ -85,7 +85,8 @@ struct State {
     int32_t m, K, reorth, second;   // `second`: run the second update of this step
     int32_t n_items, n_long, sweeps;
     int32_t arith;        // LZ_ARITH_FP32: dots, norms, reorthogonalisation and SpMV epilogue in FP32
-    int32_t remeasure;    // two-pass modes: this step's second coefficients are re-measured (see k_orth_dot)
+    int32_t remeasure;    // 1: this step's second coefficients are re-measured (two-pass modes, see k_orth_dot);
+                          // 2: measured by the store kernel, the next iteration stores
     uint32_t ticket[TK_COUNT];
     uint64_t seed;
     double u_s;           // unit roundoff of the stored basis (selective reorthogonalisation)
@@ -130,7 +131,8 @@ struct Plan {
     int32_t xcache = 0;         // Lanczos-step SpMV keeps the head of x in LDS: XC_OFF, XC_ON (set once the
                                 // row order is known) or XC_GATED (both variants launched; each returns
                                 // unless the device's row-order decision selects it)
-    int32_t strict_m = 0;       // the finish reports LZ_ERR_RESTART_BUDGET if fewer than m steps completed
+    int32_t strict_m = 0;       // STRICT_*: what the finish does if fewer than m steps completed
+    int32_t fold = 0;           // the store kernel runs the second pass when it is due (more iterations can follow)
     int32_t fff = 0;            // all-FP32 arithmetic (FP32 storage only): float instantiations
     int32_t g_slab = 0;         // grid of the per-slab launches of a host-resident matrix
     int32_t sweep = 0;          // reserve and build the sweep-block copy if the matrix is relabelled
@@ -149,6 +151,11 @@ struct Plan {
 };
 
 enum XcacheChoice { XC_OFF = 0, XC_ON = 1, XC_GATED = 2 };
+// Finish of a solve that completed fewer than m steps: go on with those, end
+// with LZ_ERR_RESTART_BUDGET (stream-ordered calls), or do nothing and leave
+// LZ_PENDING in the status (enqueued before the host knows; it then enqueues
+// more iterations and another finish).
+enum StrictSteps { STRICT_NO = 0, STRICT_BUDGET = 1, STRICT_PENDING = 2 };
 
 inline size_t storage_bytes(int prec) { return prec == 0 ? 8 : (prec == 1 ? 4 : 2); }
 inline size_t work_bytes(int prec) { return prec == 0 ? 8 : 4; }
@@ -233,6 +240,8 @@ struct Csr {
 hipError_t launch_setup(const Plan& p, const Bufs& b, const Csr& a, uint64_t seed, int reorth, int reorder,
                         hipStream_t s);
 hipError_t launch_init(const Plan& p, const Bufs& b, hipStream_t s);
+// Clears LZ_PENDING from the status (see STRICT_PENDING).
+void launch_resume(const Bufs& b, hipStream_t s);
 // One Lanczos iteration (SpMV or restart draw, reorthogonalisation, store);
 // `reorth` is the solve's LZ_REORTH_* mode (it selects the kernels).
 // `ncols_bound` >= j+1 for every j the iteration can see.

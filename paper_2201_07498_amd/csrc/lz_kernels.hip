@@ -9,9 +9,13 @@
 //   k_orth_upd_store v_{j+1} = w - V (c + c2) in the basis precision;
 //                    beta_{j+1}; the new column of G
 // With one pass or none, a restart vector (always orthogonalised twice) takes
-// the classical second pass instead: k_orth_upd_dot, w' = w - V c and
-// c2 = V^T w', runs between the two.  The two-pass modes run it too when the
-// first pass cancelled strongly (see k_orth_dot).
+// the classical second pass instead: w' = w - V c and c2 = V^T w' between the
+// two.  The two-pass modes take it too when the first pass cancelled strongly
+// (see k_orth_dot).  It is rare, so calls that can enqueue further iterations
+// fold it into k_orth_upd_store: that kernel then measures instead of storing,
+// and the next iteration, whose other kernels return at once, stores.  The
+// stream-ordered call, whose iterations are counted beforehand, launches it as
+// k_orth_upd_dot at every step (it returns at once: 4.5 us a step).
 // Global sums are per-workgroup partials that the last workgroup to finish
 // adds in a fixed order, so results do not depend on scheduling.  The step
 // index and every coefficient stay in device memory.
@@ -262,7 +266,7 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_dot(State* st, const typename T
     __shared__ A sred[OBLOCK];
     __shared__ int s_last;
     const int j = st->j;
-    if (st->status != 0 || j >= st->m || !dot_active(st)) return;
+    if (st->status != 0 || j >= st->m || st->remeasure == 2 || !dot_active(st)) return;
     const int nc = j + 1;
     if (nc > NC) {                       // launch contract broken: flag, do nothing
         if (blockIdx.x == 0 && threadIdx.x == 0) st->status = -1;
@@ -417,28 +421,27 @@ __device__ __forceinline__ void split_update(const typename Ch<P>::T (&ch)[Split
     for (int rr = 0; rr < R; ++rr) u[rr] = group_lane_sum<CS>(u[rr]);
 }
 
+// LDS of the second pass and the store.
+template <int NC, class A> struct OrthShared {
+    A coef[NC];
+    A red[OWAVES][NC];
+    A redn[OWAVES];
+    A lout[NC];
+    A sred[OBLOCK];
+    A tot[1], sn[1];
+    double shd[OWAVES];
+    int last, accept;
+};
+
 // w' = w - V c (stored in the working precision), then c2 = V^T w' and ||w'||^2.
+// Returns true in the last workgroup, which has written c2.
 template <int P, int NC, class A>
-__global__ __launch_bounds__(OBLOCK) void k_orth_upd_dot(State* st, const typename Tr<P>::V* __restrict__ Vb,
-                                                        typename Tr<P>::W* __restrict__ w, int64_t ld,
-                                                        double* part, double* part2) {
+__device__ __forceinline__ bool orth_measure(State* st, const typename Tr<P>::V* __restrict__ Vb,
+                                             typename Tr<P>::W* __restrict__ w, int64_t ld, int nc, double* part,
+                                             double* part2, OrthShared<NC, A>& sh) {
     using CT = typename Ch<P>::T;
     constexpr int R = Ch<P>::R, CS = Split<P, NC>::CS, NCL = Split<P, NC>::NCL, GPW = 64 / CS;
-    __shared__ A coef[NC];
-    __shared__ A red[OWAVES][NC];
-    __shared__ A redn[OWAVES];
-    __shared__ A lout[NC];
-    __shared__ A s_tot[1];
-    __shared__ A sred[OBLOCK];
-    __shared__ int s_last;
-    const int j = st->j;
-    if (st->status != 0 || j >= st->m || !upd_dot_active(st)) return;
-    const int nc = j + 1;
-    if (nc > NC) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) st->status = -1;
-        return;
-    }
-    for (int k = threadIdx.x; k < NC; k += OBLOCK) coef[k] = k < nc ? (A)st->c[k] * (A)st->scale[k] : A(0);
+    for (int k = threadIdx.x; k < NC; k += OBLOCK) sh.coef[k] = k < nc ? (A)st->c[k] * (A)st->scale[k] : A(0);
     __syncthreads();
     const int ln = threadIdx.x & 63, cs = ln % CS;
     constexpr int64_t RBW = (int64_t)GPW * R;
@@ -459,7 +462,7 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_dot(State* st, const typena
             if (k < nc) ch[kk] = *(const CT*)(Vb + (int64_t)k * ld + r0);
         }
         A u[R];
-        split_update<P, NC>(ch, coef, cs, 0, nc, u);
+        split_update<P, NC>(ch, sh.coef, cs, 0, nc, u);
 #pragma unroll
         for (int kk = 0; kk < NCL; ++kk) opaque(ch[kk]);
 #pragma unroll
@@ -481,14 +484,30 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_dot(State* st, const typena
             }
         }
     }
-    publish_split<NC, CS, NCL>(acc, nrm, nc, part, part2, red, redn);
-    if (last_block(&st->ticket[TK_UPD], gridDim.x, &s_last)) {
-        const A wn = reduce_columns<NC>(part, part2, gridDim.x, nc, st->scale, st->c2, lout, sred, s_tot, [] {});
-        if (threadIdx.x == 0) {
-            st->wnorm2 = (double)wn;
-            st->second = 1;
-        }
+    publish_split<NC, CS, NCL>(acc, nrm, nc, part, part2, sh.red, sh.redn);
+    if (!last_block(&st->ticket[TK_UPD], gridDim.x, &sh.last)) return false;
+    const A wn = reduce_columns<NC>(part, part2, gridDim.x, nc, st->scale, st->c2, sh.lout, sh.sred, sh.tot, [] {});
+    if (threadIdx.x == 0) {
+        st->wnorm2 = (double)wn;
+        st->second = 1;
     }
+    return true;
+}
+
+// The second pass as a kernel of its own (stream-ordered calls).
+template <int P, int NC, class A>
+__global__ __launch_bounds__(OBLOCK) void k_orth_upd_dot(State* st, const typename Tr<P>::V* __restrict__ Vb,
+                                                        typename Tr<P>::W* __restrict__ w, int64_t ld,
+                                                        double* part, double* part2) {
+    __shared__ OrthShared<NC, A> sh;
+    const int j = st->j;
+    if (st->status != 0 || j >= st->m || !upd_dot_active(st)) return;
+    const int nc = j + 1;
+    if (nc > NC) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) st->status = -1;
+        return;
+    }
+    orth_measure<P, NC, A>(st, Vb, w, ld, nc, part, part2, sh);
 }
 
 // v_{j+1} = w - V c2 (c2 holds the total coefficients) stored in the basis
@@ -497,20 +516,16 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_dot(State* st, const typena
 // the working vector, starts a restart).  In the
 // two-pass modes the same pass takes the dots of the stored column with the
 // basis: the new row and column of the Gram matrix.
-template <int P, int NC, bool GRAM, class A>
+// With FOLD the second pass runs here when it is due: this launch then measures
+// (remeasure becomes 2) and the next iteration's launch stores.
+template <int P, int NC, bool GRAM, class A, bool FOLD>
 __global__ __launch_bounds__(OBLOCK) void k_orth_upd_store(State* st, typename Tr<P>::V* __restrict__ Vb,
-                                                          const typename Tr<P>::W* __restrict__ w, int64_t ld,
+                                                          typename Tr<P>::W* __restrict__ w, int64_t ld,
                                                           double* part, double* part2, double* gm) {
     using CT = typename Ch<P>::T;
     constexpr int R = Ch<P>::R, CS = Split<P, NC>::CS, NCL = Split<P, NC>::NCL, GPW = 64 / CS;
-    __shared__ A coef[NC];
-    __shared__ A red[OWAVES][NC];
-    __shared__ A redn[OWAVES];
-    __shared__ A gcol[NC];
-    __shared__ double shd[OWAVES];
-    __shared__ A s_tot[1], s_sn[1];
-    __shared__ A sred[OBLOCK];
-    __shared__ int s_last, s_accept;
+    __shared__ OrthShared<NC, A> sh;
+    auto& coef = sh.coef;
     // The coefficients do not depend on the step index: their loads go out
     // with it.
     double c2k = 0.0, sk = 0.0;
@@ -524,6 +539,12 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_store(State* st, typename T
     if (nc > NC) {
         if (blockIdx.x == 0 && threadIdx.x == 0) st->status = -1;
         return;
+    }
+    if constexpr (FOLD) {
+        if (st->remeasure != 2 && upd_dot_active(st)) {
+            if (orth_measure<P, NC, A>(st, Vb, w, ld, nc, part, part2, sh) && threadIdx.x == 0) st->remeasure = 2;
+            return;
+        }
     }
     // The Gram variant runs in the two-pass modes, where every column takes
     // part in the update.
@@ -583,12 +604,12 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_store(State* st, typename T
             for (int rr = 0; rr < R; ++rr) nrm += x[rr] * x[rr];
     }
     if constexpr (GRAM) {
-        publish_split<NC, CS, NCL>(acc, nrm, nc, part, part2, red, redn);
+        publish_split<NC, CS, NCL>(acc, nrm, nc, part, part2, sh.red, sh.redn);
     } else {
-        nrm = block_sum(nrm, redn, OWAVES);
+        nrm = block_sum(nrm, sh.redn, OWAVES);
         if (threadIdx.x == 0) st_dev(&part2[blockIdx.x], (double)nrm);
     }
-    if (last_block(&st->ticket[TK_STORE], gridDim.x, &s_last)) {
+    if (last_block(&st->ticket[TK_STORE], gridDim.x, &sh.last)) {
         // The scalars of thread 0 are loaded in the same round as the partials.
         double alpha_j = 0.0, beta_j = 0.0, tnorm = 0.0;
         int mode = 0;
@@ -600,9 +621,9 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_store(State* st, typename T
         }
         A tot;
         if constexpr (GRAM)
-            tot = reduce_columns<NC>(part, part2, gridDim.x, nc, st->scale, nullptr, gcol, sred, s_tot, [] {});
+            tot = reduce_columns<NC>(part, part2, gridDim.x, nc, st->scale, nullptr, sh.lout, sh.sred, sh.tot, [] {});
         else
-            tot = (A)ordered_sum_dev(part2, gridDim.x, shd);
+            tot = (A)ordered_sum_dev(part2, gridDim.x, sh.shd);
         if (threadIdx.x == 0) {
             const A b = sqrt(tot);
             int accept = 0;
@@ -640,17 +661,18 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_store(State* st, typename T
                     accept = 1;
                 }
             }
-            s_accept = accept;
-            s_sn[0] = (A)sn;
+            sh.accept = accept;
+            sh.sn[0] = (A)sn;
+            if (FOLD) st->remeasure = 0;
         }
         if constexpr (GRAM) {
             __syncthreads();
-            if (s_accept) {
+            if (sh.accept) {
                 // Gram entries of the unit stored vectors: column j+1 against
-                // 0..j (gcol already carries scale_k) and its own squared norm.
-                const A sn = s_sn[0];
+                // 0..j (lout already carries scale_k) and its own squared norm.
+                const A sn = sh.sn[0];
                 for (int k = threadIdx.x; k < nc; k += OBLOCK) {
-                    const double g = (double)(gcol[k] * sn);
+                    const double g = (double)(sh.lout[k] * sn);
                     gm[k * NCMAX + (j + 1)] = g;
                     gm[(j + 1) * NCMAX + k] = g;
                 }
@@ -681,19 +703,26 @@ static hipError_t iteration_pa(const Plan& p, const Bufs& b, const Csr& a, int n
     // The two-pass modes re-measure their second coefficients only where the
     // dots are no more precise than the storage (see k_orth_dot).
     const bool remeasure_possible = P == 0 || sizeof(A) == 4;
+    const bool measure = reorth < 2 || remeasure_possible;      // the second pass can become due
+    const bool fold = measure && p.fold;
+#define LZ_ORTH_STORE(NCV, GRAMV, FOLDV)                                                                   \
+    hipLaunchKernelGGL((k_orth_upd_store<P, NCV, GRAMV, A, FOLDV>), dim3(p.g_orth), dim3(OBLOCK), 0, s, b.st, V, w, \
+                       p.ld, b.part, b.part2, b.gm)
 #define LZ_ORTH_CASE(NCV)                                                                                  \
     case NCV:                                                                                              \
         hipLaunchKernelGGL((k_orth_dot<P, NCV, A>), dim3(p.g_orth), dim3(OBLOCK), 0, s, b.st, V, w, p.ld,      \
                            b.part, b.part2, b.gm);                                                         \
-        if (reorth < 2 || remeasure_possible)                                                              \
+        if (measure && !fold)                                                                              \
             hipLaunchKernelGGL((k_orth_upd_dot<P, NCV, A>), dim3(p.g_orth), dim3(OBLOCK), 0, s, b.st, V, w,    \
                                p.ld, b.part, b.part2);                                                     \
-        if (reorth >= 2)                                                                                   \
-            hipLaunchKernelGGL((k_orth_upd_store<P, NCV, true, A>), dim3(p.g_orth), dim3(OBLOCK), 0, s, b.st, V, \
-                               w, p.ld, b.part, b.part2, b.gm);                                            \
+        if (reorth >= 2 && fold)                                                                           \
+            LZ_ORTH_STORE(NCV, true, true);                                                                \
+        else if (reorth >= 2)                                                                              \
+            LZ_ORTH_STORE(NCV, true, false);                                                               \
+        else if (fold)                                                                                     \
+            LZ_ORTH_STORE(NCV, false, true);                                                               \
         else                                                                                               \
-            hipLaunchKernelGGL((k_orth_upd_store<P, NCV, false, A>), dim3(p.g_orth), dim3(OBLOCK), 0, s, b.st,  \
-                               V, w, p.ld, b.part, b.part2, b.gm);                                         \
+            LZ_ORTH_STORE(NCV, false, false);                                                              \
         break;
     switch (nb) {
         LZ_ORTH_CASE(8)
@@ -708,6 +737,7 @@ static hipError_t iteration_pa(const Plan& p, const Bufs& b, const Csr& a, int n
             return hipErrorInvalidValue;
     }
 #undef LZ_ORTH_CASE
+#undef LZ_ORTH_STORE
     return hipGetLastError();
 }
 

@@ -11,9 +11,11 @@
 // different sizes and precisions run concurrently on the device.  The Lanczos
 // iterations of a request can be captured in a hipGraph and replayed.  A
 // slot's thread advances it through a small state machine, waiting on events:
-//   ADMIT:   H2D of the CSR, setup, start vector, m iterations, D2H of state
-//   LANCZOS: restart check (more iterations if breakdowns consumed some),
-//            then Jacobi, selection, Ritz vectors, report, D2H of results
+//   ADMIT:   H2D of the CSR, setup, start vector, m iterations, then Jacobi,
+//            selection, Ritz vectors, report (these return at once if
+//            breakdowns consumed some iterations), D2H of results
+//   LANCZOS: only then: more iterations until the m steps are done, and the
+//            results again
 //   FINISH:  results to the caller, arena block and slot released.
 // Launch shapes depend only on the request, so a request's results are the
 // same alone and in any mix.
@@ -186,7 +188,25 @@ struct Server {
     void advance(Slot& s);
     void complete(Slot& s, int status);
     hipError_t launch_lanczos(Slot& s);
+    hipError_t launch_results(Slot& s, int strict);
 };
+
+// The finish and the copies of its results, then the phase event.
+hipError_t Server::launch_results(Slot& s, int strict) {
+    Req* q = s.req;
+    Plan p = q->plan;
+    p.strict_m = strict;
+    hipError_t e = launch_finish(p, s.bufs, s.csr, s.dvals, s.dvecs, 1, s.stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(s.hvals, s.dvals, sizeof(double) * p.K, hipMemcpyDeviceToHost, s.stream);
+    if (e == hipSuccess && q->r.out_vecs)
+        e = hipMemcpyAsync(q->r.out_vecs, s.dvecs, sizeof(double) * p.n * p.K, hipMemcpyDeviceToHost, s.stream);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(s.hstate, s.bufs.st, STATE_REPORT_BYTES, hipMemcpyDeviceToHost, s.stream);
+    if (e == hipSuccess) e = hipEventRecord(s.ev_phase, s.stream);
+    s.phase = FINISH;
+    return e;
+}
 
 hipError_t Server::launch_lanczos(Slot& s) {
     const Plan& p = s.req->plan;
@@ -228,9 +248,9 @@ bool Server::admit(Slot& s, Req* q) {
     if (e == hipSuccess && r.nnz > 0) e = hipMemcpyAsync(base + l.col, r.col, (size_t)r.nnz * 4, hipMemcpyHostToDevice, s.stream);
     if (e == hipSuccess && r.nnz > 0) e = hipMemcpyAsync(base + l.val, r.val, (size_t)r.nnz * vb, hipMemcpyHostToDevice, s.stream);
     if (e == hipSuccess) e = launch_lanczos(s);
-    if (e == hipSuccess) e = hipMemcpyAsync(s.hstate, s.bufs.st, STATE_REPORT_BYTES, hipMemcpyDeviceToHost, s.stream);
-    if (e == hipSuccess) e = hipEventRecord(s.ev_phase, s.stream);
-    s.phase = LANCZOS;
+    // The results go out right behind the iterations, which nearly always
+    // complete the m steps.
+    if (e == hipSuccess) e = launch_results(s, STRICT_PENDING);
     return e == hipSuccess;
 }
 
@@ -285,15 +305,14 @@ void Server::advance(Slot& s) {
             if (e != hipSuccess) complete(s, LZ_ERR_HIP);
             return;
         }
-        hipError_t e = launch_finish(p, s.bufs, s.csr, s.dvals, s.dvecs, 1, s.stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(s.hvals, s.dvals, sizeof(double) * p.K, hipMemcpyDeviceToHost, s.stream);
-        if (e == hipSuccess && q->r.out_vecs)
-            e = hipMemcpyAsync(q->r.out_vecs, s.dvecs, sizeof(double) * p.n * p.K, hipMemcpyDeviceToHost, s.stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(s.hstate, s.bufs.st, STATE_REPORT_BYTES, hipMemcpyDeviceToHost, s.stream);
-        if (e == hipSuccess) e = hipEventRecord(s.ev_phase, s.stream);
-        if (e != hipSuccess) return complete(s, LZ_ERR_HIP);
-        s.phase = FINISH;
+        if (launch_results(s, STRICT_NO) != hipSuccess) return complete(s, LZ_ERR_HIP);
         return;
+    }
+    if (s.phase == FINISH && st->status == LZ_PENDING) {
+        launch_resume(s.bufs, s.stream);
+        s.hstate->status = LZ_OK;
+        s.phase = LANCZOS;
+        return advance(s);
     }
     if (s.phase == FINISH) complete(s, st->status);
 }
@@ -417,6 +436,7 @@ int lz_server_submit(lz_server* srv, const lz_request* req, uint64_t* ticket) {
     auto q = std::make_unique<Req>();
     q->r = *req;
     q->plan = make_plan(req->n, req->nnz, req->K, req->m, req->precision);
+    q->plan.fold = 1;
     // The SpMV variant is fixed when the graph is captured: take the device's
     // relabelling decision on the host, from the caller's row pointer.
     if (!q->plan.sweep && want_xcache(q->plan, true))

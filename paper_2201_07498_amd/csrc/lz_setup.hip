@@ -47,12 +47,24 @@ __global__ void k_reset(State* st, int m, int K, int reorth, int reorder, double
     }
 }
 
+// Where the relabelled copy goes and whether sweep blocks are reserved.
+struct Relabelled {
+    int64_t* rp2;
+    int32_t* col2;
+    void* val2;
+    int32_t* perm;
+    int32_t* iperm;
+    int sweep;
+};
+
 // Input checks before any kernel indexes memory through the CSR arrays:
 // rowptr[0] = 0, rowptr[n] = nnz, rows non-decreasing, 0 <= col < n.  Also
-// finds the longest row.  With col null (entries in host memory) only the
-// row pointers are checked here; k_validate_cols checks each slab.
-__global__ __launch_bounds__(BLOCK) void k_validate(State* st, const int64_t* rp, const int32_t* col, int64_t n,
-                                                    int64_t nnz) {
+// finds the longest row, and the last workgroup to finish chooses the matrix
+// of the solve and publishes its pointers in the state.  With col null (entries
+// in host memory) only the row pointers are checked here; k_validate_cols
+// checks each slab.
+__global__ __launch_bounds__(BLOCK) void k_validate(State* st, const int64_t* rp, const int32_t* col,
+                                                    const void* val, int64_t n, int64_t nnz, Relabelled rl) {
     bool bad = false;
     uint64_t mx = 0;
     const int64_t stride = (int64_t)gridDim.x * BLOCK;
@@ -68,6 +80,7 @@ __global__ __launch_bounds__(BLOCK) void k_validate(State* st, const int64_t* rp
     if (bad) __hip_atomic_store(&st->status, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // One atomic per workgroup (the grid is capped, so contention is small).
     __shared__ uint64_t smx[BLOCK / 64];
+    __shared__ int s_last;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const uint64_t v = __shfl_xor(mx, o, 64);
@@ -80,6 +93,28 @@ __global__ __launch_bounds__(BLOCK) void k_validate(State* st, const int64_t* rp
         if (mx > 0)
             __hip_atomic_fetch_max(&st->maxdeg, (unsigned long long)mx, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (last_block(&st->ticket[TK_INIT], gridDim.x, &s_last) && threadIdx.x == 0) {
+        const int opt = st->reorder;
+        const int status = __hip_atomic_load(&st->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long longest =
+            __hip_atomic_load(&st->maxdeg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bool use = false;
+        if (status == 0 && n > 1 && nnz > 0) {
+            if (opt == LZ_REORDER_HUBS) use = true;
+            if (opt == LZ_REORDER_AUTO)
+                use = n >= REORDER_MIN_N && (double)longest * (double)n >= REORDER_SKEW * (double)nnz;
+        }
+        st->reordered = use ? 1 : 0;
+        st->packed = !use ? PACK_NONE
+                     : rl.sweep ? PACK_SWEEP
+                     : n <= (int64_t(1) << GROUP_COLBITS) ? PACK_GROUP
+                     : n < (int64_t(1) << PACK_COLBITS) ? PACK_TILE : PACK_NONE;
+        st->crp = use ? rl.rp2 : rp;
+        st->ccol = use ? rl.col2 : col;
+        st->cval = use ? rl.val2 : val;
+        st->perm = use ? rl.perm : nullptr;
+        st->iperm = use ? rl.iperm : nullptr;
     }
 }
 
@@ -98,30 +133,6 @@ void launch_validate_cols(State* st, const int32_t* col, int64_t e0, int64_t e1,
     if (e1 <= e0) return;
     const int g = (int)std::min<int64_t>((e1 - e0 + BLOCK - 1) / BLOCK, 1024);
     hipLaunchKernelGGL(k_validate_cols, dim3(g), dim3(BLOCK), 0, s, st, col, e0, e1, n);
-}
-
-// Chooses the matrix of the solve and publishes its pointers in the state.
-__global__ void k_reorder_decide(State* st, const int64_t* rp, const int32_t* col, const void* val, int64_t n,
-                                 int64_t nnz, int64_t* rp2, int32_t* col2, void* val2, int32_t* perm,
-                                 int32_t* iperm, int sweep) {
-    if (threadIdx.x != 0) return;
-    const int opt = st->reorder;
-    bool use = false;
-    if (st->status == 0 && n > 1 && nnz > 0) {
-        if (opt == LZ_REORDER_HUBS) use = true;
-        if (opt == LZ_REORDER_AUTO)
-            use = n >= REORDER_MIN_N && (double)st->maxdeg * (double)n >= REORDER_SKEW * (double)nnz;
-    }
-    st->reordered = use ? 1 : 0;
-    st->packed = !use ? PACK_NONE
-                 : sweep ? PACK_SWEEP
-                 : n <= (int64_t(1) << GROUP_COLBITS) ? PACK_GROUP
-                 : n < (int64_t(1) << PACK_COLBITS) ? PACK_TILE : PACK_NONE;
-    st->crp = use ? rp2 : rp;
-    st->ccol = use ? col2 : col;
-    st->cval = use ? val2 : val;
-    st->perm = use ? perm : nullptr;
-    st->iperm = use ? iperm : nullptr;
 }
 
 // ------------------------------------------------------------- scans
@@ -580,6 +591,12 @@ bool host_relabel_decision(const int64_t* rp, int64_t n, int64_t nnz, int reorde
     return (double)mx * (double)n >= REORDER_SKEW * (double)nnz;
 }
 
+__global__ void k_resume(State* st) {
+    if (st->status == LZ_PENDING) st->status = 0;
+}
+
+void launch_resume(const Bufs& b, hipStream_t s) { hipLaunchKernelGGL(k_resume, dim3(1), dim3(1), 0, s, b.st); }
+
 hipError_t launch_setup(const Plan& p, const Bufs& b, const Csr& a, uint64_t seed, int reorth, int reorder,
                         hipStream_t s) {
     hipLaunchKernelGGL(k_reset, dim3(1), dim3(BLOCK), 0, s, b.st, p.m, p.K, reorth, reorder, unit_roundoff(p.prec),
@@ -587,11 +604,13 @@ hipError_t launch_setup(const Plan& p, const Bufs& b, const Csr& a, uint64_t see
     const int64_t n = a.n, nnz = a.nnz;
     const int g = (int)std::min<int64_t>((n + BLOCK - 1) / BLOCK, 8192);
     const int gv = (int)std::min<int64_t>((std::max(n, nnz) + BLOCK - 1) / BLOCK, 1024);
-    hipLaunchKernelGGL(k_validate, dim3(gv), dim3(BLOCK), 0, s, b.st, a.rowptr, a.col, n, nnz);
-    hipLaunchKernelGGL(k_reorder_decide, dim3(1), dim3(64), 0, s, b.st, a.rowptr, a.col, a.val, n, nnz, b.rp2,
-                       b.col2, b.val2, b.perm, b.iperm, p.sweep);
+    hipLaunchKernelGGL(k_validate, dim3(gv), dim3(BLOCK), 0, s, b.st, a.rowptr, a.col, a.val, n, nnz,
+                       Relabelled{b.rp2, b.col2, b.val2, b.perm, b.iperm, p.sweep});
+    // The device cannot choose the relabelling where these rule it out, and its
+    // kernels (11 to 14 that would return at once) are not launched.
+    const bool relabel = reorder == LZ_REORDER_HUBS || (reorder == LZ_REORDER_AUTO && n >= REORDER_MIN_N);
     const int32_t* gate = &b.st->reordered;
-    if (reorder != LZ_REORDER_OFF) {
+    if (relabel) {
         const int64_t nch = (n + CHR - 1) / CHR;
         hipLaunchKernelGGL(k_rl_hist, dim3((unsigned)nch), dim3(BLOCK), 0, s, b.st, a.rowptr, n, nch, b.scan);
         launch_scan(gate, b.scan, NKEY * nch, b.bsum, s);
@@ -601,7 +620,7 @@ hipError_t launch_setup(const Plan& p, const Bufs& b, const Csr& a, uint64_t see
         launch_scan(gate, (uint64_t*)b.rp2, n, b.bsum, s);
     }
     hipLaunchKernelGGL(k_setup_tiles, dim3(g), dim3(BLOCK), 0, s, b.st, n, p.n_tiles, b.ob, b.tk);
-    if (reorder != LZ_REORDER_OFF) {
+    if (relabel) {
         launch_sweep_blocks(p, b, s);             // the relabelling fill writes the sort payload by block
         switch (p.prec) {
             case 0:

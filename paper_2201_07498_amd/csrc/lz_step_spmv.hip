@@ -66,7 +66,7 @@ __global__ __launch_bounds__(NW * 64) void k_spmv_step(State* st, const typename
     // on the caller's, -1 always.
     if (gate >= 0 && (st->reordered != 0) != (gate == 1)) return;
     const int j = st->j;
-    if (j >= st->m) return;
+    if (j >= st->m || st->remeasure == 2) return;
     if (st->mode == MODE_RESTART) {
         // Restart: a fresh random vector; the Gram-Schmidt kernels that follow
         // orthogonalise it against the basis.
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(SWT_THREADS) void k_sweep_tail(const State* st, con
     __shared__ int64_t start[SW_PANELS_MAX + 1];
     if (st->status != 0 || !st->reordered || st->packed != PACK_SWEEP) return;
     const int j = st->j;
-    if (j >= st->m || st->mode == MODE_RESTART) return;
+    if (j >= st->m || st->remeasure == 2 || st->mode == MODE_RESTART) return;
     const VT* __restrict__ x = Vb + (int64_t)j * ld;
     const int np = ta.np, t = threadIdx.x;
     for (int i = t; i <= np; i += SWT_THREADS) start[i] = (int64_t)ta.pre[i * ta.nb];
