@@ -81,7 +81,8 @@ __global__ __launch_bounds__(BLOCK) void k_init(State* st, typename Tr<P>::V* V,
 // from it; the one-pass modes run the classical second pass only for a
 // restart vector (always orthogonalised twice).
 __device__ __forceinline__ bool dot_active(const State* st) {
-    return st->reorth != 0 || st->mode == MODE_RESTART;
+    const int reorth = st->reorth, mode = st->mode;
+    return (reorth != 0) | (mode == MODE_RESTART);
 }
 __device__ __forceinline__ bool gram_mode(const State* st) { return st->reorth >= 2; }
 __device__ __forceinline__ bool upd_dot_active(const State* st) {
@@ -265,8 +266,9 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_dot(State* st, const typename T
     __shared__ A s_tot[1];
     __shared__ A sred[OBLOCK];
     __shared__ int s_last;
-    const int j = st->j;
-    if (st->status != 0 || j >= st->m || st->remeasure == 2 || !dot_active(st)) return;
+    const int j = st->j, status = st->status, m = st->m, remeasure = st->remeasure;   // one round of loads
+    const bool active = dot_active(st);
+    if (status != 0 || j >= m || remeasure == 2 || !active) return;
     const int nc = j + 1;
     if (nc > NC) {                       // launch contract broken: flag, do nothing
         if (blockIdx.x == 0 && threadIdx.x == 0) st->status = -1;
@@ -533,24 +535,25 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_store(State* st, typename T
         c2k = st->c2[threadIdx.x];
         sk = st->scale[threadIdx.x];
     }
-    const int j = st->j;
-    if (st->status != 0 || j >= st->m) return;
+    const int j = st->j, status = st->status, m = st->m, mode_now = st->mode, remeasure = st->remeasure,
+              reorth = st->reorth, second_now = st->second;
+    if (status != 0 || j >= m) return;
     const int nc = j + 1;
     if (nc > NC) {
         if (blockIdx.x == 0 && threadIdx.x == 0) st->status = -1;
         return;
     }
     if constexpr (FOLD) {
-        if (st->remeasure != 2 && upd_dot_active(st)) {
+        if (GRAM ? remeasure == 1 : mode_now == MODE_RESTART && remeasure != 2) {
             if (orth_measure<P, NC, A>(st, Vb, w, ld, nc, part, part2, sh) && threadIdx.x == 0) st->remeasure = 2;
             return;
         }
     }
     // The Gram variant runs in the two-pass modes, where every column takes
     // part in the update.
-    const bool second = GRAM || st->second != 0;
+    const bool second = GRAM || second_now != 0;
     constexpr bool gram = GRAM;
-    const int lo = (!GRAM && st->reorth == 0 && st->mode != MODE_RESTART) ? j : 0;
+    const int lo = (!GRAM && reorth == 0 && mode_now != MODE_RESTART) ? j : 0;
     if ((int)threadIdx.x < NC) {
         const int k = threadIdx.x;
         coef[k] = (second && k >= lo && k < nc) ? (A)c2k * (A)sk : A(0);

@@ -60,14 +60,17 @@ __global__ __launch_bounds__(NW * 64) void k_spmv_step(State* st, const typename
     __shared__ E shd[NW];
     __shared__ int s_last;
     __shared__ VT xs[H];
-    if (st->status != 0) return;
+    // One round of loads for everything the launch depends on.
+    const int status = st->status, j = st->j, m = st->m, mode = st->mode, remeasure = st->remeasure,
+              reorth = st->reorth, st_packed = st->packed;
+    const bool rl = st->reordered != 0;
+    if (status != 0) return;
     // Gated launch (the row order is decided on the device and the host does
     // not wait for it): gate 1 runs only on the relabelled matrix, gate 0 only
     // on the caller's, -1 always.
-    if (gate >= 0 && (st->reordered != 0) != (gate == 1)) return;
-    const int j = st->j;
-    if (j >= st->m || st->remeasure == 2) return;
-    if (st->mode == MODE_RESTART) {
+    if (gate >= 0 && rl != (gate == 1)) return;
+    if (j >= m || remeasure == 2) return;
+    if (mode == MODE_RESTART) {
         // Restart: a fresh random vector; the Gram-Schmidt kernels that follow
         // orthogonalise it against the basis.
         if (slab != 0) return;
@@ -77,7 +80,6 @@ __global__ __launch_bounds__(NW * 64) void k_spmv_step(State* st, const typename
             w[r] = (WT)(r < n ? u01(rs, (uint64_t)(perm ? perm[r] : r)) : 0.0);
         return;
     }
-    const bool rl = st->reordered != 0;
     const int64_t* rp = rl ? rp_b : rp_a;
     const int32_t* col = rl ? col_b : col_a;
     const VT* val = (const VT*)(rl ? val_b : val_a);
@@ -90,7 +92,7 @@ __global__ __launch_bounds__(NW * 64) void k_spmv_step(State* st, const typename
     // row adds one term per piece and the w update waits for the whole sum.
     // In the two-pass modes alpha comes from the first Gram-Schmidt pass
     // (alpha_j = c_j + beta_j v_j . v_{j-1}); only the other modes reduce it here.
-    const bool need_alpha = st->reorth < 2;
+    const bool need_alpha = reorth < 2;
     auto pre = [&](int64_t r) { return xp ? to_d(xp[r]) : 0.0; };
     auto row = [&](int64_t r, double acc, double xpr) {
         const E y = sj * (E)acc;
@@ -107,7 +109,7 @@ __global__ __launch_bounds__(NW * 64) void k_spmv_step(State* st, const typename
         for (int i = threadIdx.x; i < hn; i += NW * 64) xs[i] = x[i];
         __syncthreads();
     }
-    const int packing = rl ? st->packed : PACK_NONE;
+    const int packing = rl ? st_packed : PACK_NONE;
     if constexpr (SWEEP != SWEEP_NO) {
         if (packing != PACK_SWEEP) return;
         spmv_sweep<VT, NW, SweepShape<P>::ROWS, SWEEP == SWEEP_TAIL, OFF32>(sw, rp, x, n, tk, head, tail, pre, row, piece, fin);
@@ -128,7 +130,7 @@ __global__ __launch_bounds__(NW * 64) void k_spmv_step(State* st, const typename
         const double alpha = (double)(E)ordered_sum_dev(part, nslab * (int)gridDim.x, shs);
         if (threadIdx.x == 0) {
             st->alpha[j] = alpha;
-            if (st->reorth == 0) {          // three-term recurrence only
+            if (reorth == 0) {              // three-term recurrence only
                 st->c2[j] = alpha;
                 st->second = 1;
             }
