@@ -495,37 +495,22 @@ __global__ __launch_bounds__(BLOCK) void k_colstats(State* st, const double* __r
 
 // Residual check (Sec. IV-D) in FP64 for all K Ritz pairs at once.
 // First Z = A Y (stored matrix values upcast exactly) over the SpMV tiles:
-// each wavefront stages its tile's col/val in LDS (values in the storage
-// precision, upcast when used); lane k of a group of KB2
-// lanes owns pair k and gathers K-wide rows of Y.  Rows are spread over the
-// 64/KB2 groups; a row longer than LONGZ, and a split row's piece, is shared
-// by all groups.  Split rows are finished by their last piece as in the
-// SpMV, the pieces added in tile order.
-constexpr int LONGZ = 32;
-
-// sum over p = p0, p0+step, ... < e of sval[p] * Y[scol[p]][k].  Eight
-// gathers per lane are issued together, those past the end clamped to the
-// batch's first entry and discarded, so a row of up to eight entries costs
-// one round of requests; fixed association order.
-template <class VT>
-__device__ __forceinline__ double gather_dot(const int* scol, const VT* sval, int p0, int e, int step,
-                                             const double* __restrict__ Y, int K, int k) {
-    double z[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int p = p0; p < e; p += 8 * step) {
-        double y[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int q = p + i * step < e ? p + i * step : p;
-            y[i] = Y[(int64_t)scol[q] * K + k];
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int q = p + i * step;
-            z[i] += q < e ? to_d(sval[q]) * y[i] : 0.0;
-        }
-    }
-    return ((z[0] + z[1]) + (z[2] + z[3])) + ((z[4] + z[5]) + (z[6] + z[7]));
-}
+// each wavefront stages its tile's col/val in LDS in row order (values in the
+// storage precision, upcast when used); lane k of a group of KB2 lanes owns
+// pair k and gathers K-wide rows of Y.  The tile's entries are split evenly
+// over the 64/KB2 groups, whatever rows they belong to: a group keeps SPMM_U
+// gathers in flight and closes a row where the column word carries its mark.
+// (By rows, a group had at most the eight gathers of one row in flight, and a
+// long row kept three of four groups waiting: R-MAT 20 K = 16 FP32 / FP64 558 /
+// 686 -> 290 / 410 us, R-MAT 150k FP64 142 -> 50 us, R-MAT 23 K = 24 BF16 11.7 ->
+// 7.9 ms, R-MAT 25 K = 8 FP32 18.7 -> 16.6 ms; ER 500k FP32, whose gathers all
+// miss L2, 174 -> 172 us.)  Rows cut by a group's bounds are joined in group order,
+// rows cut by tile bounds by their last piece as in the SpMV, the pieces added
+// in tile order.
+// Gathers per lane of 8 / 12 / 16 / 24: finish of R-MAT 20 FP32 0.99 / 0.98 /
+// 1.03 / 1.02 ms, R-MAT 25 FP32 24.97 / 25.01 / 25.44 / 25.47 ms.
+constexpr int SPMM_U = 12;
+constexpr int SPMM_END = (int)0x80000000;      // mark of a row's last entry
 
 // Adds the groups' values (lanes that differ in the group bits), fixed order.
 __device__ __forceinline__ double group_sum(double v, int KB2) {
@@ -545,6 +530,7 @@ __global__ __launch_bounds__(BLOCK) void k_spmm(State* st, const double* __restr
     using VT = typename Tr<P>::V;
     __shared__ int scol_all[WAVES][TILE];
     __shared__ VT sval_all[WAVES][TILE];
+    __shared__ uint16_t srow_all[WAVES][TILE];
     if (st->status != 0) return;
     const bool rl = st->reordered != 0;
     const int packing = rl ? st->packed : PACK_NONE;
@@ -557,6 +543,7 @@ __global__ __launch_bounds__(BLOCK) void k_spmm(State* st, const double* __restr
     const bool act = k < K;
     int* scol = scol_all[threadIdx.x >> 6];
     VT* sval = sval_all[threadIdx.x >> 6];
+    uint16_t* srow = srow_all[threadIdx.x >> 6];
     // Pieces of split row r (tail pieces in t1..t2-1, head piece in t2),
     // added group-strided in tile order; the whole row sum in every group.
     auto split_total_k = [&](int64_t t1, int64_t t2) {
@@ -567,58 +554,100 @@ __global__ __launch_bounds__(BLOCK) void k_spmm(State* st, const double* __restr
         return act ? z + ld_dev(&head[t2 * KB2 + k]) : 0.0;
     };
     // Rows of tile t from its entries in row order, scol/sval[0..cnt).
-    auto tile_body = [&](int64_t t, const int* scol, const VT* sval) {
+    auto tile_body = [&](int64_t t, int* scol, const VT* sval, uint16_t* srow) {
         const int64_t r_lo = ob[t], r_hi = ob[t + 1];
         const int64_t t0 = t * TILE - r_lo;
         const int cnt = (int)(min<int64_t>((t + 1) * TILE, nnz + n) - r_hi - t0);
-        const bool split_head = r_lo < r_hi && rp[r_lo] < t0;
-        double head_z = 0.0;
-        for (int64_t base = r_lo; base < r_hi; base += G) {
-            const int64_t r = base + g;
-            const bool valid = r < r_hi;
-            int b = 0, e = 0;
-            if (valid) {
-                b = (int)(max(rp[r], t0) - t0);
-                e = (int)(rp[r + 1] - t0);
-            }
-            const bool islong = valid && e - b > LONGZ;
-            double z = (valid && !islong && act) ? gather_dot(scol, sval, b, e, 1, Y, K, k) : 0.0;
-            uint64_t mask = __ballot(islong && k == 0);
-            while (mask) {
-                const int L = __builtin_ctzll(mask);
-                mask &= mask - 1;
-                const int bL = lane_value(b, L), eL = lane_value(e, L);
-                double zz = act ? gather_dot(scol, sval, bL + g, eL, G, Y, K, k) : 0.0;
-                zz = group_sum(zz, KB2);
-                if (g == L / KB2) z = zz;
-            }
-            if (valid && act) {
-                if (split_head && r == r_lo)
-                    head_z = z;
-                else
-                    Z[r * K + k] = z;
-            }
-        }
-        if (split_head) {
-            if (g == 0 && act) st_dev(&head[t * KB2 + k], head_z);
-            const int64_t t1 = item_tile(rp[r_lo] + r_lo, n_tiles);
-            if (last_wave(&tk[t], (uint32_t)(t - t1 + 1))) {
-                const double z = split_total_k(t1, t);
-                if (g == 0 && act) Z[r_lo * K + k] = z;
-            }
-        }
-        if (r_hi < n) {
-            const int64_t rb = rp[r_hi];
-            if (rb < t0 + cnt) {
-                double zz = act ? gather_dot(scol, sval, (int)(max(rb, t0) - t0) + g, cnt, G, Y, K, k) : 0.0;
-                zz = group_sum(zz, KB2);
-                if (g == 0 && act) st_dev(&tail[t * KB2 + k], zz);
-                const int64_t t1 = item_tile(rb + r_hi, n_tiles), t2 = row_owner(rp, r_hi, n_tiles);
-                if (last_wave(&tk[t2], (uint32_t)(t2 - t1 + 1))) {
-                    const double z = split_total_k(t1, t2);
-                    if (g == 0 && act) Z[r_hi * K + k] = z;
+        const int64_t rb_lo = r_lo < n ? rp[r_lo] : 0, rb_hi = r_hi < n ? rp[r_hi] : 0,
+                      re_hi = r_hi < n ? rp[r_hi + 1] : 0;
+        const bool split_head = r_lo < r_hi && rb_lo < t0, split_tail = r_hi < n && rb_hi < t0 + cnt;
+        // Mark every owned row's last entry; rows without entries are zero.
+        for (int64_t base = r_lo; base < r_hi; base += 64) {
+            const int64_t r = base + lane;
+            bool empty = false;
+            if (r < r_hi) {
+                const int b = (int)(max(rp[r], t0) - t0), e = (int)(rp[r + 1] - t0);
+                if (e > b) {
+                    scol[e - 1] |= SPMM_END;
+                    srow[e - 1] = (uint16_t)(r - r_lo);
+                } else {
+                    empty = !(split_head && r == r_lo);
                 }
             }
+            const uint64_t mask = __ballot(empty);
+            if (mask)
+                for (int i = g; i < 64; i += G)
+                    if (((mask >> i) & 1) && act) Z[(base + i) * K + k] = 0.0;
+        }
+        wave_sync();
+        // Group g takes entries [lo, hi).  The first row it closes may have
+        // begun in an earlier group: its sum waits in first_z, that of the row
+        // left open in acc.
+        const int S = (cnt + G - 1) / G, lo = min(g * S, cnt), hi = min(lo + S, cnt);
+        double acc = 0.0, first_z = 0.0;
+        int first_row = -1;
+        for (int p = lo; p < hi; p += SPMM_U) {
+            int w[SPMM_U];
+            double y[SPMM_U];
+#pragma unroll
+            for (int i = 0; i < SPMM_U; ++i) w[i] = scol[min(p + i, hi - 1)];
+#pragma unroll
+            for (int i = 0; i < SPMM_U; ++i) y[i] = act ? Y[(int64_t)(w[i] & ~SPMM_END) * K + k] : 0.0;
+#pragma unroll
+            for (int i = 0; i < SPMM_U; ++i) {
+                if (p + i < hi) {
+                    acc = fma(to_d(sval[p + i]), y[i], acc);
+                    if (w[i] < 0) {
+                        const int row = srow[p + i];
+                        if (first_row < 0) {
+                            first_row = row;
+                            first_z = acc;
+                        } else if (act) {
+                            Z[(r_lo + row) * K + k] = acc;
+                        }
+                        acc = 0.0;
+                    }
+                }
+            }
+        }
+        // Rows across the groups, in group order; every lane follows its pair.
+        double carry = 0.0, head_z = 0.0;
+        for (int gg = 0; gg < G; ++gg) {
+            const int row = lane_value(first_row, gg * KB2);
+            const double open = __shfl(acc, gg * KB2 + k, 64);
+            if (row >= 0) {
+                const double z = carry + __shfl(first_z, gg * KB2 + k, 64);
+                if (split_head && row == 0)
+                    head_z = z;
+                else if (g == 0 && act)
+                    Z[(r_lo + row) * K + k] = z;
+                carry = open;
+            } else {
+                carry += open;
+            }
+        }
+        if (!split_head && !split_tail) return;
+        // Pieces of split rows: published together, tickets taken together.
+        const int64_t h1 = split_head ? item_tile(rb_lo + r_lo, n_tiles) : 0;
+        const int64_t t1 = split_tail ? item_tile(rb_hi + r_hi, n_tiles) : 0;
+        const int64_t t2 = split_tail ? item_tile(re_hi + r_hi, n_tiles) : 0;
+        if (g == 0 && act) {
+            if (split_head) st_dev(&head[t * KB2 + k], head_z);
+            if (split_tail) st_dev(&tail[t * KB2 + k], carry);
+        }
+        __builtin_amdgcn_s_waitcnt(0);
+        uint32_t got = 0;
+        if ((lane == 0 && split_head) || (lane == 1 && split_tail))
+            got = __hip_atomic_fetch_add(lane == 0 ? &tk[t] : &tk[t2], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (split_head && (uint32_t)lane_value((int)got, 0) == (uint32_t)(t - h1)) {
+            if (lane == 0) __hip_atomic_store(&tk[t], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const double z = split_total_k(h1, t);
+            if (g == 0 && act) Z[r_lo * K + k] = z;
+        }
+        if (split_tail && (uint32_t)lane_value((int)got, 1) == (uint32_t)(t2 - t1)) {
+            if (lane == 0) __hip_atomic_store(&tk[t2], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const double z = split_total_k(t1, t2);
+            if (g == 0 && act) Z[r_hi * K + k] = z;
         }
     };
     if (packing == PACK_GROUP) {
@@ -645,7 +674,7 @@ __global__ __launch_bounds__(BLOCK) void k_spmm(State* st, const double* __restr
             const int64_t t = tg + w;
             if (t < n_tiles) {
                 const int off = (int)(t * TILE - ob[t] - g0);
-                tile_body(t, gcol + off, gval + off);
+                tile_body(t, gcol + off, gval + off, &srow_all[0][0] + off);
             }
             __syncthreads();
         }
@@ -664,7 +693,7 @@ __global__ __launch_bounds__(BLOCK) void k_spmm(State* st, const double* __restr
             sval[sl] = val[t0 + i];
         }
         wave_sync();
-        tile_body(t, scol, sval);
+        tile_body(t, scol, sval, srow);
         wave_sync();
     }
 }
@@ -990,7 +1019,9 @@ static hipError_t finish_p(const Plan& p, const Bufs& b, const Csr& a, double* o
                                       });
         if (e != hipSuccess) return e;
     } else if (report) {
-        hipLaunchKernelGGL((k_spmm<P>), dim3(p.g_tile), dim3(BLOCK), 0, s, b.st, b.Y, b.Z, p.n, p.nnz, p.n_tiles,
+        // Up to 8192 workgroups: 2048 took 0.5 ms more at R-MAT 23 and 25.
+        const unsigned gt = (unsigned)(std::min<int64_t>(1024, (p.n_tiles + 8 * WAVES - 1) / (8 * WAVES)) * 8);
+        hipLaunchKernelGGL((k_spmm<P>), dim3(gt), dim3(BLOCK), 0, s, b.st, b.Y, b.Z, p.n, p.nnz, p.n_tiles,
                            b.ob, b.tk, b.head, b.tail, kb2, a.rowptr, a.col, a.val, b.rp2, b.col2, b.val2,
                            (int64_t)0, p.n_tiles);
     }
