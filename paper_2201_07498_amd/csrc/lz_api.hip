@@ -71,7 +71,7 @@ Plan make_plan(int64_t n, int64_t nnz, int32_t K, int32_t m, int32_t prec, bool 
     p.off_bsum = take((size_t)(ceil_div(scan_n, 2048) + 2) * 8);
     p.off_Y = take((size_t)n * (size_t)K * 8);
     p.off_Z = take((size_t)n * (size_t)K * 8);
-    p.off_gram = take((size_t)(GRAM_PARTS + 1) * 64 * 64 * 8);
+    p.off_gram = take((size_t)GRAM_DOUBLES * 8);
     p.off_ob = take((size_t)(p.n_tiles + 1) * 4);
     p.off_tk = take((size_t)p.n_tiles * 4);
     p.off_head = take((size_t)p.n_tiles * kb2 * 8);
@@ -805,14 +805,14 @@ int lz_ortho_loss(const void* X, int64_t ldx, int64_t n, int32_t c, int32_t prec
     hst->j = c;
     hst->m = c;
     for (int k = 0; k < c; ++k) hst->scale[k] = 1.0;
-    if (hipMalloc((void**)&d, so + (size_t)(GRAM_PARTS + 1) * 64 * 64 * 8) != hipSuccess) {
+    if (hipMalloc((void**)&d, so + (size_t)GRAM_DOUBLES * 8) != hipSuccess) {
         delete hst;
         return LZ_ERR_OUT_OF_MEMORY;
     }
     {
         State* st = (State*)d;
         LZ_HIP(hipMemcpyAsync(st, hst, sizeof(State), hipMemcpyHostToDevice, s));
-        LZ_HIP(launch_gram_only(precision, X, ldx, n, st, (double*)(d + so), s));
+        LZ_HIP(launch_gram_only(precision, X, ldx, n, c, st, (double*)(d + so), s));
         LZ_HIP(hipMemcpyAsync(hst, st, sizeof(State), hipMemcpyDeviceToHost, s));
         LZ_HIP(hipStreamSynchronize(s));
         *out_loss = hst->ortho_loss;

@@ -407,89 +407,102 @@ __global__ __launch_bounds__(BLOCK) void k_ritz(const State* st, const typename 
 // Per Ritz column k: norm and the entry of largest modulus (lowest original
 // row on ties) -> ysc[k] = sign(that entry) / norm.  Lane k of each group of
 // KB2 lanes owns column k.  NOROW marks "no row yet" (exact as a double and
-// as an int64).
+// as an int64).  The original row is looked up only where moduli tie and for
+// the winners; values are joined across the lanes of a wavefront, the
+// wavefronts and the workgroups in a fixed order.  Measured, R-MAT 20 K = 16:
+// 77 -> 49 us (a row lookup per entry, 64 serial joins through LDS),
+// n = 3000 K = 4: 19 -> 6 us.
 constexpr int64_t NOROW = int64_t(1) << 62;
+struct ColStat {
+    double nrm, mod, val;     // sum of squares; largest modulus and its value
+    int64_t row;              // its original row
+};
+__device__ __forceinline__ void join(ColStat& a, double nrm, double mod, double val, int64_t row) {
+    a.nrm += nrm;
+    if (mod > a.mod || (mod == a.mod && row < a.row)) {
+        a.mod = mod;
+        a.val = val;
+        a.row = row;
+    }
+}
+__device__ __forceinline__ void join_lanes(ColStat& a, int KB2) {
+    for (int o = KB2; o < 64; o <<= 1) {
+        const double nrm = __shfl_xor(a.nrm, o, 64), mod = __shfl_xor(a.mod, o, 64), val = __shfl_xor(a.val, o, 64);
+        const int64_t row = __shfl_xor((long long)a.row, o, 64);
+        join(a, nrm, mod, val, row);
+    }
+}
 __global__ __launch_bounds__(BLOCK) void k_colstats(State* st, const double* __restrict__ Y, int64_t n, int KB2,
                                                     double* part) {
-    __shared__ double s_n[BLOCK], s_a[BLOCK], s_v[BLOCK];
-    __shared__ int64_t s_i[BLOCK];
+    __shared__ ColStat sw[WAVES][64];
     __shared__ int s_last;
     if (st->status != 0) return;
     const int K = st->K, G = gridDim.x;
     const int groups = BLOCK / KB2, g = threadIdx.x / KB2, k = threadIdx.x % KB2;
-    double nrm = 0.0, best = -1.0, bval = 0.0;
-    int64_t bidx = NOROW;
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int32_t* perm = st->perm;
-    auto visit = [&](int64_t r, double v) {
-        nrm += v * v;
-        const double a = fabs(v);
-        const int64_t ro = perm ? perm[r] : r;
-        if (a > best || (a == best && ro < bidx)) { best = a; bval = v; bidx = ro; }
-    };
+    auto original = [&](int64_t r) { return perm ? (int64_t)perm[r] : r; };
+    ColStat a{0.0, -1.0, 0.0, NOROW};
     if (k < K) {
+        int64_t best = -1;                         // row of the largest modulus so far, in the solve's order
+        auto visit = [&](int64_t r, double v) {
+            a.nrm += v * v;
+            const double m = fabs(v);
+            if (m > a.mod || (m == a.mod && original(r) < original(best))) {
+                a.mod = m;
+                a.val = v;
+                best = r;
+            }
+        };
         const int64_t S = (int64_t)G * groups;
         int64_t r = (int64_t)blockIdx.x * groups + g;
-        for (; r + 3 * S < n; r += 4 * S) {       // four rows in flight
-            const double v0 = Y[r * K + k], v1 = Y[(r + S) * K + k], v2 = Y[(r + 2 * S) * K + k],
-                         v3 = Y[(r + 3 * S) * K + k];
-            visit(r, v0);
-            visit(r + S, v1);
-            visit(r + 2 * S, v2);
-            visit(r + 3 * S, v3);
+        for (; r + 7 * S < n; r += 8 * S) {       // eight rows in flight
+            double v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = Y[(r + i * S) * K + k];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) visit(r + i * S, v[i]);
         }
         for (; r < n; r += S) visit(r, Y[r * K + k]);
+        if (best >= 0) a.row = original(best);
     }
-    s_n[threadIdx.x] = nrm; s_a[threadIdx.x] = best; s_v[threadIdx.x] = bval; s_i[threadIdx.x] = bidx;
-    __syncthreads();
+    // Within a workgroup; lanes 0 .. KB2 - 1 of the first wavefront end with
+    // the workgroup's values.
+    auto join_block = [&]() {
+        join_lanes(a, KB2);
+        __syncthreads();
+        if (lane < KB2) sw[wv][lane] = a;
+        __syncthreads();
+        if (wv == 0 && lane < KB2)
+            for (int w = 1; w < WAVES; ++w) join(a, sw[w][lane].nrm, sw[w][lane].mod, sw[w][lane].val, sw[w][lane].row);
+    };
+    join_block();
     if ((int)threadIdx.x < K) {
-        double tn = 0.0, ta = -1.0, tv = 0.0;
-        int64_t ti = NOROW;
-        for (int gg = 0; gg < groups; ++gg) {
-            const int t = gg * KB2 + threadIdx.x;
-            tn += s_n[t];
-            if (s_a[t] > ta || (s_a[t] == ta && s_i[t] < ti)) { ta = s_a[t]; tv = s_v[t]; ti = s_i[t]; }
-        }
         double* pb = part + ((int64_t)blockIdx.x * 64 + threadIdx.x) * 4;
-        st_dev(pb + 0, tn);
-        st_dev(pb + 1, ta);
-        st_dev(pb + 2, tv);
-        st_dev(pb + 3, (double)ti);
+        st_dev(pb + 0, a.nrm);
+        st_dev(pb + 1, a.mod);
+        st_dev(pb + 2, a.val);
+        st_dev(pb + 3, (double)a.row);
     }
     if (last_block(&st->ticket[TK_RITZ], (uint32_t)G, &s_last)) {
-        // Thread (g, k) folds workgroups g, g + groups, ... of column k (four
-        // loads in flight), then the groups are folded in order.
-        double tn = 0.0, ta = -1.0, tv = 0.0, ti = (double)NOROW;
-        auto fold = [&](const double* pb) {
-            const double nn = ld_dev(pb), a = ld_dev(pb + 1), v = ld_dev(pb + 2), i = ld_dev(pb + 3);
-            tn += nn;
-            if (a > ta || (a == ta && i < ti)) { ta = a; tv = v; ti = i; }
-        };
-        if (k < K) {
-            int b = g;
-            for (; b + 3 * groups < G; b += 4 * groups) {
-                const double* p0 = part + ((int64_t)b * 64 + k) * 4;
-                const double* p1 = part + ((int64_t)(b + groups) * 64 + k) * 4;
-                const double* p2 = part + ((int64_t)(b + 2 * groups) * 64 + k) * 4;
-                const double* p3 = part + ((int64_t)(b + 3 * groups) * 64 + k) * 4;
-                fold(p0);
-                fold(p1);
-                fold(p2);
-                fold(p3);
+        // Thread (g, k) joins workgroups g, g + groups, ... of column k, four
+        // loads in flight (past the end: the last one's, not joined).
+        a = ColStat{0.0, -1.0, 0.0, NOROW};
+        if (k < K)
+            for (int b = g; b < G; b += 4 * groups) {
+                double v[4][4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const double* pb = part + ((int64_t)min(b + i * groups, G - 1) * 64 + k) * 4;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) v[i][q] = ld_dev(pb + q);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (b + i * groups < G) join(a, v[i][0], v[i][1], v[i][2], (int64_t)v[i][3]);
             }
-            for (; b < G; b += groups) fold(part + ((int64_t)b * 64 + k) * 4);
-        }
-        s_n[threadIdx.x] = tn; s_a[threadIdx.x] = ta; s_v[threadIdx.x] = tv; s_i[threadIdx.x] = (int64_t)ti;
-        __syncthreads();
-        if ((int)threadIdx.x < K) {
-            double n2 = 0.0, a2 = -1.0, v2 = 0.0;
-            int64_t i2 = NOROW;
-            for (int gg = 0; gg < groups; ++gg) {
-                const int t = gg * KB2 + threadIdx.x;
-                n2 += s_n[t];
-                if (s_a[t] > a2 || (s_a[t] == a2 && s_i[t] < i2)) { a2 = s_a[t]; v2 = s_v[t]; i2 = s_i[t]; }
-            }
-            st->ysc[threadIdx.x] = (v2 < 0.0 ? -1.0 : 1.0) / sqrt(n2);
-        }
+        join_block();
+        if ((int)threadIdx.x < K) st->ysc[threadIdx.x] = (a.val < 0.0 ? -1.0 : 1.0) / sqrt(a.nrm);
     }
 }
 
@@ -698,62 +711,6 @@ __global__ __launch_bounds__(BLOCK) void k_spmm(State* st, const double* __restr
     }
 }
 
-// Residuals ||A y_k - theta_k y_k|| = ||ysc_k Z[:,k] - theta_k ysc_k Y[:,k]||
-// (Sec. IV-D), streaming Y and Z in the solve's row order; thread (g, k)
-// sums rows g, g + groups, ... of pair k (four rows in flight), workgroup
-// partials are added in a fixed order by the last workgroup.
-__global__ __launch_bounds__(BLOCK) void k_resid(State* st, const double* __restrict__ Y,
-                                                 const double* __restrict__ Z, int64_t n, int KB2, double* part) {
-    __shared__ double shz[BLOCK];
-    __shared__ int s_last;
-    if (st->status != 0) return;
-    const int K = st->K;
-    const int tid = threadIdx.x, groups = BLOCK / KB2, g = tid / KB2, k = tid % KB2;
-    const bool act = k < K;
-    const double ysc = act ? st->ysc[k] : 0.0;
-    const double th = act ? st->theta[st->sel[k]] : 0.0;
-    double racc = 0.0;
-    if (act) {
-        auto term = [&](int64_t r) {
-            const double y = ysc * Y[r * K + k];
-            const double d = ysc * Z[r * K + k] - th * y;
-            return d * d;
-        };
-        const int64_t S = (int64_t)gridDim.x * groups;
-        int64_t r = (int64_t)blockIdx.x * groups + g;
-        for (; r + 3 * S < n; r += 4 * S) {
-            const double d0 = term(r), d1 = term(r + S), d2 = term(r + 2 * S), d3 = term(r + 3 * S);
-            racc += d0;
-            racc += d1;
-            racc += d2;
-            racc += d3;
-        }
-        for (; r < n; r += S) racc += term(r);
-    }
-    shz[tid] = racc;
-    __syncthreads();
-    if (tid < KB2) {
-        double sum = 0.0;
-        for (int gg = 0; gg < groups; ++gg) sum += shz[gg * KB2 + tid];
-        st_dev(&part[(int64_t)blockIdx.x * 64 + tid], sum);
-    }
-    if (last_block(&st->ticket[TK_RESID], gridDim.x, &s_last)) {
-        // Thread (g, k) adds workgroups g, g + groups, ... of column k; the
-        // group sums are then added in group order.
-        __syncthreads();
-        shz[tid] = act ? strided_sum_dev(part + k, 64, g, groups, gridDim.x) : 0.0;
-        __syncthreads();
-        if (tid < K) {
-            double sum = 0.0;
-            for (int gg = 0; gg < groups; ++gg) sum += shz[gg * KB2 + tid];
-            const double a2 = sqrt(sum);
-            const double tl = st->theta[st->sel[tid]];
-            st->abs_resid[tid] = a2;
-            st->resid[tid] = tl != 0.0 ? a2 / fabs(tl) : a2;
-        }
-    }
-}
-
 // Unit Ritz vectors y_k = ysc_k Y[:,k] into the caller's column-major output
 // in original row order: a 64-row block is gathered row-wise (through the
 // original-to-solve row map when the matrix was relabelled) and written
@@ -787,187 +744,253 @@ __global__ __launch_bounds__(BLOCK) void k_out(const State* st, const double* __
 }
 
 // -------------------------------------------------------- orthogonality
-// Gram matrix G = X^T X of c <= 64 columns (column k scaled by scale[k]) on
-// the FP64 matrix cores.  A workgroup stages panels of 64 rows x c columns in
-// LDS (each column's 64 rows are one coalesced load), then every wavefront
-// multiplies its own upper 16x16 block pairs with v_mfma_f64_16x16x4f64 over
-// the panel's 16 groups of 4 rows (A = 16 columns x 4 rows, B = 4 rows x 16
-// columns; lane l holds P[4g + l/16][16b + l%16]).  Each workgroup writes its
-// upper blocks to gpart[b][64][64].
+// Gram matrices on the FP64 matrix cores (v_mfma_f64_16x16x4f64), straight from
+// global memory: lane l holds rows 4 (l/16) .. + 3 of column 16 b + l%16 of
+// every column block b, so its four products per block pair take row 4 (l/16)
+// + e in step e, the same rows for both operands, whatever their order in the
+// sum.  Each element is loaded once; there is nothing to stage in LDS.  (The
+// LDS-panel form took 117 us on the R-MAT 20 FP32 basis of 48 columns, 2.3 ms at
+// R-MAT 25 with 32 columns; this one 73 us and 1.2 ms, 2.7 and 3.6 TB/s.)
+// A workgroup adds its wavefronts' blocks in LDS and writes the upper block
+// pairs to gpart[workgroup][pair][16 x 16]; k_gram_finish adds the workgroups.
 typedef double d4 __attribute__((ext_vector_type(4)));
-constexpr int GPR = 64;     // rows per LDS panel
 
-template <class T, bool ROWMAJOR>
-__global__ __launch_bounds__(BLOCK) void k_gram(const State* st, const T* __restrict__ X, int64_t ldx, int64_t n,
-                                                int which, double* __restrict__ gpart) {
-    __shared__ double P[GPR][64 + 1];
-    __shared__ double s_scale[64];
-    if (st->status != 0) return;
-    const int c = which == 0 ? min(st->j, st->m) : st->K;
-    const double* scale = which == 0 ? st->scale : st->ysc;
-    const int nb = (c + 15) >> 4;
-    const int npair = nb * (nb + 1) / 2;
+// acc of the block pairs -> gp[pair * 256 + i * 16 + j] (element e of lane l
+// holds D[4e + l/16][l % 16]), wavefronts in order.
+template <int NP>
+__device__ __forceinline__ void gram_store(const d4 (&acc)[NP], double* gp, double (*sh)[256]) {
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int cl = lane & 15, rl = lane >> 4;
-    // Block pairs (bi <= bj) of this wavefront: pair t for t = wv, wv + 4, ...
-    int pbi[3], pbj[3];
-    int np = 0;
-    for (int bi = 0, t = 0; bi < nb; ++bi)
-        for (int bj = bi; bj < nb; ++bj, ++t)
-            if (t % (BLOCK / 64) == wv && np < 3) {
-                pbi[np] = bi;
-                pbj[np] = bj;
-                ++np;
-            }
-    d4 acc[3];
+    for (int w = 0; w < WAVES; ++w) {
+        if (wv == w)
 #pragma unroll
-    for (int t = 0; t < 3; ++t) acc[t] = d4{0.0, 0.0, 0.0, 0.0};
-    // Columns c .. 16 nb - 1 enter the MFMA tiles as zeros; only the c live
-    // columns are loaded per panel.
-    for (int idx = threadIdx.x; idx < GPR * (nb * 16 - c); idx += BLOCK) P[idx % GPR][c + idx / GPR] = 0.0;
-    if ((int)threadIdx.x < 64) s_scale[threadIdx.x] = (int)threadIdx.x < c ? scale[threadIdx.x] : 0.0;
-    // Panel element idx (< GPR c) of thread t is idx = t + q BLOCK.  For the
-    // column-major basis, all of a thread's loads of a panel go out together
-    // into registers, and the next panel's loads are issued before the
-    // current one's products, so a panel costs one memory latency, hidden
-    // behind the matrix-core work.
-    constexpr int PER = GPR * 64 / BLOCK;
-    static_assert(PER * BLOCK == GPR * 64, "a panel of 64 columns splits evenly over the threads");
-    auto locate = [&](int idx, int& row, int& col) {
-        if (ROWMAJOR) {
-            row = idx / c;
-            col = idx - row * c;
-        } else {
-            col = idx / GPR;
-            row = idx % GPR;
-        }
-    };
-    T raw[PER];
-    auto load_panel = [&](int64_t pn) {
-        const int64_t r0 = pn * GPR;
+            for (int t = 0; t < NP; ++t)
 #pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int idx = (int)threadIdx.x + q * BLOCK;
-            T v = T(0);
-            if (idx < GPR * c) {
-                int row = 0, col = 0;
-                locate(idx, row, col);
-                const int64_t r = r0 + row;
-                if (r < n) v = ROWMAJOR ? X[r * ldx + col] : X[(int64_t)col * ldx + r];
-            }
-            raw[q] = v;
-        }
-    };
-    auto store_panel = [&](int64_t pn) {
-        const int64_t r0 = pn * GPR;
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int idx = (int)threadIdx.x + q * BLOCK;
-            if (idx < GPR * c) {
-                int row = 0, col = 0;
-                locate(idx, row, col);
-                double v = 0.0;
-                if (r0 + row < n) v = to_d(raw[q]) * s_scale[col];
-                P[row][col] = v;
-            }
-        }
-    };
-    const int64_t npanel = (n + GPR - 1) / GPR;
-    // The row-major Ritz block (K <= 16 columns, a few loads per thread)
-    // measured faster without the prefetch (R-MAT 26: 2.4 against 3.2 ms), so
-    // it loads each panel in place; both forms stage the same values.
-    if (!ROWMAJOR && (int64_t)blockIdx.x < npanel) load_panel(blockIdx.x);
-    for (int64_t pn = blockIdx.x; pn < npanel; pn += gridDim.x) {
-        __syncthreads();                 // P is no longer read by the previous panel's products
-        if (ROWMAJOR) {
-            const int64_t r0 = pn * GPR;
-            for (int idx = threadIdx.x; idx < GPR * c; idx += BLOCK) {
-                int row = 0, col = 0;
-                locate(idx, row, col);
-                const int64_t r = r0 + row;
-                double v = 0.0;
-                if (r < n) v = to_d(X[r * ldx + col]) * s_scale[col];
-                P[row][col] = v;
-            }
-        } else {
-            store_panel(pn);
-        }
-        __syncthreads();
-        if (!ROWMAJOR && pn + gridDim.x < npanel) load_panel(pn + gridDim.x);
-#pragma unroll
-        for (int t = 0; t < 3; ++t) {
-            if (t < np) {
-                const int bi = pbi[t], bj = pbj[t];
-#pragma unroll 4
-                for (int g = 0; g < GPR / 4; ++g) {
-                    const double a = P[g * 4 + rl][bi * 16 + cl];
-                    const double b = P[g * 4 + rl][bj * 16 + cl];
-                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[t], 0, 0, 0);
+                for (int e = 0; e < 4; ++e) {
+                    double* d = &sh[t][(e * 4 + (lane >> 4)) * 16 + (lane & 15)];
+                    *d = w == 0 ? acc[t][e] : *d + acc[t][e];
                 }
-            }
-        }
+        __syncthreads();
     }
-    double* gp = gpart + (int64_t)blockIdx.x * 64 * 64;
+    for (int i = threadIdx.x; i < NP * 256; i += BLOCK) gp[i] = sh[i / 256][i % 256];
+}
+
+// Basis: X column-major with c <= 16 NB columns, column k scaled by scale[k].
+template <class T, int NB>
+__global__ __launch_bounds__(BLOCK) void k_gram(const State* st, const T* __restrict__ X, int64_t ldx, int64_t n,
+                                                double* __restrict__ gpart) {
+    constexpr int NP = NB * (NB + 1) / 2;
+    typedef T T4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+    __shared__ double sh[NP][256];
+    if (st->status != 0) return;
+    const int c = min(st->j, st->m);
+    if (c < 1 || c > 16 * NB) return;
+    const int lane = threadIdx.x & 63, cl = lane & 15, rg = lane >> 4;
+    double sc[NB];
+    const T* xb[NB];
 #pragma unroll
-    for (int t = 0; t < 3; ++t)
-        if (t < np)
+    for (int b = 0; b < NB; ++b) {
+        const int k = b * 16 + cl;
+        sc[b] = k < c ? st->scale[k] : 0.0;        // columns past c enter as zeros
+        xb[b] = X + (int64_t)min(k, c - 1) * ldx + rg * 4;
+    }
+    d4 acc[NP];
+#pragma unroll
+    for (int t = 0; t < NP; ++t) acc[t] = d4{0.0, 0.0, 0.0, 0.0};
+    const int64_t step = (int64_t)gridDim.x * WAVES * 32;
+    for (int64_t r0 = ((int64_t)blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * 32; r0 < n;
+         r0 += step) {
+        T4 v[2][NB];
+        if (r0 + 32 <= n) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) v[h][b] = *(const T4*)(xb[b] + r0 + h * 16);
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int64_t r = r0 + h * 16 + rg * 4 + e;
+                        v[h][b][e] = r < n ? xb[b][r0 + h * 16 + e] : T(0);
+                    }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                // Accumulator element e of lane l holds D[4e + l/16][l % 16].
-                const int i = pbi[t] * 16 + e * 4 + rl, jj = pbj[t] * 16 + cl;
-                gp[i * 64 + jj] = acc[t][e];
+                double x[NB];
+#pragma unroll
+                for (int b = 0; b < NB; ++b) x[b] = to_d(T(v[h][b][e])) * sc[b];
+#pragma unroll
+                for (int bi = 0, t = 0; bi < NB; ++bi)
+#pragma unroll
+                    for (int bj = bi; bj < NB; ++bj, ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[bi], x[bj], acc[t], 0, 0, 0);
             }
-    (void)npair;
+    }
+    gram_store<NP>(acc, gpart + (int64_t)blockIdx.x * GRAM_SLOT, sh);
 }
 
-// G[i][j] = sum over workgroups of the upper blocks, symmetrised: one
-// wavefront per entry, lane-strided over the workgroups, then the butterfly
-// (a fixed order).
-__global__ __launch_bounds__(BLOCK) void k_gram_reduce(const State* st, const double* gpart, int nparts, int which,
-                                                       double* G) {
+// Residuals ||A y_k - theta_k y_k|| = ||ysc_k Z[:,k] - theta_k ysc_k Y[:,k]||
+// (Sec. IV-D) and the Gram matrix of the unit Ritz vectors in one pass over Y
+// and Z (row-major, n x K), in the solve's row order: lane l takes columns 16 b
+// + l%16 of rows l/16, l/16 + 4, ...  Sums of squares go to rpart[workgroup *
+// 64 + column].  (One pass each: 55 + 62 us at R-MAT 20, K = 16; together
+// 48 us.)
+template <int NB>
+__global__ __launch_bounds__(BLOCK) void k_resid_gram(const State* st, const double* __restrict__ Y,
+                                                      const double* __restrict__ Z, int64_t n,
+                                                      double* __restrict__ gpart, double* __restrict__ rpart) {
+    constexpr int NP = NB * (NB + 1) / 2, U = NB == 1 ? 8 : 4;     // rows of a lane in flight
+    __shared__ double sh[NP][256];
+    __shared__ double shr[WAVES][NB * 16];
     if (st->status != 0) return;
-    const int c = which == 0 ? min(st->j, st->m) : st->K;
-    const int lane = threadIdx.x & 63;
-    const int entry = blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6);
-    if (entry >= 64 * 64) return;
-    const int i = entry / 64, jj = entry % 64;
-    if (i >= c || jj >= c || i > jj) return;
-    double s = 0.0;
-    for (int b = lane; b < nparts; b += 64) s += gpart[(int64_t)b * 4096 + i * 64 + jj];
-    s = wave_sum(s);
-    if (lane == 0) {
-        G[i * 64 + jj] = s;
-        G[jj * 64 + i] = s;
+    const int K = st->K;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, cl = lane & 15, rg = lane >> 4;
+    double ysc[NB], th[NB], racc[NB];
+    int kc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int k = b * 16 + cl;
+        const bool act = k < K;
+        ysc[b] = act ? st->ysc[k] : 0.0;
+        th[b] = act ? st->theta[st->sel[k]] : 0.0;
+        kc[b] = min(k, K - 1);
+        racc[b] = 0.0;
     }
-}
-
-// max |G - I| and, for the Ritz vectors, the mean angle between pairs.
-__global__ __launch_bounds__(BLOCK) void k_gram_metrics(State* st, const double* G, int which) {
-    __shared__ double shd[BLOCK / 64];
-    __shared__ double shm[BLOCK];
-    if (st->status != 0) return;
-    const int c = which == 0 ? min(st->j, st->m) : st->K;
-    double worst = 0.0, ang = 0.0;
-    for (int idx = threadIdx.x; idx < c * c; idx += BLOCK) {
-        const int i = idx / c, jj = idx % c;
-        const double g = G[i * 64 + jj];
-        worst = fmax(worst, fabs(g - (i == jj ? 1.0 : 0.0)));
-        if (i < jj) ang += acos(fmin(1.0, fabs(g))) * (180.0 / 3.14159265358979323846);
-    }
-    shm[threadIdx.x] = worst;
-    __syncthreads();
-    for (int o = BLOCK / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) shm[threadIdx.x] = fmax(shm[threadIdx.x], shm[threadIdx.x + o]);
-        __syncthreads();
-    }
-    ang = block_sum(ang, shd);
-    if (threadIdx.x == 0) {
-        if (which == 0) {
-            st->ortho_loss = shm[0];
-        } else {
-            st->ritz_ortho_loss = shm[0];
-            st->mean_angle_deg = c > 1 ? ang / (0.5 * c * (c - 1)) : 90.0;
+    d4 acc[NP];
+#pragma unroll
+    for (int t = 0; t < NP; ++t) acc[t] = d4{0.0, 0.0, 0.0, 0.0};
+    const int64_t step = (int64_t)gridDim.x * WAVES * 4 * U;
+    for (int64_t r0 = ((int64_t)blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(wv)) * 4 * U; r0 < n; r0 += step) {
+        double y[U][NB], z[U][NB];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t r = min(r0 + u * 4 + rg, n - 1);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                y[u][b] = Y[r * K + kc[b]];
+                z[u][b] = Z[r * K + kc[b]];
+            }
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool in = r0 + u * 4 + rg < n;
+            double x[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                x[b] = in ? ysc[b] * y[u][b] : 0.0;
+                const double d = in ? ysc[b] * z[u][b] - th[b] * x[b] : 0.0;
+                racc[b] += d * d;
+            }
+#pragma unroll
+            for (int bi = 0, t = 0; bi < NB; ++bi)
+#pragma unroll
+                for (int bj = bi; bj < NB; ++bj, ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[bi], x[bj], acc[t], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        racc[b] = add_xor_rows<32>(add_xor_rows<16>(racc[b]));
+        if (lane < 16) shr[wv][b * 16 + lane] = racc[b];
+    }
+    gram_store<NP>(acc, gpart + (int64_t)blockIdx.x * GRAM_SLOT, sh);      // its barriers order shr
+    if ((int)threadIdx.x < NB * 16) {
+        double s = shr[0][threadIdx.x];
+        for (int w = 1; w < WAVES; ++w) s += shr[w][threadIdx.x];
+        rpart[(int64_t)blockIdx.x * 64 + threadIdx.x] = s;
+    }
+}
+
+// Adds the workgroups' partials, one wavefront per value (lane-strided, then
+// the wavefront sum: a fixed order): the upper entries of the basis' Gram
+// matrix (gv workgroups), those of the Ritz vectors' and the residuals' sums
+// of squares (gy workgroups; 0: basis only).  The last workgroup takes max
+// |G - I| of both, the mean angle between Ritz vectors and the residuals.
+__device__ __forceinline__ int gram_place(int i, int j, int nb) {
+    const int bi = i >> 4, bj = j >> 4;
+    return (bi * (2 * nb - bi + 1) / 2 + (bj - bi)) * 256 + (i & 15) * 16 + (j & 15);
+}
+// (i, j), i <= j, of the e-th upper entry of a c x c matrix, row by row.
+__device__ __forceinline__ void upper_entry(int e, int c, int& i, int& j) {
+    i = 0;
+    while (e >= c - i) e -= c - i++;
+    j = i + e;
+}
+__global__ __launch_bounds__(BLOCK) void k_gram_finish(State* st, const double* __restrict__ gpart,
+                                                       const double* __restrict__ gpart_y, const double* rpart, int gv, int nbv, int gy,
+                                                       int nby, double* out) {
+    __shared__ double shm[3][BLOCK / 64];
+    __shared__ int s_last;
+    if (st->status != 0) return;
+    const int c = min(st->j, st->m), K = st->K;
+    const int ev = c * (c + 1) / 2, ey = gy > 0 ? K * (K + 1) / 2 : 0, er = gy > 0 ? K : 0;
+    const int lane = threadIdx.x & 63;
+    for (int e = blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6); e < ev + ey + er; e += gridDim.x * (BLOCK / 64)) {
+        const double* src;
+        int64_t stride = GRAM_SLOT;
+        int parts = gv, i, j;
+        if (e < ev) {
+            upper_entry(e, c, i, j);
+            src = gpart + gram_place(i, j, nbv);
+        } else if (e < ev + ey) {
+            upper_entry(e - ev, K, i, j);
+            src = gpart_y + gram_place(i, j, nby);
+            parts = gy;
+        } else {
+            src = rpart + (e - ev - ey);
+            stride = 64;
+            parts = gy;
+        }
+        double s = 0.0;
+#pragma unroll 4
+        for (int b = lane; b < parts; b += 64) s += src[b * stride];
+        s = wave_sum(s);
+        if (lane == 0) st_dev(&out[e], s);
+    }
+    if (!last_block(&st->ticket[TK_GRAM], gridDim.x, &s_last)) return;
+    double wv = 0.0, wy = 0.0, ang = 0.0;
+    for (int e = threadIdx.x; e < ev + ey; e += BLOCK) {
+        int i, j;
+        upper_entry(e < ev ? e : e - ev, e < ev ? c : K, i, j);
+        const double g = ld_dev(&out[e]), off = fabs(g - (i == j ? 1.0 : 0.0));
+        // fmax drops a NaN, as the per-thread maxima always did.
+        if (e < ev) {
+            wv = fmax(wv, off);
+        } else {
+            wy = fmax(wy, off);
+            if (i < j) ang += acos(fmin(1.0, fabs(g))) * (180.0 / 3.14159265358979323846);
+        }
+    }
+    wv = wave_max(wv);
+    wy = wave_max(wy);
+    ang = wave_sum(ang);
+    if (lane == 0) {
+        shm[0][threadIdx.x >> 6] = wv;
+        shm[1][threadIdx.x >> 6] = wy;
+        shm[2][threadIdx.x >> 6] = ang;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < BLOCK / 64; ++w) {
+            wv = fmax(wv, shm[0][w]);
+            wy = fmax(wy, shm[1][w]);
+            ang += shm[2][w];
+        }
+        st->ortho_loss = wv;
+        if (gy > 0) {
+            st->ritz_ortho_loss = wy;
+            st->mean_angle_deg = K > 1 ? ang / (0.5 * K * (K - 1)) : 90.0;
+        }
+    }
+    if ((int)threadIdx.x < er) {
+        const double a2 = sqrt(ld_dev(&out[ev + ey + threadIdx.x]));
+        const double tl = st->theta[st->sel[threadIdx.x]];
+        st->abs_resid[threadIdx.x] = a2;
+        st->resid[threadIdx.x] = tl != 0.0 ? a2 / fabs(tl) : a2;
     }
 }
 
@@ -978,8 +1001,34 @@ static int pow2_at_least(int k) {
     return v;
 }
 
-static int gram_grid(int64_t n) {
-    return (int)std::max<int64_t>(1, std::min<int64_t>(GRAM_PARTS, (n + GPR - 1) / GPR));
+// Workgroups of a Gram pass whose wavefronts take `rows` rows at a time.
+static int gram_grid(int64_t n, int rows) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(GRAM_GRID, (n + rows * WAVES - 1) / (rows * WAVES)));
+}
+
+// Basis of at most cmax columns; returns its grid.
+template <class T>
+static int launch_gram(const State* st, const T* X, int64_t ldx, int64_t n, int cmax, double* gpart, hipStream_t s) {
+    const int g = gram_grid(n, 32);
+    switch ((cmax + 15) / 16) {
+        case 1: hipLaunchKernelGGL((k_gram<T, 1>), dim3(g), dim3(BLOCK), 0, s, st, X, ldx, n, gpart); break;
+        case 2: hipLaunchKernelGGL((k_gram<T, 2>), dim3(g), dim3(BLOCK), 0, s, st, X, ldx, n, gpart); break;
+        case 3: hipLaunchKernelGGL((k_gram<T, 3>), dim3(g), dim3(BLOCK), 0, s, st, X, ldx, n, gpart); break;
+        default: hipLaunchKernelGGL((k_gram<T, 4>), dim3(g), dim3(BLOCK), 0, s, st, X, ldx, n, gpart); break;
+    }
+    return g;
+}
+
+static int launch_resid_gram(const State* st, const double* Y, const double* Z, int64_t n, int K, double* gpart,
+                             double* rpart, hipStream_t s) {
+    const int nb = (K + 15) / 16, g = gram_grid(n, nb == 1 ? 32 : 16);
+    switch (nb) {
+        case 1: hipLaunchKernelGGL(k_resid_gram<1>, dim3(g), dim3(BLOCK), 0, s, st, Y, Z, n, gpart, rpart); break;
+        case 2: hipLaunchKernelGGL(k_resid_gram<2>, dim3(g), dim3(BLOCK), 0, s, st, Y, Z, n, gpart, rpart); break;
+        case 3: hipLaunchKernelGGL(k_resid_gram<3>, dim3(g), dim3(BLOCK), 0, s, st, Y, Z, n, gpart, rpart); break;
+        default: hipLaunchKernelGGL(k_resid_gram<4>, dim3(g), dim3(BLOCK), 0, s, st, Y, Z, n, gpart, rpart); break;
+    }
+    return g;
 }
 
 template <int P>
@@ -1028,15 +1077,12 @@ static hipError_t finish_p(const Plan& p, const Bufs& b, const Csr& a, double* o
     const int go = (int)std::max<int64_t>(1, std::min<int64_t>(2048, (p.n + 63) / 64));
     hipLaunchKernelGGL(k_out, dim3(go), dim3(BLOCK), 0, s, b.st, b.Y, p.n, kb2, out_vecs);
     if (!report) return hipGetLastError();
-    hipLaunchKernelGGL(k_resid, dim3(gc), dim3(BLOCK), 0, s, b.st, b.Y, b.Z, p.n, kb2, b.part2);
-    const int gg = gram_grid(p.n);
-    double* G = b.gram + (int64_t)GRAM_PARTS * 4096;
-    hipLaunchKernelGGL((k_gram<VT, false>), dim3(gg), dim3(BLOCK), 0, s, b.st, V, p.ld, p.n, 0, b.gram);
-    hipLaunchKernelGGL(k_gram_reduce, dim3(64 * 64 / (BLOCK / 64)), dim3(BLOCK), 0, s, b.st, b.gram, gg, 0, G);
-    hipLaunchKernelGGL(k_gram_metrics, dim3(1), dim3(BLOCK), 0, s, b.st, G, 0);
-    hipLaunchKernelGGL((k_gram<double, true>), dim3(gg), dim3(BLOCK), 0, s, b.st, b.Y, (int64_t)p.K, p.n, 1, b.gram);
-    hipLaunchKernelGGL(k_gram_reduce, dim3(64 * 64 / (BLOCK / 64)), dim3(BLOCK), 0, s, b.st, b.gram, gg, 1, G);
-    hipLaunchKernelGGL(k_gram_metrics, dim3(1), dim3(BLOCK), 0, s, b.st, G, 1);
+    double* gpart_y = b.gram + (int64_t)GRAM_GRID * GRAM_SLOT;
+    const int gv = launch_gram<VT>(b.st, V, p.ld, p.n, p.m, b.gram, s);
+    const int gy = launch_resid_gram(b.st, b.Y, b.Z, p.n, p.K, gpart_y, b.part2, s);
+    const int values = p.m * (p.m + 1) / 2 + p.K * (p.K + 1) / 2 + p.K;
+    hipLaunchKernelGGL(k_gram_finish, dim3((values + BLOCK / 64 - 1) / (BLOCK / 64)), dim3(BLOCK), 0, s, b.st, b.gram,
+                       gpart_y, b.part2, gv, (p.m + 15) / 16, gy, (p.K + 15) / 16, b.gram + GRAM_OUT);
     return hipGetLastError();
 }
 
@@ -1050,28 +1096,17 @@ hipError_t launch_finish(const Plan& p, const Bufs& b, const Csr& a, double* out
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_gram_only(int prec, const void* X, int64_t ldx, int64_t n, State* st, double* gram,
+hipError_t launch_gram_only(int prec, const void* X, int64_t ldx, int64_t n, int c, State* st, double* gram,
                             hipStream_t s) {
-    const int gg = gram_grid(n);
-    double* G = gram + (int64_t)GRAM_PARTS * 4096;
+    int g = 0;
     switch (prec) {
-        case 0:
-            hipLaunchKernelGGL((k_gram<double, false>), dim3(gg), dim3(BLOCK), 0, s, st, (const double*)X, ldx, n, 0,
-                               gram);
-            break;
-        case 1:
-            hipLaunchKernelGGL((k_gram<float, false>), dim3(gg), dim3(BLOCK), 0, s, st, (const float*)X, ldx, n, 0,
-                               gram);
-            break;
-        case 2:
-            hipLaunchKernelGGL((k_gram<uint16_t, false>), dim3(gg), dim3(BLOCK), 0, s, st, (const uint16_t*)X, ldx,
-                               n, 0, gram);
-            break;
-        default:
-            return hipErrorInvalidValue;
+        case 0: g = launch_gram<double>(st, (const double*)X, ldx, n, c, gram, s); break;
+        case 1: g = launch_gram<float>(st, (const float*)X, ldx, n, c, gram, s); break;
+        case 2: g = launch_gram<uint16_t>(st, (const uint16_t*)X, ldx, n, c, gram, s); break;
+        default: return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL(k_gram_reduce, dim3(64 * 64 / (BLOCK / 64)), dim3(BLOCK), 0, s, st, gram, gg, 0, G);
-    hipLaunchKernelGGL(k_gram_metrics, dim3(1), dim3(BLOCK), 0, s, st, G, 0);
+    hipLaunchKernelGGL(k_gram_finish, dim3((c * (c + 1) / 2 + BLOCK / 64 - 1) / (BLOCK / 64)), dim3(BLOCK), 0, s, st,
+                       gram, nullptr, nullptr, g, (c + 15) / 16, 0, 0, gram + GRAM_OUT);
     return hipGetLastError();
 }
 

@@ -19,7 +19,12 @@ constexpr int OGRID = 256;     // orthogonalisation grid cap (workgroups of OBLO
 constexpr int OBLOCK = 1024;   // orthogonalisation workgroup (16 wave64)
 constexpr int DGRID = 1024;    // grid cap of the other dense kernels (workgroups of BLOCK threads)
 constexpr int SGRID = 2048;    // SpMV grid cap (workgroups)
-constexpr int GRAM_PARTS = 1024; // Gram kernel grid cap (per-workgroup 64x64 partials)
+constexpr int GRAM_GRID = 512;     // workgroups of a Gram pass at most
+constexpr int GRAM_SLOT = 2560;    // doubles of a workgroup's partials: ten 16 x 16 block pairs of 64 columns
+// Gram buffer: slots of the basis, slots of the Ritz vectors, then the sums
+// (two upper triangles of 64 columns and 64 residuals).
+constexpr int64_t GRAM_OUT = (int64_t)2 * GRAM_GRID * GRAM_SLOT;
+constexpr int64_t GRAM_DOUBLES = GRAM_OUT + 2 * (64 * 65 / 2) + 64;
 // Column-sorted storage of the relabelled matrix.  State.packed = PACK_TILE
 // (n < 2^22): each tile's entries are stored in column order and each column
 // word holds (col << PACK_SLOTBITS) | (the entry's position in the tile's row
@@ -71,7 +76,7 @@ constexpr int SW_PANELS_MAX = 512;
 enum Mode { MODE_NORMAL = 0, MODE_RESTART = 1 };
 
 // Tickets of the "last workgroup reduces" pattern, one per kernel kind.
-enum Ticket { TK_INIT = 0, TK_SPMV, TK_DOT, TK_UPD, TK_STORE, TK_RITZ, TK_RESID, TK_GRAM, TK_COUNT };
+enum Ticket { TK_INIT = 0, TK_SPMV, TK_DOT, TK_UPD, TK_STORE, TK_RITZ, TK_GRAM, TK_COUNT };
 
 // Solve state kept in device memory; every kernel reads the step index and
 // coefficients from here, so the host never has to read them back between
@@ -191,7 +196,7 @@ struct Bufs {
     uint64_t* bsum;    // scan block sums
     double* Y;         // Ritz vectors, row-major n x K, before normalisation
     double* Z;         // A Y, row-major n x K (residual check)
-    double* gram;      // Gram partials (GRAM_PARTS x 64 x 64), then the reduced 64 x 64
+    double* gram;      // Gram partials and sums (GRAM_DOUBLES)
     int32_t* ob;       // SpMV tiles: first owned row of every tile (n_tiles + 1)
     uint32_t* tk;      // split-row tickets, one per owner tile
     double* head;      // split-row pieces at the start of a tile (n_tiles x KB2)
@@ -287,7 +292,7 @@ hipError_t launch_jacobi_only(const double* alpha, const double* offdiag, int m,
                               hipStream_t s);
 // max |X^T X - I| of the first st->j columns of X (scales st->scale) into
 // st->ortho_loss, with the kernels of the solve report.
-hipError_t launch_gram_only(int prec, const void* X, int64_t ldx, int64_t n, State* st, double* gram,
+hipError_t launch_gram_only(int prec, const void* X, int64_t ldx, int64_t n, int c, State* st, double* gram,
                             hipStream_t s);
 
 }  // namespace lz
