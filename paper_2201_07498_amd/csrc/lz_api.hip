@@ -46,7 +46,6 @@ Plan make_plan(int64_t n, int64_t nnz, int32_t K, int32_t m, int32_t prec, bool 
     // channel (a power-of-two column stride sends them all to one).
     p.ld = ceil_div(n, LDPAD) * LDPAD;
     if ((p.ld / LDPAD) % 2 == 0) p.ld += LDPAD;
-    p.KB = (int32_t)std::max<int64_t>(8, ceil_div(K, 8) * 8);
     p.g_orth = (int32_t)std::min<int64_t>(OGRID, p.ld / OBLOCK);
     p.g_dense = (int32_t)std::min<int64_t>(DGRID, p.ld / BLOCK);
     p.n_tiles = ceil_div(nnz + n, TILE);

@@ -375,43 +375,9 @@ __global__ __launch_bounds__(JBLOCK) void k_jacobi_only(const double* alpha, con
 }
 
 // ------------------------------------------------------------ Ritz vectors
-// Y[r][k] = sum_i scale_i V[r,i] S[i, sel_k]  (eigenvectors of the matrix are
-// the Lanczos basis times those of T).  Y is row-major n x K (a K-wide row
-// per matrix row, the layout the residual SpMM gathers), not normalised.
-template <int P, int KB>
-__global__ __launch_bounds__(BLOCK) void k_ritz(const State* st, const typename Tr<P>::V* __restrict__ Vb, int64_t n,
-                                                int64_t ld, double* __restrict__ Y) {
-    __shared__ double Ss[MMAX][KB];
-    if (st->status != 0) return;
-    const int m = min(st->j, st->m), K = st->K;
-    for (int idx = threadIdx.x; idx < MMAX * KB; idx += BLOCK) {
-        const int i = idx / KB, k = idx % KB;
-        Ss[i][k] = (i < m && k < K) ? st->S[i * MMAX + st->sel[k]] * st->scale[i] : 0.0;
-    }
-    __syncthreads();
-    for (int64_t r = (int64_t)blockIdx.x * BLOCK + threadIdx.x; r < n; r += (int64_t)gridDim.x * BLOCK) {
-        double acc[KB];
-#pragma unroll
-        for (int k = 0; k < KB; ++k) acc[k] = 0.0;
-        for (int i = 0; i < m; ++i) {
-            const double v = to_d(Vb[(int64_t)i * ld + r]);
-#pragma unroll
-            for (int k = 0; k < KB; ++k) acc[k] += v * Ss[i][k];
-        }
-#pragma unroll
-        for (int k = 0; k < KB; ++k)
-            if (k < K) Y[r * K + k] = acc[k];
-    }
-}
-
-// Per Ritz column k: norm and the entry of largest modulus (lowest original
-// row on ties) -> ysc[k] = sign(that entry) / norm.  Lane k of each group of
-// KB2 lanes owns column k.  NOROW marks "no row yet" (exact as a double and
-// as an int64).  The original row is looked up only where moduli tie and for
-// the winners; values are joined across the lanes of a wavefront, the
-// wavefronts and the workgroups in a fixed order.  Measured, R-MAT 20 K = 16:
-// 77 -> 49 us (a row lookup per entry, 64 serial joins through LDS),
-// n = 3000 K = 4: 19 -> 6 us.
+// Joins (norm, entry of largest modulus) over rows; the lowest original row
+// wins among equal moduli.  NOROW marks "no row yet" (exact as a double and
+// as an int64).
 constexpr int64_t NOROW = int64_t(1) << 62;
 struct ColStat {
     double nrm, mod, val;     // sum of squares; largest modulus and its value
@@ -425,84 +391,144 @@ __device__ __forceinline__ void join(ColStat& a, double nrm, double mod, double 
         a.row = row;
     }
 }
-__device__ __forceinline__ void join_lanes(ColStat& a, int KB2) {
-    for (int o = KB2; o < 64; o <<= 1) {
+// Over the lanes with the same lane % kb (a power of two), pairwise.
+__device__ __forceinline__ void join_lanes(ColStat& a, int kb) {
+    for (int o = kb; o < 64; o <<= 1) {
         const double nrm = __shfl_xor(a.nrm, o, 64), mod = __shfl_xor(a.mod, o, 64), val = __shfl_xor(a.val, o, 64);
         const int64_t row = __shfl_xor((long long)a.row, o, 64);
         join(a, nrm, mod, val, row);
     }
 }
-__global__ __launch_bounds__(BLOCK) void k_colstats(State* st, const double* __restrict__ Y, int64_t n, int KB2,
-                                                    double* part) {
+
+// Y[r][k] = sum_i scale_i V[r,i] S[i, sel_k]  (eigenvectors of the matrix are
+// the Lanczos basis times those of T).  Y is row-major n x K (a K-wide row
+// per matrix row, the layout the residual SpMM gathers), not normalised.
+// And per Ritz column: norm and the entry of largest modulus (lowest original
+// row on ties) -> ysc[k] = sign(that entry) / norm.
+// A wavefront takes 64 rows on the FP64 matrix cores: lane l loads rows 4 (l %
+// 16) .. + 3 of basis column 4 q + l/16 as one vector, product e of step q
+// takes the e-th of them, and the result's 16 columns leave as one contiguous
+// piece per row.  Bound by the basis' bytes and Y's.  The original row is
+// looked up only where moduli tie and for the winners.  (One thread per row
+// with K serial stores took 125 us at R-MAT 20, m = 48, K = 16, and a pass
+// over Y for the column values 49 us; together 84 us.  R-MAT 25: 1.87 +
+// 0.37 -> 1.45 ms.)
+template <int P, int NB>
+__global__ __launch_bounds__(BLOCK) void k_ritz(State* st, const typename Tr<P>::V* __restrict__ Vb, int64_t n,
+                                                int64_t ld, double* __restrict__ Y, double* part) {
+    using VT = typename Tr<P>::V;
+    typedef VT V4 __attribute__((ext_vector_type(4)));
+    typedef double d4 __attribute__((ext_vector_type(4)));
+    constexpr int KC = NB * 16, KP = NB == 1 ? 16 : NB == 2 ? 32 : 64, U = P == 0 ? 4 : 6;
+    __shared__ double Ss[MMAX][KC];
     __shared__ ColStat sw[WAVES][64];
     __shared__ int s_last;
     if (st->status != 0) return;
-    const int K = st->K, G = gridDim.x;
-    const int groups = BLOCK / KB2, g = threadIdx.x / KB2, k = threadIdx.x % KB2;
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int m = min(st->j, st->m), K = st->K, G = gridDim.x;
+    for (int idx = threadIdx.x; idx < MMAX * KC; idx += BLOCK) {
+        const int i = idx / KC, k = idx % KC;
+        Ss[i][k] = (i < m && k < K) ? st->S[i * MMAX + st->sel[k]] * st->scale[i] : 0.0;
+    }
+    __syncthreads();
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, cl = lane & 15, rg = lane >> 4;
     const int32_t* perm = st->perm;
     auto original = [&](int64_t r) { return perm ? (int64_t)perm[r] : r; };
-    ColStat a{0.0, -1.0, 0.0, NOROW};
-    if (k < K) {
-        int64_t best = -1;                         // row of the largest modulus so far, in the solve's order
-        auto visit = [&](int64_t r, double v) {
-            a.nrm += v * v;
-            const double m = fabs(v);
-            if (m > a.mod || (m == a.mod && original(r) < original(best))) {
-                a.mod = m;
-                a.val = v;
-                best = r;
-            }
-        };
-        const int64_t S = (int64_t)G * groups;
-        int64_t r = (int64_t)blockIdx.x * groups + g;
-        for (; r + 7 * S < n; r += 8 * S) {       // eight rows in flight
-            double v[8];
+    ColStat a[NB];
+    int64_t best[NB];                              // row of the largest modulus so far, in the solve's order
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = Y[(r + i * S) * K + k];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) visit(r + i * S, v[i]);
-        }
-        for (; r < n; r += S) visit(r, Y[r * K + k]);
-        if (best >= 0) a.row = original(best);
+    for (int b = 0; b < NB; ++b) {
+        a[b] = ColStat{0.0, -1.0, 0.0, NOROW};
+        best[b] = -1;
     }
-    // Within a workgroup; lanes 0 .. KB2 - 1 of the first wavefront end with
-    // the workgroup's values.
-    auto join_block = [&]() {
-        join_lanes(a, KB2);
-        __syncthreads();
-        if (lane < KB2) sw[wv][lane] = a;
-        __syncthreads();
-        if (wv == 0 && lane < KB2)
-            for (int w = 1; w < WAVES; ++w) join(a, sw[w][lane].nrm, sw[w][lane].mod, sw[w][lane].val, sw[w][lane].row);
-    };
-    join_block();
-    if ((int)threadIdx.x < K) {
-        double* pb = part + ((int64_t)blockIdx.x * 64 + threadIdx.x) * 4;
-        st_dev(pb + 0, a.nrm);
-        st_dev(pb + 1, a.mod);
-        st_dev(pb + 2, a.val);
-        st_dev(pb + 3, (double)a.row);
-    }
-    if (last_block(&st->ticket[TK_RITZ], (uint32_t)G, &s_last)) {
-        // Thread (g, k) joins workgroups g, g + groups, ... of column k, four
-        // loads in flight (past the end: the last one's, not joined).
-        a = ColStat{0.0, -1.0, 0.0, NOROW};
-        if (k < K)
-            for (int b = g; b < G; b += 4 * groups) {
-                double v[4][4];
+    // ld is a multiple of 64 past n, so whole vectors can be loaded.
+    for (int64_t r0 = ((int64_t)blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(wv)) * 64; r0 < n;
+         r0 += (int64_t)G * WAVES * 64) {
+        d4 acc[4][NB];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const double* pb = part + ((int64_t)min(b + i * groups, G - 1) * 64 + k) * 4;
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) v[i][q] = ld_dev(pb + q);
+            for (int b = 0; b < NB; ++b) acc[e][b] = d4{0.0, 0.0, 0.0, 0.0};
+        const VT* x = Vb + r0 + cl * 4;
+        for (int i0 = 0; i0 < m; i0 += 4 * U) {
+            V4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = *(const V4*)(x + (int64_t)min(i0 + u * 4 + rg, m - 1) * ld);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (i0 + u * 4 >= m) break;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const double s = Ss[i0 + u * 4 + rg][b * 16 + cl];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        acc[e][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(to_d(VT(v[u][e])), s, acc[e][b], 0, 0, 0);
                 }
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (b + i * groups < G) join(a, v[i][0], v[i][1], v[i][2], (int64_t)v[i][3]);
             }
-        join_block();
-        if ((int)threadIdx.x < K) st->ysc[threadIdx.x] = (a.val < 0.0 ? -1.0 : 1.0) / sqrt(a.nrm);
+        }
+        // Element t of lane l in acc[e]: row r0 + 4 (4 t + l/16) + e, column 16 b + l%16.
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t r = r0 + (t * 4 + rg) * 4 + e;
+                if (r < n)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        const int k = b * 16 + cl;
+                        if (k < K) {
+                            const double y = acc[e][b][t], mod = fabs(y);
+                            Y[r * K + k] = y;
+                            a[b].nrm += y * y;
+                            if (mod > a[b].mod || (mod == a[b].mod && original(r) < original(best[b]))) {
+                                a[b].mod = mod;
+                                a[b].val = y;
+                                best[b] = r;
+                            }
+                        }
+                    }
+            }
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        if (best[b] >= 0) a[b].row = original(best[b]);
+        join_lanes(a[b], 16);
+        if (lane < 16) sw[wv][b * 16 + lane] = a[b];
+    }
+    __syncthreads();
+    const int k = threadIdx.x % KP, g = threadIdx.x / KP, groups = BLOCK / KP;
+    if ((int)threadIdx.x < K) {
+        ColStat c = sw[0][k];
+        for (int w = 1; w < WAVES; ++w) join(c, sw[w][k].nrm, sw[w][k].mod, sw[w][k].val, sw[w][k].row);
+        double* pb = part + ((int64_t)blockIdx.x * 64 + k) * 4;
+        st_dev(pb + 0, c.nrm);
+        st_dev(pb + 1, c.mod);
+        st_dev(pb + 2, c.val);
+        st_dev(pb + 3, (double)c.row);
+    }
+    if (!last_block(&st->ticket[TK_RITZ], (uint32_t)G, &s_last)) return;
+    // Thread (g, k) joins workgroups g, g + groups, ... of column k, four
+    // loads in flight (past the end: the last one's, not joined).
+    ColStat c{0.0, -1.0, 0.0, NOROW};
+    if (k < K)
+        for (int b = g; b < G; b += 4 * groups) {
+            double v[4][4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const double* pb = part + ((int64_t)min(b + i * groups, G - 1) * 64 + k) * 4;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[i][q] = ld_dev(pb + q);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (b + i * groups < G) join(c, v[i][0], v[i][1], v[i][2], (int64_t)v[i][3]);
+        }
+    join_lanes(c, KP);
+    __syncthreads();
+    if (lane < KP) sw[wv][lane] = c;
+    __syncthreads();
+    if ((int)threadIdx.x < K) {
+        for (int w = 1; w < WAVES; ++w) join(c, sw[w][k].nrm, sw[w][k].mod, sw[w][k].val, sw[w][k].row);
+        st->ysc[k] = (c.val < 0.0 ? -1.0 : 1.0) / sqrt(c.nrm);
     }
 }
 
@@ -1037,26 +1063,15 @@ static hipError_t finish_p(const Plan& p, const Bufs& b, const Csr& a, double* o
     using VT = typename Tr<P>::V;
     const VT* V = (const VT*)b.V;
     hipLaunchKernelGGL(k_jacobi_select, dim3(1), dim3(JBLOCK), 0, s, b.st, out_vals, p.strict_m);
-    switch (p.KB) {
-#define LZ_RITZ_CASE(KBV)                                                                                    \
-    case KBV:                                                                                                \
-        hipLaunchKernelGGL((k_ritz<P, KBV>), dim3(p.g_dense), dim3(BLOCK), 0, s, b.st, V, p.n, p.ld, b.Y);  \
-        break;
-        LZ_RITZ_CASE(8)
-        LZ_RITZ_CASE(16)
-        LZ_RITZ_CASE(24)
-        LZ_RITZ_CASE(32)
-        LZ_RITZ_CASE(40)
-        LZ_RITZ_CASE(48)
-        LZ_RITZ_CASE(56)
-        LZ_RITZ_CASE(64)
-#undef LZ_RITZ_CASE
-        default:
-            return hipErrorInvalidValue;
+    // A wavefront takes 64 rows at a time.
+    const int gr = (int)std::max<int64_t>(1, std::min<int64_t>(1024, (p.n + 64 * WAVES - 1) / (64 * WAVES)));
+    switch ((p.K + 15) / 16) {
+        case 1: hipLaunchKernelGGL((k_ritz<P, 1>), dim3(gr), dim3(BLOCK), 0, s, b.st, V, p.n, p.ld, b.Y, b.part); break;
+        case 2: hipLaunchKernelGGL((k_ritz<P, 2>), dim3(gr), dim3(BLOCK), 0, s, b.st, V, p.n, p.ld, b.Y, b.part); break;
+        case 3: hipLaunchKernelGGL((k_ritz<P, 3>), dim3(gr), dim3(BLOCK), 0, s, b.st, V, p.n, p.ld, b.Y, b.part); break;
+        default: hipLaunchKernelGGL((k_ritz<P, 4>), dim3(gr), dim3(BLOCK), 0, s, b.st, V, p.n, p.ld, b.Y, b.part); break;
     }
     const int kb2 = pow2_at_least(p.K);
-    const int gc = (int)std::max<int64_t>(1, std::min<int64_t>(1024, (p.n * kb2 + 4 * BLOCK - 1) / (4 * BLOCK)));
-    hipLaunchKernelGGL(k_colstats, dim3(gc), dim3(BLOCK), 0, s, b.st, b.Y, p.n, kb2, b.part);
     if (report && p.ooc) {
         // Host-resident matrix: the residual product streams the slabs too.
         const hipError_t e = ooc_pass(*p.ooc, b.st, s,

@@ -131,7 +131,7 @@ struct Ooc;   // host-resident matrix streamed in slabs (lz_ooc.h)
 // Workspace layout of one solve.  All offsets are in bytes from the base.
 struct Plan {
     int64_t n = 0, nnz = 0, ld = 0;
-    int32_t K = 0, m = 0, prec = 0, KB = 0;
+    int32_t K = 0, m = 0, prec = 0;
     int32_t g_orth = 0, g_dense = 0, g_tile = 0;
     int32_t xcache = 0;         // Lanczos-step SpMV keeps the head of x in LDS: XC_OFF, XC_ON (set once the
                                 // row order is known) or XC_GATED (both variants launched; each returns
