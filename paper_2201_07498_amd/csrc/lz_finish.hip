@@ -737,38 +737,6 @@ __global__ __launch_bounds__(BLOCK) void k_spmm(State* st, const double* __restr
     }
 }
 
-// Unit Ritz vectors y_k = ysc_k Y[:,k] into the caller's column-major output
-// in original row order: a 64-row block is gathered row-wise (through the
-// original-to-solve row map when the matrix was relabelled) and written
-// column-wise through LDS.
-__global__ __launch_bounds__(BLOCK) void k_out(const State* st, const double* __restrict__ Y, int64_t n, int KB2,
-                                               double* __restrict__ out) {
-    __shared__ double ys[64][65];
-    if (st->status != 0) return;
-    const int K = st->K;
-    const int tid = threadIdx.x, k = tid % KB2;
-    const bool act = k < K;
-    const double ysc = act ? st->ysc[k] : 0.0;
-    const int32_t* iperm = st->iperm;
-    for (int64_t r0 = (int64_t)blockIdx.x * 64; r0 < n; r0 += (int64_t)gridDim.x * 64) {
-        for (int idx = tid; idx < 64 * KB2; idx += BLOCK) {
-            const int row = idx / KB2;
-            const int64_t r = r0 + row;
-            if (r < n && act) {
-                const int64_t i = iperm ? iperm[r] : r;
-                ys[row][k] = ysc * Y[i * K + k];
-            }
-        }
-        __syncthreads();
-        for (int idx = tid; idx < 64 * K; idx += BLOCK) {
-            const int kk = idx / 64, row = idx % 64;
-            const int64_t r = r0 + row;
-            if (r < n) out[(int64_t)kk * n + r] = ys[row][kk];
-        }
-        __syncthreads();
-    }
-}
-
 // -------------------------------------------------------- orthogonality
 // Gram matrices on the FP64 matrix cores (v_mfma_f64_16x16x4f64), straight from
 // global memory: lane l holds rows 4 (l/16) .. + 3 of column 16 b + l%16 of
@@ -784,7 +752,8 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 // acc of the block pairs -> gp[pair * 256 + i * 16 + j] (element e of lane l
 // holds D[4e + l/16][l % 16]), wavefronts in order.
 template <int NP>
-__device__ __forceinline__ void gram_store(const d4 (&acc)[NP], double* gp, double (*sh)[256]) {
+__device__ __forceinline__ void gram_store(const d4 (&acc)[NP], double* gp) {
+    __shared__ double sh[NP][256];
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int w = 0; w < WAVES; ++w) {
         if (wv == w)
@@ -806,7 +775,6 @@ __global__ __launch_bounds__(BLOCK) void k_gram(const State* st, const T* __rest
                                                 double* __restrict__ gpart) {
     constexpr int NP = NB * (NB + 1) / 2;
     typedef T T4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
-    __shared__ double sh[NP][256];
     if (st->status != 0) return;
     const int c = min(st->j, st->m);
     if (c < 1 || c > 16 * NB) return;
@@ -856,25 +824,32 @@ __global__ __launch_bounds__(BLOCK) void k_gram(const State* st, const T* __rest
                         acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[bi], x[bj], acc[t], 0, 0, 0);
             }
     }
-    gram_store<NP>(acc, gpart + (int64_t)blockIdx.x * GRAM_SLOT, sh);
+    gram_store<NP>(acc, gpart + (int64_t)blockIdx.x * GRAM_SLOT);
 }
 
-// Residuals ||A y_k - theta_k y_k|| = ||ysc_k Z[:,k] - theta_k ysc_k Y[:,k]||
-// (Sec. IV-D) and the Gram matrix of the unit Ritz vectors in one pass over Y
-// and Z (row-major, n x K), in the solve's row order: lane l takes columns 16 b
-// + l%16 of rows l/16, l/16 + 4, ...  Sums of squares go to rpart[workgroup *
-// 64 + column].  (One pass each: 55 + 62 us at R-MAT 20, K = 16; together
-// 48 us.)
-template <int NB>
-__global__ __launch_bounds__(BLOCK) void k_resid_gram(const State* st, const double* __restrict__ Y,
-                                                      const double* __restrict__ Z, int64_t n,
-                                                      double* __restrict__ gpart, double* __restrict__ rpart) {
-    constexpr int NP = NB * (NB + 1) / 2, U = NB == 1 ? 8 : 4;     // rows of a lane in flight
-    __shared__ double sh[NP][256];
+// Unit Ritz vectors y_k = ysc_k Y[:,k] into the caller's column-major output
+// in original row order and, with REPORT, in the same pass over Y and Z (both
+// row-major, n x K) the residuals ||A y_k - theta_k y_k|| = ||ysc_k Z[:,k] -
+// theta_k ysc_k Y[:,k]|| (Sec. IV-D) and the Gram matrix of the unit vectors.
+// A wavefront takes 4 U rows on its own: lane l gathers columns 16 b + l%16 of
+// rows l/16, l/16 + 4, ... (through the original-to-solve row map when the
+// matrix was relabelled; the next rows' map entries are loaded ahead), which are
+// the operands of the FP64 matrix cores, and the rows leave column-wise
+// through LDS.  Bound by the bytes of Y, Z and the output.  Sums of squares go
+// to rpart[workgroup * 64 + column].  (R-MAT 20, K = 16: output 99 us and
+// residual with Gram 48 us as separate passes; together 86 us.  R-MAT 25, K
+// = 8: 1.55 + 0.84 -> 2.02 ms.)
+template <int NB, bool REPORT>
+__global__ __launch_bounds__(BLOCK) void k_out(const State* st, const double* __restrict__ Y,
+                                               const double* __restrict__ Z, int64_t n, double* __restrict__ out,
+                                               double* __restrict__ gpart, double* __restrict__ rpart) {
+    constexpr int NP = NB * (NB + 1) / 2, U = NB <= 2 ? 8 : 4, R = 4 * U;
+    __shared__ double ys[WAVES][R][NB * 16 + 1];
     __shared__ double shr[WAVES][NB * 16];
     if (st->status != 0) return;
     const int K = st->K;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, cl = lane & 15, rg = lane >> 4;
+    const int32_t* __restrict__ iperm = st->iperm;
     double ysc[NB], th[NB], racc[NB];
     int kc[NB];
 #pragma unroll
@@ -882,48 +857,72 @@ __global__ __launch_bounds__(BLOCK) void k_resid_gram(const State* st, const dou
         const int k = b * 16 + cl;
         const bool act = k < K;
         ysc[b] = act ? st->ysc[k] : 0.0;
-        th[b] = act ? st->theta[st->sel[k]] : 0.0;
+        th[b] = REPORT && act ? st->theta[st->sel[k]] : 0.0;
         kc[b] = min(k, K - 1);
         racc[b] = 0.0;
     }
     d4 acc[NP];
 #pragma unroll
     for (int t = 0; t < NP; ++t) acc[t] = d4{0.0, 0.0, 0.0, 0.0};
-    const int64_t step = (int64_t)gridDim.x * WAVES * 4 * U;
-    for (int64_t r0 = ((int64_t)blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(wv)) * 4 * U; r0 < n; r0 += step) {
-        double y[U][NB], z[U][NB];
+    const int64_t step = (int64_t)gridDim.x * WAVES * R;
+    int64_t r0 = ((int64_t)blockIdx.x * WAVES + __builtin_amdgcn_readfirstlane(wv)) * R;
+    int64_t src[U];
+    auto rows = [&](int64_t base) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t r = min(r0 + u * 4 + rg, n - 1);
+            const int64_t r = min(base + u * 4 + rg, n - 1);
+            src[u] = iperm ? (int64_t)iperm[r] : r;
+        }
+    };
+    rows(r0);
+    for (; r0 < n; r0 += step) {
+        double y[U][NB], z[U][NB];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                y[u][b] = Y[r * K + kc[b]];
-                z[u][b] = Z[r * K + kc[b]];
+                y[u][b] = Y[src[u] * K + kc[b]];
+                if (REPORT) z[u][b] = Z[src[u] * K + kc[b]];
             }
-        }
+        rows(r0 + step);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const bool in = r0 + u * 4 + rg < n;
             double x[NB];
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
-                x[b] = in ? ysc[b] * y[u][b] : 0.0;
-                const double d = in ? ysc[b] * z[u][b] - th[b] * x[b] : 0.0;
-                racc[b] += d * d;
+                const double v = ysc[b] * y[u][b];
+                ys[wv][u * 4 + rg][b * 16 + cl] = v;
+                x[b] = in ? v : 0.0;
+                if (REPORT) {
+                    const double d = in ? ysc[b] * z[u][b] - th[b] * v : 0.0;
+                    racc[b] += d * d;
+                }
             }
+            if (REPORT)
 #pragma unroll
-            for (int bi = 0, t = 0; bi < NB; ++bi)
+                for (int bi = 0, t = 0; bi < NB; ++bi)
 #pragma unroll
-                for (int bj = bi; bj < NB; ++bj, ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[bi], x[bj], acc[t], 0, 0, 0);
+                    for (int bj = bi; bj < NB; ++bj, ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[bi], x[bj], acc[t], 0, 0, 0);
         }
+        // The wavefront's own rows: its LDS accesses stay in order.
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int row = lane % R;
+        if (r0 + row < n)
+            for (int k = lane / R; k < K; k += 64 / R) out[(int64_t)k * n + r0 + row] = ys[wv][row][k];
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
+    if (!REPORT) return;
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         racc[b] = add_xor_rows<32>(add_xor_rows<16>(racc[b]));
         if (lane < 16) shr[wv][b * 16 + lane] = racc[b];
     }
-    gram_store<NP>(acc, gpart + (int64_t)blockIdx.x * GRAM_SLOT, sh);      // its barriers order shr
+    __syncthreads();
+    gram_store<NP>(acc, gpart + (int64_t)blockIdx.x * GRAM_SLOT);
     if ((int)threadIdx.x < NB * 16) {
         double s = shr[0][threadIdx.x];
         for (int w = 1; w < WAVES; ++w) s += shr[w][threadIdx.x];
@@ -1045,14 +1044,16 @@ static int launch_gram(const State* st, const T* X, int64_t ldx, int64_t n, int 
     return g;
 }
 
-static int launch_resid_gram(const State* st, const double* Y, const double* Z, int64_t n, int K, double* gpart,
-                             double* rpart, hipStream_t s) {
-    const int nb = (K + 15) / 16, g = gram_grid(n, nb == 1 ? 32 : 16);
+// Returns its grid; a wavefront takes 32 rows, past 32 columns 16.
+template <bool REPORT>
+static int launch_out(const State* st, const double* Y, const double* Z, int64_t n, int K, double* out, double* gpart,
+                      double* rpart, hipStream_t s) {
+    const int nb = (K + 15) / 16, g = gram_grid(n, nb <= 2 ? 32 : 16);
     switch (nb) {
-        case 1: hipLaunchKernelGGL(k_resid_gram<1>, dim3(g), dim3(BLOCK), 0, s, st, Y, Z, n, gpart, rpart); break;
-        case 2: hipLaunchKernelGGL(k_resid_gram<2>, dim3(g), dim3(BLOCK), 0, s, st, Y, Z, n, gpart, rpart); break;
-        case 3: hipLaunchKernelGGL(k_resid_gram<3>, dim3(g), dim3(BLOCK), 0, s, st, Y, Z, n, gpart, rpart); break;
-        default: hipLaunchKernelGGL(k_resid_gram<4>, dim3(g), dim3(BLOCK), 0, s, st, Y, Z, n, gpart, rpart); break;
+        case 1: hipLaunchKernelGGL((k_out<1, REPORT>), dim3(g), dim3(BLOCK), 0, s, st, Y, Z, n, out, gpart, rpart); break;
+        case 2: hipLaunchKernelGGL((k_out<2, REPORT>), dim3(g), dim3(BLOCK), 0, s, st, Y, Z, n, out, gpart, rpart); break;
+        case 3: hipLaunchKernelGGL((k_out<3, REPORT>), dim3(g), dim3(BLOCK), 0, s, st, Y, Z, n, out, gpart, rpart); break;
+        default: hipLaunchKernelGGL((k_out<4, REPORT>), dim3(g), dim3(BLOCK), 0, s, st, Y, Z, n, out, gpart, rpart); break;
     }
     return g;
 }
@@ -1089,12 +1090,13 @@ static hipError_t finish_p(const Plan& p, const Bufs& b, const Csr& a, double* o
                            b.ob, b.tk, b.head, b.tail, kb2, a.rowptr, a.col, a.val, b.rp2, b.col2, b.val2,
                            (int64_t)0, p.n_tiles);
     }
-    const int go = (int)std::max<int64_t>(1, std::min<int64_t>(2048, (p.n + 63) / 64));
-    hipLaunchKernelGGL(k_out, dim3(go), dim3(BLOCK), 0, s, b.st, b.Y, p.n, kb2, out_vecs);
-    if (!report) return hipGetLastError();
+    if (!report) {
+        launch_out<false>(b.st, b.Y, nullptr, p.n, p.K, out_vecs, nullptr, nullptr, s);
+        return hipGetLastError();
+    }
     double* gpart_y = b.gram + (int64_t)GRAM_GRID * GRAM_SLOT;
+    const int gy = launch_out<true>(b.st, b.Y, b.Z, p.n, p.K, out_vecs, gpart_y, b.part2, s);
     const int gv = launch_gram<VT>(b.st, V, p.ld, p.n, p.m, b.gram, s);
-    const int gy = launch_resid_gram(b.st, b.Y, b.Z, p.n, p.K, gpart_y, b.part2, s);
     const int values = p.m * (p.m + 1) / 2 + p.K * (p.K + 1) / 2 + p.K;
     hipLaunchKernelGGL(k_gram_finish, dim3((values + BLOCK / 64 - 1) / (BLOCK / 64)), dim3(BLOCK), 0, s, b.st, b.gram,
                        gpart_y, b.part2, gv, (p.m + 15) / 16, gy, (p.K + 15) / 16, b.gram + GRAM_OUT);
