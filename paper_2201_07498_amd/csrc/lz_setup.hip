@@ -225,11 +225,35 @@ __device__ __forceinline__ int degree_key(int64_t d) {
     return __builtin_clzll(x);       // = 63 - floor(log2 x), in [2, 63]
 }
 
-// hist[key * nch + c] = rows of class key in chunk c.
+// New labels of the longest rows by old label, for the relabelling fill: a
+// direct-mapped table of HOT_SLOTS words, (new label << HOT_TAGBITS) | tag.
+// Slot and tag are the high and low bits of hot_hash, a bijection of 32 bits,
+// so they name the old label exactly; where two labels want a slot, the longer
+// row has it.  Gathering iperm for every entry (128 MiB at n = 2^25) costs an L2
+// miss each: 1.10e9 misses for 1.04e9 entries at R-MAT 25, at the 52 G lines/s
+// that random lines from beyond L2 reach, 20.8 ms.  The table stays in each XCD's
+// L2 and its rows own many entries of a skewed matrix, so only the rest goes to
+// iperm: 0.80e9 misses, 15.7 ms (16.1 with the outputs through L2; 18.0 with
+// a division and two loads per entry in the sweep payload).  R-MAT 23 BF16:
+// 3.91 -> 3.14 ms.  Tables of 1 and 4 MiB took 18.4 ms where this one took 18.0.
+constexpr int HOT_BITS = 19, HOT_TAGBITS = 32 - HOT_BITS;       // 2 MiB
+constexpr int64_t HOT_SLOTS = int64_t(1) << HOT_BITS, HOT_LABELS = int64_t(1) << 18;
+static_assert(HOT_LABELS << HOT_TAGBITS <= int64_t(0xffffffff), "an empty slot's label is past the last hot one");
+static_assert(HOT_SLOTS * 4 <= GRAM_DOUBLES * 8, "kept in the Gram buffer until the solve reports");
+// From 2^22 rows (iperm of 16 MiB against an L2 of 4 MiB); below, most gathers of
+// iperm hit L2 and the table costs a load more.
+constexpr int64_t HOT_MIN_N = int64_t(1) << 22;
+__device__ __forceinline__ uint32_t hot_hash(int32_t old_label) { return (uint32_t)old_label * 0x9e3779b1u; }
+
+// hist[key * nch + c] = rows of class key in chunk c.  Empties the table of
+// hot labels on the way.
 __global__ __launch_bounds__(BLOCK) void k_rl_hist(const State* st, const int64_t* rp, int64_t n, int64_t nch,
-                                                   uint64_t* hist) {
+                                                   uint64_t* hist, uint32_t* hot) {
     __shared__ uint32_t cnt[NKEY];
     if (!st->reordered) return;
+    if (hot)
+        for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < HOT_SLOTS; i += (int64_t)gridDim.x * BLOCK)
+            hot[i] = 0xffffffffu;
     const int64_t c = blockIdx.x;
     if (threadIdx.x < NKEY) cnt[threadIdx.x] = 0u;
     __syncthreads();
@@ -284,13 +308,18 @@ __global__ __launch_bounds__(BLOCK) void k_rl_rank(const State* st, const int64_
     }
 }
 
-// Row lengths of the relabelled matrix into rp2 (scanned afterwards).
+// Row lengths of the relabelled matrix into rp2 (scanned afterwards) and the
+// hot labels into their table.
 __global__ __launch_bounds__(BLOCK) void k_rl_rowlen(const State* st, const int64_t* rp, int64_t n,
-                                                     const int32_t* perm, int64_t* rp2, int64_t nnz) {
+                                                     const int32_t* perm, int64_t* rp2, int64_t nnz, uint32_t* hot) {
     if (!st->reordered) return;
     for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLOCK) {
         const int64_t r = perm[i];
         rp2[i] = rp[r + 1] - rp[r];
+        if (hot && i < HOT_LABELS) {
+            const uint32_t h = hot_hash((int32_t)r);
+            atomicMin(&hot[h >> HOT_TAGBITS], ((uint32_t)i << HOT_TAGBITS) | (h & ((1u << HOT_TAGBITS) - 1u)));
+        }
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) rp2[n] = nnz;
 }
@@ -360,14 +389,14 @@ __device__ __forceinline__ void sort_keys(uint32_t (&kr)[TP], int tid, uint32_t*
 // the tile (clamped at -1: only the first row can start before it) and the
 // shift from new to old position (rp[perm[row]] - rp2[row]).  Returns the
 // tile's entry count (0: row ends only, nothing loaded).
-template <class VT>
+template <bool HOT = false, class VT>
 __device__ __forceinline__ int fill_tile_gather(int64_t t, const int64_t* __restrict__ rp,
                                                 const int32_t* __restrict__ col, const VT* __restrict__ val,
                                                 int64_t n, int64_t nnz, const int32_t* __restrict__ ob,
                                                 const int32_t* __restrict__ perm, const int32_t* __restrict__ iperm,
                                                 const int64_t* __restrict__ rp2, int32_t* s, int64_t* d, int lane,
                                                 int64_t* t0_out, int32_t (&c)[TP], VT (&v)[TP],
-                                                int32_t (&rows)[TP]) {
+                                                int32_t (&rows)[TP], const uint32_t* __restrict__ hot = nullptr) {
     const int64_t r_lo = ob[t], r_hi = ob[t + 1];
     const int64_t t0 = t * TILE - r_lo;
     *t0_out = t0;
@@ -391,17 +420,38 @@ __device__ __forceinline__ int fill_tile_gather(int64_t t, const int64_t* __rest
         src[e] = t0 + k + d[lo];
         rows[e] = (int32_t)(r_lo + lo);
     }
+    if constexpr (HOT) {
+        // The streams pass L2 by, the table stays.
 #pragma unroll
-    for (int e = 0; e < TP; ++e) {
-        c[e] = col[src[e]];
-        v[e] = val[src[e]];
+        for (int e = 0; e < TP; ++e) {
+            c[e] = __builtin_nontemporal_load(col + src[e]);
+            v[e] = __builtin_nontemporal_load(val + src[e]);
+        }
+        uint32_t word[TP];
+#pragma unroll
+        for (int e = 0; e < TP; ++e) word[e] = hot[hot_hash(c[e]) >> HOT_TAGBITS];
+#pragma unroll
+        for (int e = 0; e < TP; ++e) {
+            const bool hit = ((word[e] ^ hot_hash(c[e])) & ((1u << HOT_TAGBITS) - 1u)) == 0u &&
+                             (word[e] >> HOT_TAGBITS) < (uint32_t)HOT_LABELS;
+            if (hit)
+                c[e] = (int32_t)(word[e] >> HOT_TAGBITS);
+            else
+                c[e] = iperm[c[e]];
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < TP; ++e) {
+            c[e] = col[src[e]];
+            v[e] = val[src[e]];
+        }
+#pragma unroll
+        for (int e = 0; e < TP; ++e) c[e] = iperm[c[e]];
     }
-#pragma unroll
-    for (int e = 0; e < TP; ++e) c[e] = iperm[c[e]];
     return cnt;
 }
 
-template <class VT>
+template <class VT, bool HOT>
 __global__ __launch_bounds__(FILL_WAVES * 64) void k_rl_fill(const State* st, const int64_t* __restrict__ rp,
                                                             const int32_t* __restrict__ col,
                                                             const VT* __restrict__ val, int64_t n, int64_t nnz,
@@ -411,8 +461,9 @@ __global__ __launch_bounds__(FILL_WAVES * 64) void k_rl_fill(const State* st, co
                                                             const int64_t* __restrict__ rp2,
                                                             int32_t* __restrict__ col2, VT* __restrict__ val2,
                                                             const int32_t* __restrict__ swob,
-                                                            const int64_t* __restrict__ swe, int64_t sw_items,
-                                                            uint32_t* __restrict__ swvin) {
+                                                            const int64_t* __restrict__ swe, int64_t sw_items, int64_t sw_nb,
+                                                            uint32_t* __restrict__ swvin,
+                                                            const uint32_t* __restrict__ hot) {
     __shared__ int32_t srp[FILL_WAVES][TILE + 2];
     __shared__ int64_t sdel[FILL_WAVES][TILE + 1];
     if (!st->reordered) return;
@@ -428,27 +479,40 @@ __global__ __launch_bounds__(FILL_WAVES * 64) void k_rl_fill(const State* st, co
         VT v[TP];
         int32_t rows[TP];
         int64_t t0 = 0;
-        const int cnt = fill_tile_gather(t, rp, col, val, n, nnz, ob, perm, iperm, rp2, s, d, lane, &t0, c, v, rows);
+        const int cnt =
+            fill_tile_gather<HOT>(t, rp, col, val, n, nnz, ob, perm, iperm, rp2, s, d, lane, &t0, c, v, rows, hot);
         if (cnt <= 0) continue;                   // row ends only: no entries to move
         if (!packed) {
 #pragma unroll
             for (int e = 0; e < TP; ++e) {
                 const int k = e * 64 + lane;
                 if (k < cnt) {
-                    col2[t0 + k] = c[e];
-                    val2[t0 + k] = v[e];
+                    __builtin_nontemporal_store(c[e], col2 + t0 + k);
+                    __builtin_nontemporal_store(v[e], val2 + t0 + k);
                 }
             }
             if (sweep) {
                 // Sort payload of the sweep blocks: the entry's row within its
-                // block (high bits) and its position in the block.
+                // block (high bits) and its position in the block.  A tile's
+                // items span fewer than a block's, so its entries lie in the
+                // block of its first one or the next: both blocks' offsets
+                // are loaded once for the tile, relative to its first row and
+                // entry.
+                static_assert(SW_W * sweep_rows(1) > TILE + SW_W * (TILE + 1) && sweep_rows(0) >= sweep_rows(1) &&
+                                  sweep_rows(2) >= sweep_rows(1),
+                              "a tile spans two sweep blocks at most");
+                const int64_t r_lo = ob[t], b0 = (t0 + SW_W * r_lo) / sw_items, b1 = min(b0 + 1, sw_nb);
+                const int64_t left = (b0 + 1) * sw_items - (t0 + SW_W * r_lo);
+                const int32_t dr0 = (int32_t)r_lo - swob[b0], dr1 = (int32_t)r_lo - swob[b1];
+                const int32_t dp0 = (int32_t)(t0 - swe[b0]), dp1 = (int32_t)(t0 - swe[b1]);
+                const int32_t room = (int32_t)min<int64_t>(left, INT32_MAX);
 #pragma unroll
                 for (int e = 0; e < TP; ++e) {
                     const int k = e * 64 + lane;
                     if (k < cnt) {
-                        const int64_t pos = t0 + k, r = rows[e];
-                        const int64_t b = (pos + SW_W * r) / sw_items;
-                        swvin[pos] = ((uint32_t)(r - swob[b]) << SW_POSBITS) | (uint32_t)(pos - swe[b]);
+                        const int32_t dr = rows[e] - (int32_t)r_lo;
+                        const bool next = k + SW_W * dr >= room;
+                        __builtin_nontemporal_store(((uint32_t)(dr + (next ? dr1 : dr0)) << SW_POSBITS) | (uint32_t)(k + (next ? dp1 : dp0)), swvin + t0 + k);
                     }
                 }
             }
@@ -597,6 +661,18 @@ __global__ void k_resume(State* st) {
 
 void launch_resume(const Bufs& b, hipStream_t s) { hipLaunchKernelGGL(k_resume, dim3(1), dim3(1), 0, s, b.st); }
 
+template <class VT> static void launch_fill(const Plan& p, const Bufs& b, const Csr& a, const uint32_t* hot, hipStream_t s) {
+    const dim3 grid(p.g_tile * (WAVES / FILL_WAVES)), block(FILL_WAVES * 64);
+    if (hot)
+        hipLaunchKernelGGL((k_rl_fill<VT, true>), grid, block, 0, s, b.st, a.rowptr, a.col, (const VT*)a.val, a.n, a.nnz,
+                           p.n_tiles, b.ob, b.perm, b.iperm, b.rp2, b.col2, (VT*)b.val2, b.swob, b.swe, p.sw_items, p.sw_nb,
+                           b.swvin, hot);
+    else
+        hipLaunchKernelGGL((k_rl_fill<VT, false>), grid, block, 0, s, b.st, a.rowptr, a.col, (const VT*)a.val, a.n, a.nnz,
+                           p.n_tiles, b.ob, b.perm, b.iperm, b.rp2, b.col2, (VT*)b.val2, b.swob, b.swe, p.sw_items, p.sw_nb,
+                           b.swvin, hot);
+}
+
 hipError_t launch_setup(const Plan& p, const Bufs& b, const Csr& a, uint64_t seed, int reorth, int reorder,
                         hipStream_t s) {
     hipLaunchKernelGGL(k_reset, dim3(1), dim3(BLOCK), 0, s, b.st, p.m, p.K, reorth, reorder, unit_roundoff(p.prec),
@@ -610,34 +686,25 @@ hipError_t launch_setup(const Plan& p, const Bufs& b, const Csr& a, uint64_t see
     // kernels (11 to 14 that would return at once) are not launched.
     const bool relabel = reorder == LZ_REORDER_HUBS || (reorder == LZ_REORDER_AUTO && n >= REORDER_MIN_N);
     const int32_t* gate = &b.st->reordered;
+    uint32_t* hot = n >= HOT_MIN_N ? (uint32_t*)b.gram : nullptr;
     if (relabel) {
         const int64_t nch = (n + CHR - 1) / CHR;
-        hipLaunchKernelGGL(k_rl_hist, dim3((unsigned)nch), dim3(BLOCK), 0, s, b.st, a.rowptr, n, nch, b.scan);
+        hipLaunchKernelGGL(k_rl_hist, dim3((unsigned)nch), dim3(BLOCK), 0, s, b.st, a.rowptr, n, nch, b.scan,
+                           hot);
         launch_scan(gate, b.scan, NKEY * nch, b.bsum, s);
         hipLaunchKernelGGL(k_rl_rank, dim3((unsigned)nch), dim3(BLOCK), 0, s, b.st, a.rowptr, n, nch, b.scan,
                            b.perm, b.iperm);
-        hipLaunchKernelGGL(k_rl_rowlen, dim3(g), dim3(BLOCK), 0, s, b.st, a.rowptr, n, b.perm, b.rp2, nnz);
+        hipLaunchKernelGGL(k_rl_rowlen, dim3(g), dim3(BLOCK), 0, s, b.st, a.rowptr, n, b.perm, b.rp2, nnz,
+                           hot);
         launch_scan(gate, (uint64_t*)b.rp2, n, b.bsum, s);
     }
     hipLaunchKernelGGL(k_setup_tiles, dim3(g), dim3(BLOCK), 0, s, b.st, n, p.n_tiles, b.ob, b.tk);
     if (relabel) {
         launch_sweep_blocks(p, b, s);             // the relabelling fill writes the sort payload by block
         switch (p.prec) {
-            case 0:
-                hipLaunchKernelGGL(k_rl_fill<double>, dim3(p.g_tile * (WAVES / FILL_WAVES)), dim3(FILL_WAVES * 64), 0, s, b.st, a.rowptr, a.col,
-                                   (const double*)a.val, n, nnz, p.n_tiles, b.ob, b.perm, b.iperm, b.rp2, b.col2,
-                                   (double*)b.val2, b.swob, b.swe, p.sw_items, b.swvin);
-                break;
-            case 1:
-                hipLaunchKernelGGL(k_rl_fill<float>, dim3(p.g_tile * (WAVES / FILL_WAVES)), dim3(FILL_WAVES * 64), 0, s, b.st, a.rowptr, a.col,
-                                   (const float*)a.val, n, nnz, p.n_tiles, b.ob, b.perm, b.iperm, b.rp2, b.col2,
-                                   (float*)b.val2, b.swob, b.swe, p.sw_items, b.swvin);
-                break;
-            default:
-                hipLaunchKernelGGL(k_rl_fill<uint16_t>, dim3(p.g_tile * (WAVES / FILL_WAVES)), dim3(FILL_WAVES * 64), 0, s, b.st, a.rowptr, a.col,
-                                   (const uint16_t*)a.val, n, nnz, p.n_tiles, b.ob, b.perm, b.iperm, b.rp2, b.col2,
-                                   (uint16_t*)b.val2, b.swob, b.swe, p.sw_items, b.swvin);
-                break;
+            case 0: launch_fill<double>(p, b, a, hot, s); break;
+            case 1: launch_fill<float>(p, b, a, hot, s); break;
+            default: launch_fill<uint16_t>(p, b, a, hot, s); break;
         }
         // Group-sorted copy (decided on the device; the kernel returns unless
         // the state asks for it).
