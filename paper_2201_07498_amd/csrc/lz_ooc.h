@@ -31,6 +31,8 @@ namespace lz {
 struct Ooc {
     const int32_t* hcol = nullptr;   // pinned host arrays of the caller, nnz entries
     const char* hval = nullptr;
+    const int32_t* dcol = nullptr;   // the same as the device addresses them; null if it cannot
+    const char* dval = nullptr;
     size_t vb = 0;                   // bytes per value
     int64_t n = 0;
     std::vector<int64_t> tb;         // slab k: tiles [tb[k], tb[k+1])
@@ -59,6 +61,9 @@ inline T* entry_base(T* p, int64_t e0, size_t bytes) {
     return (T*)((uintptr_t)p - (uintptr_t)e0 * (uintptr_t)bytes);
 }
 
+// Copies entries [e0, e1) into staging buffer i on the copy stream.
+hipError_t ooc_pull(const Ooc& o, int i, int64_t e0, int64_t e1);
+
 // One pass over a host-resident matrix on stream s: for slab k = 0 .. nslab-1
 // in order, launch(col, val, tb, te, k, nslab) once the slab's entries are on
 // the device, with col/val indexed by matrix entry.
@@ -79,12 +84,7 @@ hipError_t ooc_pass(Ooc& o, State* st, hipStream_t s, L&& launch) {
             o.next ^= 1;
             if ((e = hipStreamWaitEvent(o.cs, o.freed[i], 0)) != hipSuccess) return e;
             if (e1 > e0) {
-                if ((e = hipMemcpyAsync(o.scol[i], o.hcol + e0, (size_t)(e1 - e0) * 4, hipMemcpyHostToDevice,
-                                        o.cs)) != hipSuccess)
-                    return e;
-                if ((e = hipMemcpyAsync(o.sval[i], o.hval + (size_t)e0 * o.vb, (size_t)(e1 - e0) * o.vb,
-                                        hipMemcpyHostToDevice, o.cs)) != hipSuccess)
-                    return e;
+                if ((e = ooc_pull(o, i, e0, e1)) != hipSuccess) return e;
                 o.streamed += (e1 - e0) * (int64_t)(4 + o.vb);
             }
             if ((e = hipEventRecord(o.ready[i], o.cs)) != hipSuccess) return e;

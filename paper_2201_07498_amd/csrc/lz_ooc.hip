@@ -8,6 +8,61 @@
 
 namespace lz {
 
+// A slab's column indices and values from pinned host memory to a staging buffer.
+// The host link bounds it (57.5 GB/s for one large copy): 16 workgroups keep
+// 512 KiB in flight, several times what the link's latency asks for, and leave the
+// chip to the slab before.  Loads are aligned to 16 bytes of the source, which
+// starts anywhere; the stores take what alignment that leaves.  Copies by the
+// runtime cost the host thread 70 to 450 us inside a call about once per slab,
+// while the copy stream idled.  16.1M FP32 entries, 16 steps, slabs of 2^18 / 2^20 /
+// 2^22 / 2^24 entries: 76.7 / 62.7 / 48.3 / 51.8 -> 62.6 / 47.0 / 43.4 / 42.2 ms a
+// solve.  256 / 128 / 64 / 32 workgroups with 4 loads a thread took 25.2 / 23.8 /
+// 23.1 / 21.9 ms where 16 with 8 took 21.7, 8 with 4 27.9 (8.4M entries, half
+// resident, slabs of 2^20).
+constexpr int PULL_GRID = 16, PULL_U = 8;
+__global__ __launch_bounds__(BLOCK) void k_pull(const char* __restrict__ src0, char* __restrict__ dst0, int64_t bytes0,
+                                                const char* __restrict__ src1, char* __restrict__ dst1,
+                                                int64_t bytes1) {
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t u4any __attribute__((ext_vector_type(4), aligned(1)));
+    const int64_t T = (int64_t)gridDim.x * BLOCK, first = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+        const char* src = a == 0 ? src0 : src1;
+        char* dst = a == 0 ? dst0 : dst1;
+        const int64_t bytes = a == 0 ? bytes0 : bytes1;
+        const int64_t head = min<int64_t>(bytes, (int64_t)(-(uintptr_t)src & 15u)), words = (bytes - head) >> 4;
+        const u4* s = (const u4*)(src + head);
+        char* d = dst + head;
+        for (int64_t i = first; i < words; i += PULL_U * T) {
+            u4 v[PULL_U];
+#pragma unroll
+            for (int q = 0; q < PULL_U; ++q) v[q] = __builtin_nontemporal_load(s + min(i + q * T, words - 1));
+#pragma unroll
+            for (int q = 0; q < PULL_U; ++q)
+                if (i + q * T < words) *(u4any*)(d + (i + q * T) * 16) = v[q];
+        }
+        if (first < head) dst[first] = src[first];
+        const int64_t done = head + words * 16;
+        if (first < bytes - done) dst[done + first] = src[done + first];
+    }
+}
+
+hipError_t ooc_pull(const Ooc& o, int i, int64_t e0, int64_t e1) {
+    const int64_t cb = (e1 - e0) * 4, vb = (e1 - e0) * (int64_t)o.vb;
+    if (o.dcol) {
+        const int g = (int)std::max<int64_t>(1, std::min<int64_t>(PULL_GRID, (std::max(cb, vb) + BLOCK * 16 - 1) / (BLOCK * 16)));
+        hipLaunchKernelGGL(k_pull, dim3(g), dim3(BLOCK), 0, o.cs, (const char*)(o.dcol + e0), (char*)o.scol[i], cb,
+                           o.dval + (size_t)e0 * o.vb, o.sval[i], vb);
+        return hipGetLastError();
+    }
+    // Pinned memory that the device cannot address.
+    hipError_t e = hipMemcpyAsync(o.scol[i], o.hcol + e0, (size_t)cb, hipMemcpyHostToDevice, o.cs);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(o.sval[i], o.hval + (size_t)e0 * o.vb, (size_t)vb, hipMemcpyHostToDevice, o.cs);
+    return e;
+}
+
 namespace {
 // Streams and events of the host-resident solves, created on first use per
 // host thread and device and kept for the process: a freshly created pair of
@@ -136,7 +191,18 @@ hipError_t ooc_prepare(Plan& p, const Bufs& b, Ooc& o, int64_t slab_nnz, int64_t
         o.streamed += eres * (int64_t)(4 + o.vb);
     }
     // Staging buffers and the copy stream for the others.
+    o.dcol = nullptr;
+    o.dval = nullptr;
     if (o.nres < ns) {
+        void *dc = nullptr, *dv = nullptr;
+        if (hipHostGetDevicePointer(&dc, (void*)o.hcol, 0) == hipSuccess &&
+            hipHostGetDevicePointer(&dv, (void*)o.hval, 0) == hipSuccess && dc == (const void*)o.hcol &&
+            dv == (const void*)o.hval) {
+            o.dcol = (const int32_t*)dc;
+            o.dval = (const char*)dv;
+        } else {
+            (void)hipGetLastError();
+        }
         const size_t me = (size_t)std::max<int64_t>(maxe, 1);
         for (int i = 0; i < 2; ++i) {
             if ((e = hipMalloc((void**)&o.scol[i], me * 4)) != hipSuccess) return e;
