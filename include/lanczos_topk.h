@@ -201,11 +201,13 @@ const char* lz_status_string(int status);
  *             lambda descending.
  *   out_vecs: device double[n*K], column-major (vector k at out_vecs+k*n),
  *             unit 2-norm, signed so its entry of largest modulus is positive.
- * Default options; the library allocates its workspace for the call
- * (stream-ordered, hipMallocAsync on `stream`).
- * Blocking: reads nnz = rowptr[n] and, after the m iterations, the step count
- * back from the device (more iterations follow breakdowns), and returns
- * after the results are in out_vals/out_vecs.  lanczos_topk_async is the
+ * Default options; the library allocates its workspace for the call,
+ * stream-ordered on `stream` from a memory pool of its own that keeps at most
+ * 2 GiB between calls (inside a stream capture: from the device's default pool).
+ * Blocking: reads nnz = rowptr[n] back from the device and returns after the
+ * results are in out_vals/out_vecs.  The finish is enqueued behind the m
+ * iterations and does nothing unless all m steps completed; after a breakdown
+ * the missing iterations follow and the finish is enqueued again.  lanczos_topk_async is the
  * stream-ordered form.
  */
 int lanczos_topk(const int64_t* csr_rowptr, const int32_t* csr_col, const void* csr_val,
@@ -228,8 +230,9 @@ size_t lanczos_topk_workspace_size_opt(int64_t n, int64_t nnz, int32_t K, int32_
  * opt may be NULL (defaults); report may be NULL.  With a caller workspace
  * the call allocates nothing; otherwise the workspace is allocated and freed
  * stream-ordered on `stream`.  Blocking like lanczos_topk: it waits for the
- * device after the m iterations (breakdown check, and the choice of SpMV
- * variant once the row order is known) and at the end (report).
+ * device at the end (report), once more for each round of iterations that
+ * breakdowns add, and where the choice of SpMV variant depends on the row
+ * order that the device picks, also after the setup.
  */
 int lanczos_topk_ex(const int64_t* csr_rowptr, const int32_t* csr_col, const void* csr_val,
                     int64_t n, int64_t nnz, int32_t K, int32_t m, int32_t precision,
@@ -253,8 +256,8 @@ int lanczos_topk_ex(const int64_t* csr_rowptr, const int32_t* csr_col, const voi
  *     kernel; timings are zero, and numerical outcomes (breakdown budget,
  *     non-finite values, Jacobi limit, invalid column indices) appear only in
  *     its status.
- *   - Without opt->workspace the workspace is allocated with hipMallocAsync
- *     and freed with hipFreeAsync on `stream`.
+ *   - Without opt->workspace the workspace is allocated stream-ordered, as in
+ *     lanczos_topk, and freed with hipFreeAsync on `stream`.
  *   - opt->profile must be 0.
  * Argument errors are returned before anything is enqueued.  Results equal
  * those of lanczos_topk_ex with the same options bit for bit.

@@ -499,7 +499,7 @@ hipError_t launch_report(const Plan&, const Bufs& b, void* d_report, int xcache_
 // return at once.  The row-order decision is made on the device, so both
 // SpMV variants that could apply are launched and each returns unless it
 // matches.  ws: the caller's workspace, or null to allocate one
-// stream-ordered (hipMallocAsync / hipFreeAsync on s).
+// stream-ordered (workspace_alloc / hipFreeAsync on s).
 int run_solve_async(Plan p, Csr a, const lz_options& o, int budget, hipStream_t s, double* out_vals,
                     double* out_vecs, void* d_report, void* ws) {
     int rc = LZ_OK;

@@ -29,7 +29,9 @@ constexpr int64_t GRAM_DOUBLES = GRAM_OUT + 2 * (64 * 65 / 2) + 64;
 // (n < 2^22): each tile's entries are stored in column order and each column
 // word holds (col << PACK_SLOTBITS) | (the entry's position in the tile's row
 // order).  PACK_GROUP (n <= 2^20): the same over groups of GROUP_TILES
-// consecutive tiles, with GROUP_SLOTBITS-bit positions in the group.
+// consecutive tiles, with GROUP_SLOTBITS-bit positions in the group.  Within a
+// tile or group the sorted entries are interleaved (sorted_place) so that a
+// lane's vector load holds entries that different gather instructions take.
 // PACK_SWEEP (large matrices, opt-in below a size threshold): the rows are
 // cut into sweep blocks and each block's entries are stored in column order
 // with their row inside the block in a separate array (see below).
