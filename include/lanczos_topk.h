@@ -206,9 +206,9 @@ const char* lz_status_string(int status);
  * 2 GiB between calls (inside a stream capture: from the device's default pool).
  * Blocking: reads nnz = rowptr[n] back from the device and returns after the
  * results are in out_vals/out_vecs.  The finish is enqueued behind the m
- * iterations and does nothing unless all m steps completed; after a breakdown
- * the missing iterations follow and the finish is enqueued again.  lanczos_topk_async is the
- * stream-ordered form.
+ * iterations and does nothing unless all m steps completed; after a breakdown,
+ * or where a second Gram-Schmidt pass became due, the missing iterations follow and the finish is
+ * enqueued again.  lanczos_topk_async is the stream-ordered form.
  */
 int lanczos_topk(const int64_t* csr_rowptr, const int32_t* csr_col, const void* csr_val,
                  int64_t n, int32_t K, int32_t m, int32_t precision, void* stream,

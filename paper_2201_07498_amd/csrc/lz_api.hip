@@ -350,7 +350,7 @@ int run_solve(Plan p, Csr a, const lz_options& o, hipStream_t s, double* out_val
             LZ_HIP(hipStreamSynchronize(s));
             p.xcache = want_xcache(p, hst->reordered != 0);
         }
-        p.fold = 1;
+        p.hold = !hc;    // (the slabs would stream for iterations that return at once)
         LZ_HIP(launch_init(p, b, s));
         if (o.profile) LZ_HIP(hipEventRecord(pev[1], s));
         for (int t = 0; t < m; ++t) LZ_HIP(launch_iteration(p, b, a, t + 1, o.reorth, s, iter_events(t)));
@@ -374,16 +374,19 @@ int run_solve(Plan p, Csr a, const lz_options& o, hipStream_t s, double* out_val
             if (!finished) launch_resume(b, s);
         }
         if (!finished) {
-            // Breakdowns and second passes consume iterations without advancing
-            // j: run more until m steps are done (bounded; each round advances j).
+            // Breakdowns consume iterations without advancing j: run more until
+            // m steps are done (bounded; each round advances j).  A held solve
+            // goes on with the iteration it stopped in.
             for (int round = 0; round < 2 * LZ_MAX_STEPS + 2; ++round) {
                 LZ_HIP(hipMemcpyAsync(hst, b.st, STATE_HEAD_BYTES, hipMemcpyDeviceToHost, s));
                 LZ_HIP(hipStreamSynchronize(s));
                 if (hst->status != 0 || hst->j >= m) break;
-                const int extra = m - hst->j;
-                for (int t = 0; t < extra; ++t)
-                    LZ_HIP(launch_iteration(p, b, a, m, o.reorth, s, iter_events(launched + t)));
-                launched += extra;
+                if (p.hold && hst->remeasure == 2) {
+                    launched = held_iteration(*hst);
+                    p.hold = 0;
+                }
+                for (int left = m - hst->j; left > 0; --left, ++launched)
+                    LZ_HIP(launch_iteration(p, b, a, std::min(launched + 1, m), o.reorth, s, iter_events(launched)));
                 if (o.profile) LZ_HIP(hipEventRecord(pev[2], s));
             }
             if (hst->status == 0 && hst->j < m) {

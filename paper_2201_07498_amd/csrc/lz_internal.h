@@ -93,7 +93,7 @@ struct State {
     int32_t n_items, n_long, sweeps;
     int32_t arith;        // LZ_ARITH_FP32: dots, norms, reorthogonalisation and SpMV epilogue in FP32
     int32_t remeasure;    // 1: this step's second coefficients are re-measured (two-pass modes, see k_orth_dot);
-                          // 2: measured by the store kernel, the next iteration stores
+                          // 2: a second pass is due and the solve is held for it (see Plan.hold)
     uint32_t ticket[TK_COUNT];
     uint64_t seed;
     double u_s;           // unit roundoff of the stored basis (selective reorthogonalisation)
@@ -139,7 +139,8 @@ struct Plan {
                                 // row order is known) or XC_GATED (both variants launched; each returns
                                 // unless the device's row-order decision selects it)
     int32_t strict_m = 0;       // STRICT_*: what the finish does if fewer than m steps completed
-    int32_t fold = 0;           // the store kernel runs the second pass when it is due (more iterations can follow)
+    int32_t hold = 0;           // no second-pass launches: where one is due the store kernel holds the solve, and the
+                                // host enqueues the step again (held_iteration) with launches of their own
     int32_t fff = 0;            // all-FP32 arithmetic (FP32 storage only): float instantiations
     int32_t g_slab = 0;         // grid of the per-slab launches of a host-resident matrix
     int32_t sweep = 0;          // reserve and build the sweep-block copy if the matrix is relabelled
@@ -249,6 +250,9 @@ hipError_t launch_setup(const Plan& p, const Bufs& b, const Csr& a, uint64_t see
 hipError_t launch_init(const Plan& p, const Bufs& b, hipStream_t s);
 // Clears LZ_PENDING from the status (see STRICT_PENDING).
 void launch_resume(const Bufs& b, hipStream_t s);
+// Index of the iteration that a held solve stopped in: every earlier one took
+// a step or was a breakdown.
+inline int held_iteration(const State& st) { return st.j + st.restarts; }
 // One Lanczos iteration (SpMV or restart draw, reorthogonalisation, store);
 // `reorth` is the solve's LZ_REORTH_* mode (it selects the kernels).
 // `ncols_bound` >= j+1 for every j the iteration can see.

@@ -9,13 +9,16 @@
 //   k_orth_upd_store v_{j+1} = w - V (c + c2) in the basis precision;
 //                    beta_{j+1}; the new column of G
 // With one pass or none, a restart vector (always orthogonalised twice) takes
-// the classical second pass instead: w' = w - V c and c2 = V^T w' between the
-// two.  The two-pass modes take it too when the first pass cancelled strongly
-// (see k_orth_dot).  It is rare, so calls that can enqueue further iterations
-// fold it into k_orth_upd_store: that kernel then measures instead of storing,
-// and the next iteration, whose other kernels return at once, stores.  The
-// stream-ordered call, whose iterations are counted beforehand, launches it as
-// k_orth_upd_dot at every step (it returns at once: 4.5 us a step).
+// the classical second pass instead (k_orth_upd_dot): w' = w - V c and c2 =
+// V^T w' between the two.  The two-pass modes take it too when the first pass
+// cancelled strongly (see k_orth_dot).  It is rare, and a launch that returns
+// at once costs 4.5 us a step.  So calls that can enqueue further iterations
+// leave it out (Plan.hold): where it is due the store kernel marks the solve as
+// held, everything behind returns at once, and the host enqueues the same
+// iteration again, from there on with the second pass.  The stream-ordered
+// call launches it at every step.  A held iteration is repeated under its own
+// index: the kernels' column bucket, and with it the order of their sums,
+// follows the index, so both kinds of call return the same bits.
 // Global sums are per-workgroup partials that the last workgroup to finish
 // adds in a fixed order, so results do not depend on scheduling.  The step
 // index and every coefficient stay in device memory.
@@ -435,14 +438,22 @@ template <int NC, class A> struct OrthShared {
     int last, accept;
 };
 
-// w' = w - V c (stored in the working precision), then c2 = V^T w' and ||w'||^2.
-// Returns true in the last workgroup, which has written c2.
+// The second pass: w' = w - V c (stored in the working precision), then c2 =
+// V^T w' and ||w'||^2.
 template <int P, int NC, class A>
-__device__ __forceinline__ bool orth_measure(State* st, const typename Tr<P>::V* __restrict__ Vb,
-                                             typename Tr<P>::W* __restrict__ w, int64_t ld, int nc, double* part,
-                                             double* part2, OrthShared<NC, A>& sh) {
+__global__ __launch_bounds__(OBLOCK) void k_orth_upd_dot(State* st, const typename Tr<P>::V* __restrict__ Vb,
+                                                        typename Tr<P>::W* __restrict__ w, int64_t ld,
+                                                        double* part, double* part2) {
     using CT = typename Ch<P>::T;
     constexpr int R = Ch<P>::R, CS = Split<P, NC>::CS, NCL = Split<P, NC>::NCL, GPW = 64 / CS;
+    __shared__ OrthShared<NC, A> sh;
+    const int j = st->j;
+    if (st->status != 0 || j >= st->m || !upd_dot_active(st)) return;
+    const int nc = j + 1;
+    if (nc > NC) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) st->status = -1;
+        return;
+    }
     for (int k = threadIdx.x; k < NC; k += OBLOCK) sh.coef[k] = k < nc ? (A)st->c[k] * (A)st->scale[k] : A(0);
     __syncthreads();
     const int ln = threadIdx.x & 63, cs = ln % CS;
@@ -487,29 +498,14 @@ __device__ __forceinline__ bool orth_measure(State* st, const typename Tr<P>::V*
         }
     }
     publish_split<NC, CS, NCL>(acc, nrm, nc, part, part2, sh.red, sh.redn);
-    if (!last_block(&st->ticket[TK_UPD], gridDim.x, &sh.last)) return false;
-    const A wn = reduce_columns<NC>(part, part2, gridDim.x, nc, st->scale, st->c2, sh.lout, sh.sred, sh.tot, [] {});
-    if (threadIdx.x == 0) {
-        st->wnorm2 = (double)wn;
-        st->second = 1;
+    if (last_block(&st->ticket[TK_UPD], gridDim.x, &sh.last)) {
+        const A wn =
+            reduce_columns<NC>(part, part2, gridDim.x, nc, st->scale, st->c2, sh.lout, sh.sred, sh.tot, [] {});
+        if (threadIdx.x == 0) {
+            st->wnorm2 = (double)wn;
+            st->second = 1;
+        }
     }
-    return true;
-}
-
-// The second pass as a kernel of its own (stream-ordered calls).
-template <int P, int NC, class A>
-__global__ __launch_bounds__(OBLOCK) void k_orth_upd_dot(State* st, const typename Tr<P>::V* __restrict__ Vb,
-                                                        typename Tr<P>::W* __restrict__ w, int64_t ld,
-                                                        double* part, double* part2) {
-    __shared__ OrthShared<NC, A> sh;
-    const int j = st->j;
-    if (st->status != 0 || j >= st->m || !upd_dot_active(st)) return;
-    const int nc = j + 1;
-    if (nc > NC) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) st->status = -1;
-        return;
-    }
-    orth_measure<P, NC, A>(st, Vb, w, ld, nc, part, part2, sh);
 }
 
 // v_{j+1} = w - V c2 (c2 holds the total coefficients) stored in the basis
@@ -518,9 +514,9 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_dot(State* st, const typena
 // the working vector, starts a restart).  In the
 // two-pass modes the same pass takes the dots of the stored column with the
 // basis: the new row and column of the Gram matrix.
-// With FOLD the second pass runs here when it is due: this launch then measures
-// (remeasure becomes 2) and the next iteration's launch stores.
-template <int P, int NC, bool GRAM, class A, bool FOLD>
+// With HOLD no second pass ran before: where one is due, this launch only marks
+// the solve as held (a workgroup that reads the mark already set returns too).
+template <int P, int NC, bool GRAM, class A, bool HOLD>
 __global__ __launch_bounds__(OBLOCK) void k_orth_upd_store(State* st, typename Tr<P>::V* __restrict__ Vb,
                                                           typename Tr<P>::W* __restrict__ w, int64_t ld,
                                                           double* part, double* part2, double* gm) {
@@ -543,9 +539,9 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_store(State* st, typename T
         if (blockIdx.x == 0 && threadIdx.x == 0) st->status = -1;
         return;
     }
-    if constexpr (FOLD) {
-        if (GRAM ? remeasure == 1 : mode_now == MODE_RESTART && remeasure != 2) {
-            if (orth_measure<P, NC, A>(st, Vb, w, ld, nc, part, part2, sh) && threadIdx.x == 0) st->remeasure = 2;
+    if constexpr (HOLD) {
+        if (GRAM ? remeasure != 0 : mode_now == MODE_RESTART) {
+            if (blockIdx.x == 0 && threadIdx.x == 0) st->remeasure = 2;
             return;
         }
     }
@@ -666,7 +662,7 @@ __global__ __launch_bounds__(OBLOCK) void k_orth_upd_store(State* st, typename T
             }
             sh.accept = accept;
             sh.sn[0] = (A)sn;
-            if (FOLD) st->remeasure = 0;
+            st->remeasure = 0;
         }
         if constexpr (GRAM) {
             __syncthreads();
@@ -707,22 +703,22 @@ static hipError_t iteration_pa(const Plan& p, const Bufs& b, const Csr& a, int n
     // dots are no more precise than the storage (see k_orth_dot).
     const bool remeasure_possible = P == 0 || sizeof(A) == 4;
     const bool measure = reorth < 2 || remeasure_possible;      // the second pass can become due
-    const bool fold = measure && p.fold;
-#define LZ_ORTH_STORE(NCV, GRAMV, FOLDV)                                                                   \
-    hipLaunchKernelGGL((k_orth_upd_store<P, NCV, GRAMV, A, FOLDV>), dim3(p.g_orth), dim3(OBLOCK), 0, s, b.st, V, w, \
+    const bool hold = measure && p.hold;
+#define LZ_ORTH_STORE(NCV, GRAMV, HOLDV)                                                                   \
+    hipLaunchKernelGGL((k_orth_upd_store<P, NCV, GRAMV, A, HOLDV>), dim3(p.g_orth), dim3(OBLOCK), 0, s, b.st, V, w, \
                        p.ld, b.part, b.part2, b.gm)
 #define LZ_ORTH_CASE(NCV)                                                                                  \
     case NCV:                                                                                              \
         hipLaunchKernelGGL((k_orth_dot<P, NCV, A>), dim3(p.g_orth), dim3(OBLOCK), 0, s, b.st, V, w, p.ld,      \
                            b.part, b.part2, b.gm);                                                         \
-        if (measure && !fold)                                                                              \
+        if (measure && !hold)                                                                              \
             hipLaunchKernelGGL((k_orth_upd_dot<P, NCV, A>), dim3(p.g_orth), dim3(OBLOCK), 0, s, b.st, V, w,    \
                                p.ld, b.part, b.part2);                                                     \
-        if (reorth >= 2 && fold)                                                                           \
+        if (reorth >= 2 && hold)                                                                           \
             LZ_ORTH_STORE(NCV, true, true);                                                                \
         else if (reorth >= 2)                                                                              \
             LZ_ORTH_STORE(NCV, true, false);                                                               \
-        else if (fold)                                                                                     \
+        else if (hold)                                                                                     \
             LZ_ORTH_STORE(NCV, false, true);                                                               \
         else                                                                                               \
             LZ_ORTH_STORE(NCV, false, false);                                                              \

@@ -152,6 +152,7 @@ struct Slot {
     double* dvecs = nullptr;
     hipGraphExec_t gexec = nullptr;
     int rounds = 0;
+    int launched = 0;             // iterations of the request enqueued so far
 };
 
 }  // namespace
@@ -234,6 +235,7 @@ hipError_t Server::launch_lanczos(Slot& s) {
 bool Server::admit(Slot& s, Req* q) {
     s.req = q;
     s.rounds = 0;
+    s.launched = q->plan.m;
     char* base = arena.base() + s.off;
     const Layout& l = q->lay;
     const lz_request& r = q->r;
@@ -291,15 +293,19 @@ void Server::complete(Slot& s, int status) {
 
 void Server::advance(Slot& s) {
     Req* q = s.req;
-    const Plan& p = q->plan;
+    Plan& p = q->plan;
     const State* st = s.hstate;
     if (s.phase == LANCZOS) {
         if (st->status != 0) return complete(s, st->status);
-        if (st->j < p.m) {              // breakdowns consumed iterations: run more
+        if (st->j < p.m) {              // breakdowns consumed iterations, or the solve is held: run more
             if (++s.rounds > MAX_RESTART_ROUNDS) return complete(s, LZ_ERR_BREAKDOWN);
+            if (p.hold && st->remeasure == 2) {
+                s.launched = held_iteration(*st);
+                p.hold = 0;
+            }
             hipError_t e = hipSuccess;
-            for (int t = st->j; t < p.m && e == hipSuccess; ++t)
-                e = launch_iteration(p, s.bufs, s.csr, p.m, q->r.reorth, s.stream);
+            for (int left = p.m - st->j; left > 0 && e == hipSuccess; --left, ++s.launched)
+                e = launch_iteration(p, s.bufs, s.csr, std::min(s.launched + 1, p.m), q->r.reorth, s.stream);
             if (e == hipSuccess) e = hipMemcpyAsync(s.hstate, s.bufs.st, STATE_REPORT_BYTES, hipMemcpyDeviceToHost, s.stream);
             if (e == hipSuccess) e = hipEventRecord(s.ev_phase, s.stream);
             if (e != hipSuccess) complete(s, LZ_ERR_HIP);
@@ -436,7 +442,7 @@ int lz_server_submit(lz_server* srv, const lz_request* req, uint64_t* ticket) {
     auto q = std::make_unique<Req>();
     q->r = *req;
     q->plan = make_plan(req->n, req->nnz, req->K, req->m, req->precision);
-    q->plan.fold = 1;
+    q->plan.hold = 1;
     // The SpMV variant is fixed when the graph is captured: take the device's
     // relabelling decision on the host, from the caller's row pointer.
     if (!q->plan.sweep && want_xcache(q->plan, true))
