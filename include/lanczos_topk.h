@@ -396,7 +396,9 @@ typedef struct lz_request {
     int32_t K, m, precision, reorth;   /* reorth: LZ_REORTH_* */
     uint64_t seed;
     double* out_vals;        /* host double[K], written on completion */
-    double* out_vecs;        /* host double[n*K] column-major, or NULL */
+    double* out_vecs;        /* host double[n*K] column-major, written on
+                                completion (untouched unless the status is
+                                LZ_OK); or NULL */
     double* out_resid;       /* host double[K]: relative residual of each
                                 returned pair (Top-K order, as out_vals),
                                 written on completion; or NULL */

@@ -13,10 +13,14 @@
 // slot's thread advances it through a small state machine, waiting on events:
 //   ADMIT:   H2D of the CSR, setup, start vector, m iterations, then Jacobi,
 //            selection, Ritz vectors, report (these return at once if
-//            breakdowns consumed some iterations), D2H of results
+//            breakdowns consumed some iterations), D2H of values and state
 //   LANCZOS: only then: more iterations until the m steps are done, and the
 //            results again
-//   FINISH:  results to the caller, arena block and slot released.
+//   FINISH:  the status is known: D2H of the vectors if it is LZ_OK and the
+//            caller wants them (a failed request's buffers stay untouched, and
+//            the call, which waits for its copy where the buffer is pageable,
+//            does not wait for the solve too)
+//   VECTORS: results to the caller, arena block and slot released.
 // Launch shapes depend only on the request, so a request's results are the
 // same alone and in any mix.
 #include <hip/hip_runtime.h>
@@ -136,11 +140,11 @@ struct Req {
     int bypassed = 0;
 };
 
-enum Phase { IDLE = 0, LANCZOS = 1, FINISH = 2 };
+enum Phase { IDLE = 0, LANCZOS = 1, FINISH = 2, VECTORS = 3 };
 
 struct Slot {
     hipStream_t stream = nullptr;
-    hipEvent_t ev_start = nullptr, ev_phase = nullptr;
+    hipEvent_t ev_start = nullptr, ev_phase = nullptr, ev_vecs = nullptr;
     State* hstate = nullptr;      // pinned copy of the device state
     double* hvals = nullptr;      // pinned eigenvalues
     Req* req = nullptr;
@@ -192,16 +196,13 @@ struct Server {
     hipError_t launch_results(Slot& s, int strict);
 };
 
-// The finish and the copies of its results, then the phase event.
+// The finish and the copies of its values and state, then the phase event.
 hipError_t Server::launch_results(Slot& s, int strict) {
-    Req* q = s.req;
-    Plan p = q->plan;
+    Plan p = s.req->plan;
     p.strict_m = strict;
     hipError_t e = launch_finish(p, s.bufs, s.csr, s.dvals, s.dvecs, 1, s.stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(s.hvals, s.dvals, sizeof(double) * p.K, hipMemcpyDeviceToHost, s.stream);
-    if (e == hipSuccess && q->r.out_vecs)
-        e = hipMemcpyAsync(q->r.out_vecs, s.dvecs, sizeof(double) * p.n * p.K, hipMemcpyDeviceToHost, s.stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(s.hstate, s.bufs.st, STATE_REPORT_BYTES, hipMemcpyDeviceToHost, s.stream);
     if (e == hipSuccess) e = hipEventRecord(s.ev_phase, s.stream);
@@ -320,7 +321,15 @@ void Server::advance(Slot& s) {
         s.phase = LANCZOS;
         return advance(s);
     }
-    if (s.phase == FINISH) complete(s, st->status);
+    if (s.phase == FINISH && st->status == LZ_OK && q->r.out_vecs) {
+        hipError_t e =
+            hipMemcpyAsync(q->r.out_vecs, s.dvecs, sizeof(double) * p.n * p.K, hipMemcpyDeviceToHost, s.stream);
+        if (e == hipSuccess) e = hipEventRecord(s.ev_vecs, s.stream);
+        if (e != hipSuccess) return complete(s, LZ_ERR_HIP);
+        s.phase = VECTORS;
+        return;
+    }
+    complete(s, st->status);
 }
 
 // The first queued request (within the backfill window) whose footprint
@@ -342,8 +351,8 @@ Req* Server::pick(Slot& s) {
 }
 
 // One worker thread per slot: it admits a request when its slot is free,
-// sleeps on the slot's phase event (created with blocking sync) while the
-// device works, and advances the slot when the event has completed.  The
+// sleeps on the phase's event (created with blocking sync) while the device
+// works, and advances the slot when the event has completed.  The
 // queue, the arena and the counters are shared under mu; every thread
 // enqueues its own slot's copies and launches, so the host-side cost of
 // capture and launch is spread over the threads.
@@ -367,7 +376,7 @@ void Server::run_slot(Slot& s) {
             add_enqueue_time(t0);
             continue;
         }
-        const hipError_t e = hipEventSynchronize(s.ev_phase);
+        const hipError_t e = hipEventSynchronize(s.phase == VECTORS ? s.ev_vecs : s.ev_phase);
         const auto t0 = std::chrono::steady_clock::now();
         if (e != hipSuccess)
             complete(s, LZ_ERR_HIP);
@@ -415,6 +424,7 @@ int lz_server_create(int device, size_t hbm_budget_bytes, int32_t max_slots, int
         if (hipStreamCreateWithFlags(&sl.stream, hipStreamNonBlocking) != hipSuccess ||
             hipEventCreate(&sl.ev_start) != hipSuccess ||
             hipEventCreateWithFlags(&sl.ev_phase, hipEventBlockingSync) != hipSuccess ||
+            hipEventCreateWithFlags(&sl.ev_vecs, hipEventBlockingSync) != hipSuccess ||
             hipHostMalloc((void**)&sl.hstate, sizeof(State), hipHostMallocDefault) != hipSuccess ||
             hipHostMalloc((void**)&sl.hvals, sizeof(double) * MMAX, hipHostMallocDefault) != hipSuccess) {
             lz_server_destroy((lz_server*)s);
@@ -518,6 +528,7 @@ int lz_server_destroy(lz_server* srv) {
         if (sl.stream) (void)hipStreamDestroy(sl.stream);
         if (sl.ev_start) (void)hipEventDestroy(sl.ev_start);
         if (sl.ev_phase) (void)hipEventDestroy(sl.ev_phase);
+        if (sl.ev_vecs) (void)hipEventDestroy(sl.ev_vecs);
         if (sl.hstate) (void)hipHostFree(sl.hstate);
         if (sl.hvals) (void)hipHostFree(sl.hvals);
     }
