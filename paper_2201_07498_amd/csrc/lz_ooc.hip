@@ -56,7 +56,7 @@ hipError_t ooc_pull(const Ooc& o, int i, int64_t e0, int64_t e1) {
                            o.dval + (size_t)e0 * o.vb, o.sval[i], vb);
         return hipGetLastError();
     }
-    // Pinned memory that the device cannot address.
+    // Pinned memory that the device cannot address, or not all of it.
     hipError_t e = hipMemcpyAsync(o.scol[i], o.hcol + e0, (size_t)cb, hipMemcpyHostToDevice, o.cs);
     if (e == hipSuccess)
         e = hipMemcpyAsync(o.sval[i], o.hval + (size_t)e0 * o.vb, (size_t)vb, hipMemcpyHostToDevice, o.cs);
@@ -106,6 +106,17 @@ hipError_t stream_set(StreamSet** out) {
     return hipSuccess;
 }
 }  // namespace
+
+// True if a kernel may read [h, h + bytes) of host memory at its host address:
+// the device addresses it there, and one pinned allocation holds all of it.
+// (The runtime's copies check their range, a kernel would fault.)
+static bool device_reads(const void* h, size_t bytes) {
+    void *d = nullptr, *base = nullptr;
+    size_t size = 0;
+    return hipHostGetDevicePointer(&d, (void*)h, 0) == hipSuccess && d == h &&
+           hipMemGetAddressRange((hipDeviceptr_t*)&base, &size, (hipDeviceptr_t)h) == hipSuccess && h >= base &&
+           bytes <= size && (size_t)((const char*)h - (const char*)base) <= size - bytes;
+}
 
 hipError_t ooc_begin(Ooc& o, hipStream_t* s) {
     StreamSet* S = nullptr;
@@ -194,12 +205,9 @@ hipError_t ooc_prepare(Plan& p, const Bufs& b, Ooc& o, int64_t slab_nnz, int64_t
     o.dcol = nullptr;
     o.dval = nullptr;
     if (o.nres < ns) {
-        void *dc = nullptr, *dv = nullptr;
-        if (hipHostGetDevicePointer(&dc, (void*)o.hcol, 0) == hipSuccess &&
-            hipHostGetDevicePointer(&dv, (void*)o.hval, 0) == hipSuccess && dc == (const void*)o.hcol &&
-            dv == (const void*)o.hval) {
-            o.dcol = (const int32_t*)dc;
-            o.dval = (const char*)dv;
+        if (device_reads(o.hcol, (size_t)p.nnz * 4) && device_reads(o.hval, (size_t)p.nnz * o.vb)) {
+            o.dcol = o.hcol;
+            o.dval = o.hval;
         } else {
             (void)hipGetLastError();
         }

@@ -1,0 +1,70 @@
+"""Host code of the library on a HIP runtime without a device (fake_hip.c):
+which copies, allocations and waits its entry points make.  Each test runs in a
+process of its own (runs without a GPU)."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, os, sys
+sys.path.insert(0, {root!r})
+import numpy as np
+hip = ctypes.CDLL({fake!r}, mode=ctypes.RTLD_GLOBAL)
+import paper_2201_07498_amd as lz
+L = lz.lib()
+for f in ("fake_used", "fake_idle"): getattr(hip, f).restype = ctypes.c_size_t
+hip.fake_count.restype = ctypes.c_long
+hip.fake_capacity.argtypes = [ctypes.c_size_t]
+hip.fake_pin.argtypes = [ctypes.c_void_p, ctypes.c_size_t]
+MB = 1 << 20
+D = ctypes.c_void_p(4096)                  # device addresses are never followed
+def stream(device=0): return ctypes.c_void_p((77 << 8) + 1 + device)
+def spmv(n=1000, nnz=5000, s=None): return L.lz_spmv(D, D, D, n, nnz, 0, D, D, s)
+def solve_async(n, nnz, s=None, opt=None):
+    return L.lanczos_topk_async(D, D, D, n, nnz, 2, 8, 0, s, D, D, opt, None)
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("fake") / "libfakehip.so")
+    subprocess.run(["gcc", "-O1", "-Wall", "-shared", "-fPIC", "-o", out, os.path.join(HERE, "fake_hip.c"),
+                    "-lpthread"], check=True)
+    return out
+
+
+def run(fake, body):
+    code = PRELUDE.format(root=ROOT, fake=fake) + body
+    p = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
+    assert p.returncode == 0, p.stdout + p.stderr
+    return p.stdout
+
+
+HOST_SOLVE = """
+n, nnz = 2, 8 * 1024 - 2                   # eight whole tiles
+rp = np.array([0, nnz // 2, nnz], np.int64)
+col, val = np.zeros(nnz, np.int32), np.zeros(nnz, np.float64)
+short_col, short_val = {short}
+hip.fake_pin(col.ctypes.data, col.nbytes - short_col)
+hip.fake_pin(val.ctypes.data, val.nbytes - short_val)
+rc = L.lanczos_topk_host(rp.ctypes.data, col.ctypes.data, val.ctypes.data, n, 1, 2, 0, 2048, 0, None, D, D,
+                         None, None)
+print(rc, hip.fake_count(2))
+"""
+
+
+@pytest.mark.parametrize("short", [(0, 0), (4, 0), (0, 8), (8192, 8192)])
+def test_host_arrays_past_their_pinned_allocation_go_through_the_runtime(fake, short):
+    # The copy kernel reads the caller's arrays at their host addresses, so it may
+    # only be used where they lie inside their pinned allocations as a whole; the
+    # runtime's copies check their range and refuse one that does not.
+    rc, copies = map(int, run(fake, HOST_SOLVE.format(short=short)).split())
+    if short == (0, 0):
+        assert copies == 0
+    else:
+        assert copies > 0 and rc == -3     # LZ_ERR_HIP
