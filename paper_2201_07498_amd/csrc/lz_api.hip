@@ -170,12 +170,14 @@ constexpr size_t POOL_KEEP_BYTES = (size_t)2 << 30;
 constexpr size_t POOL_BLOCK_MAX = (size_t)1 << 30;
 constexpr int POOL_MAX_DEVICES = 64;
 
-static hipMemPool_t workspace_pool() {
+// Pool of the device that the stream belongs to (the current one for the
+// default stream); null if it has none.
+static hipMemPool_t workspace_pool(hipStream_t s) {
     static std::mutex mu;
     static hipMemPool_t pools[POOL_MAX_DEVICES] = {};
     static bool tried[POOL_MAX_DEVICES] = {};
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= POOL_MAX_DEVICES) return nullptr;
+    const int dev = hipGetStreamDeviceId(s);
+    if (dev < 0 || dev >= POOL_MAX_DEVICES) return nullptr;
     std::lock_guard<std::mutex> lk(mu);
     if (!tried[dev]) {
         tried[dev] = true;
@@ -203,7 +205,7 @@ static hipError_t workspace_alloc(void** p, size_t bytes, hipStream_t s) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (bytes <= POOL_BLOCK_MAX && hipStreamIsCapturing(s, &cap) == hipSuccess &&
         cap == hipStreamCaptureStatusNone) {
-        const hipMemPool_t pool = workspace_pool();
+        const hipMemPool_t pool = workspace_pool(s);
         if (pool) {
             if (hipMallocFromPoolAsync(p, bytes, pool, s) == hipSuccess) return hipSuccess;
             (void)hipGetLastError();

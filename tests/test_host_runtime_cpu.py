@@ -68,3 +68,13 @@ def test_host_arrays_past_their_pinned_allocation_go_through_the_runtime(fake, s
         assert copies == 0
     else:
         assert copies > 0 and rc == -3     # LZ_ERR_HIP
+
+
+def test_workspace_comes_from_the_device_of_the_stream(fake):
+    # The current device is 0, the streams belong to devices 0, 1 and (null) 0.
+    out = run(fake, """
+for s in (stream(0), stream(1), None):
+    assert spmv(s=s) == 0 and solve_async(4000, 20000, s) == 0
+print(hip.fake_count(4))
+""")
+    assert int(out) == 0
