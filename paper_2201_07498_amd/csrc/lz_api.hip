@@ -3,7 +3,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <mutex>
 #include <utility>
 #include <vector>
 
@@ -155,64 +154,6 @@ Bufs resolve(const Plan& p, void* base) {
         b.swseg = (uint32_t*)((char*)b.swvin + off[1]);
     }
     return b;
-}
-
-// Workspaces of calls that bring none.  The device's default memory pool gives
-// every block back to the driver when the stream is next waited for, so each
-// call paid for mapping and unmapping it: 70-420 us per call for 40 MB to 1 GB
-// in a process with little memory, several milliseconds in one holding tens of
-// GB.  Blocks up to POOL_BLOCK_MAX come from a pool of the library's own (one
-// per device, created at first use) that keeps at most POOL_KEEP_BYTES of freed
-// memory and gives the rest back; 35 us per call whatever the size.  Larger
-// blocks, and allocations inside a stream capture (which become graph nodes),
-// use the default pool.  The runtime orders reuse between streams and threads.
-constexpr size_t POOL_KEEP_BYTES = (size_t)2 << 30;
-constexpr size_t POOL_BLOCK_MAX = (size_t)1 << 30;
-constexpr int POOL_MAX_DEVICES = 64;
-
-// Pool of the device that the stream belongs to (the current one for the
-// default stream); null if it has none.
-static hipMemPool_t workspace_pool(hipStream_t s) {
-    static std::mutex mu;
-    static hipMemPool_t pools[POOL_MAX_DEVICES] = {};
-    static bool tried[POOL_MAX_DEVICES] = {};
-    const int dev = hipGetStreamDeviceId(s);
-    if (dev < 0 || dev >= POOL_MAX_DEVICES) return nullptr;
-    std::lock_guard<std::mutex> lk(mu);
-    if (!tried[dev]) {
-        tried[dev] = true;
-        hipMemPoolProps props;
-        std::memset(&props, 0, sizeof(props));
-        props.allocType = hipMemAllocationTypePinned;
-        props.location.type = hipMemLocationTypeDevice;
-        props.location.id = dev;
-        hipMemPool_t pool = nullptr;
-        uint64_t keep = POOL_KEEP_BYTES;
-        if (hipMemPoolCreate(&pool, &props) != hipSuccess) {
-            (void)hipGetLastError();
-        } else if (hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
-            (void)hipGetLastError();
-            (void)hipMemPoolDestroy(pool);
-        } else {
-            pools[dev] = pool;
-        }
-    }
-    return pools[dev];
-}
-
-// Stream-ordered allocation on s; freed with hipFreeAsync.
-static hipError_t workspace_alloc(void** p, size_t bytes, hipStream_t s) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (bytes <= POOL_BLOCK_MAX && hipStreamIsCapturing(s, &cap) == hipSuccess &&
-        cap == hipStreamCaptureStatusNone) {
-        const hipMemPool_t pool = workspace_pool(s);
-        if (pool) {
-            if (hipMallocFromPoolAsync(p, bytes, pool, s) == hipSuccess) return hipSuccess;
-            (void)hipGetLastError();
-            (void)hipMemPoolTrimTo(pool, 0);      // make room for the default pool
-        }
-    }
-    return hipMallocAsync(p, bytes, s);
 }
 
 // Pinned host copy of the state (one per host thread, kept for the process):
@@ -809,7 +750,7 @@ int lz_ortho_loss(const void* X, int64_t ldx, int64_t n, int32_t c, int32_t prec
     hst->j = c;
     hst->m = c;
     for (int k = 0; k < c; ++k) hst->scale[k] = 1.0;
-    if (hipMalloc((void**)&d, so + (size_t)GRAM_DOUBLES * 8) != hipSuccess) {
+    if (device_alloc((void**)&d, so + (size_t)GRAM_DOUBLES * 8) != hipSuccess) {
         delete hst;
         return LZ_ERR_OUT_OF_MEMORY;
     }

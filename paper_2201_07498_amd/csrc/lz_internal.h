@@ -236,6 +236,11 @@ struct Bufs {
 };
 Bufs resolve(const Plan& p, void* base);
 
+// Memory of calls that bring none (lz_memory.hip): stream-ordered on s, freed
+// with hipFreeAsync; or hipMalloc on the current device.
+hipError_t workspace_alloc(void** p, size_t bytes, hipStream_t s);
+hipError_t device_alloc(void** p, size_t bytes);
+
 // Matrix pointers.
 struct Csr {
     const int64_t* rowptr;

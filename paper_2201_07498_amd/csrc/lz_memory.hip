@@ -1,0 +1,95 @@
+// Device and pinned memory of calls that bring none.
+//
+// The device's default memory pool gives every block back to the driver when
+// the stream is next waited for, so each call paid for mapping and unmapping
+// it: 70-420 us per call for 40 MB to 1 GB in a process with little memory,
+// several milliseconds in one holding tens of GB.  Blocks up to POOL_BLOCK_MAX
+// come from a pool of the library's own (one per device, created at first use)
+// that keeps at most POOL_KEEP_BYTES of freed memory and gives the rest back;
+// 35 us per call whatever the size.  Larger blocks, and allocations inside a
+// stream capture (which become graph nodes), use the default pool.  The runtime
+// orders reuse between streams and threads.  Before an allocation of the
+// library fails, the pool's idle memory is given back and it is tried again.
+#include <cstring>
+#include <mutex>
+
+#include "lz_internal.h"
+
+namespace lz {
+namespace {
+
+constexpr size_t POOL_KEEP_BYTES = (size_t)2 << 30;
+constexpr size_t POOL_BLOCK_MAX = (size_t)1 << 30;
+constexpr int POOL_MAX_DEVICES = 64;
+
+std::mutex pool_mu;
+hipMemPool_t pools[POOL_MAX_DEVICES] = {};
+bool tried[POOL_MAX_DEVICES] = {};
+
+// Pool of a device; null if it has none.
+hipMemPool_t workspace_pool(int dev) {
+    if (dev < 0 || dev >= POOL_MAX_DEVICES) return nullptr;
+    std::lock_guard<std::mutex> lk(pool_mu);
+    if (!tried[dev]) {
+        tried[dev] = true;
+        hipMemPoolProps props;
+        std::memset(&props, 0, sizeof(props));
+        props.allocType = hipMemAllocationTypePinned;
+        props.location.type = hipMemLocationTypeDevice;
+        props.location.id = dev;
+        hipMemPool_t pool = nullptr;
+        uint64_t keep = POOL_KEEP_BYTES;
+        if (hipMemPoolCreate(&pool, &props) != hipSuccess) {
+            (void)hipGetLastError();
+        } else if (hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep) != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipMemPoolDestroy(pool);
+        } else {
+            pools[dev] = pool;
+        }
+    }
+    return pools[dev];
+}
+
+// Gives the idle memory of a device's pool back to the driver; false if the
+// device has no pool.
+bool give_back(int dev) {
+    if (dev < 0 || dev >= POOL_MAX_DEVICES) return false;
+    std::lock_guard<std::mutex> lk(pool_mu);
+    return pools[dev] && hipMemPoolTrimTo(pools[dev], 0) == hipSuccess;
+}
+
+}  // namespace
+
+// An allocation that failed for good: reported by its status alone, not by the
+// next launch's error check too.
+static hipError_t settle(hipError_t e) {
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
+// Stream-ordered allocation on s; freed with hipFreeAsync.
+hipError_t workspace_alloc(void** p, size_t bytes, hipStream_t s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
+        return settle(hipMallocAsync(p, bytes, s));
+    const int dev = hipGetStreamDeviceId(s);
+    const hipMemPool_t pool = bytes <= POOL_BLOCK_MAX ? workspace_pool(dev) : nullptr;
+    if ((pool ? hipMallocFromPoolAsync(p, bytes, pool, s) : hipMallocAsync(p, bytes, s)) == hipSuccess)
+        return hipSuccess;
+    (void)hipGetLastError();
+    // Blocks that the stream has yet to free are idle once it has been waited for.
+    (void)hipStreamSynchronize(s);
+    (void)give_back(dev);
+    return settle(hipMallocAsync(p, bytes, s));
+}
+
+// hipMalloc on the current device.
+hipError_t device_alloc(void** p, size_t bytes) {
+    const hipError_t e = settle(hipMalloc(p, bytes));
+    int dev = -1;
+    if (e == hipSuccess || hipGetDevice(&dev) != hipSuccess || !give_back(dev)) return e;
+    return settle(hipMalloc(p, bytes));
+}
+
+}  // namespace lz

@@ -194,8 +194,8 @@ hipError_t ooc_prepare(Plan& p, const Bufs& b, Ooc& o, int64_t slab_nnz, int64_t
     // Resident slabs: one copy, on the solve's stream.
     const int64_t eres = o.eb[o.nres];
     if (eres > 0) {
-        if ((e = hipMalloc((void**)&o.rcol, (size_t)eres * 4)) != hipSuccess) return e;
-        if ((e = hipMalloc((void**)&o.rval, (size_t)eres * o.vb)) != hipSuccess) return e;
+        if ((e = device_alloc((void**)&o.rcol, (size_t)eres * 4)) != hipSuccess) return e;
+        if ((e = device_alloc((void**)&o.rval, (size_t)eres * o.vb)) != hipSuccess) return e;
         if ((e = hipMemcpyAsync(o.rcol, o.hcol, (size_t)eres * 4, hipMemcpyHostToDevice, s)) != hipSuccess) return e;
         if ((e = hipMemcpyAsync(o.rval, o.hval, (size_t)eres * o.vb, hipMemcpyHostToDevice, s)) != hipSuccess)
             return e;
@@ -213,8 +213,8 @@ hipError_t ooc_prepare(Plan& p, const Bufs& b, Ooc& o, int64_t slab_nnz, int64_t
         }
         const size_t me = (size_t)std::max<int64_t>(maxe, 1);
         for (int i = 0; i < 2; ++i) {
-            if ((e = hipMalloc((void**)&o.scol[i], me * 4)) != hipSuccess) return e;
-            if ((e = hipMalloc((void**)&o.sval[i], me * o.vb)) != hipSuccess) return e;
+            if ((e = device_alloc((void**)&o.scol[i], me * 4)) != hipSuccess) return e;
+            if ((e = device_alloc((void**)&o.sval[i], me * o.vb)) != hipSuccess) return e;
         }
         for (int i = 0; i < 2; ++i)
             if ((e = hipEventRecord(o.freed[i], s)) != hipSuccess) return e;

@@ -56,7 +56,7 @@ class Arena {
    public:
     bool init(size_t bytes) {
         bytes = align_up(bytes);
-        if (hipMalloc(&base_, bytes) != hipSuccess) return false;
+        if (device_alloc(&base_, bytes) != hipSuccess) return false;
         size_ = bytes;
         free_[0] = bytes;
         return true;

@@ -5,7 +5,8 @@
  *   - a block freed stream-ordered into a pool is idle until its stream is
  *     waited for ("pending") and stays the pool's until the pool is trimmed;
  *     the default pool gives a block back as soon as it is idle and waited for;
- *   - idle blocks of a pool serve that pool alone, whole. */
+ *   - idle blocks of a pool serve that pool alone, whole, and pending ones
+ *     their own stream alone. */
 #include <stddef.h>
 #include <stdint.h>
 #include <stdlib.h>
@@ -54,12 +55,13 @@ static void drop(Block* b) {
     free(b->p);
     memset(b, 0, sizeof(*b));
 }
-static int take(void** out, size_t bytes, int pool) {
+static int take(void** out, size_t bytes, int pool, void* stream) {
     pthread_mutex_lock(&mu);
     Block* slot = NULL;
     for (int i = 0; i < BLOCKS; ++i) {
         Block* b = &blocks[i];
-        if (b->p && b->idle && b->pool == pool && b->bytes >= bytes) {
+        if (b->p && b->idle && b->pool == pool && b->bytes >= bytes &&
+            (!b->pending || b->pending == (stream ? stream : (void*)-1))) {
             b->idle = 0;
             b->pending = NULL;
             *out = b->p;
@@ -93,7 +95,7 @@ int hipSetDevice(int d) { current_device = d; return OK; }
 int hipGetStreamDeviceId(void* s) { return stream_device(s); }
 int hipGetLastError(void) { int e = last_error; last_error = OK; return e; }
 int hipStreamIsCapturing(void* s, int* status) { (void)s; *status = capturing; return OK; }
-int hipMalloc(void** p, size_t bytes) { return take(p, bytes, -2); }
+int hipMalloc(void** p, size_t bytes) { return take(p, bytes, -2, NULL); }
 int hipFree(void* p) {
     pthread_mutex_lock(&mu);
     Block* b = find(p);
@@ -101,7 +103,7 @@ int hipFree(void* p) {
     pthread_mutex_unlock(&mu);
     return OK;
 }
-int hipMallocAsync(void** p, size_t bytes, void* s) { (void)s; return take(p, bytes, -1); }
+int hipMallocAsync(void** p, size_t bytes, void* s) { return take(p, bytes, -1, s); }
 int hipMemPoolCreate(void** pool, const int* props) {      /* props: type, handle types, location type, id */
     pools[npools].device = props[3];
     *pool = &pools[npools++];
@@ -111,7 +113,7 @@ int hipMemPoolSetAttribute(void* pool, int attr, void* value) { (void)pool; (voi
 int hipMemPoolDestroy(void* pool) { (void)pool; return OK; }
 int hipMallocFromPoolAsync(void** p, size_t bytes, void* pool, void* s) {
     if (((Pool*)pool)->device != stream_device(s)) ++count_pool_alloc_other_device;
-    return take(p, bytes, (int)((Pool*)pool - pools));
+    return take(p, bytes, (int)((Pool*)pool - pools), s);
 }
 int hipFreeAsync(void* p, void* s) {
     pthread_mutex_lock(&mu);

@@ -78,3 +78,54 @@ for s in (stream(0), stream(1), None):
 print(hip.fake_count(4))
 """)
     assert int(out) == 0
+
+
+FILL = """
+# A dozen solves of about 200 MB on streams of their own: idle memory stays with the pool.
+streams = [ctypes.c_void_p((k << 8) + 1) for k in range(1, 13)]
+for s in streams: assert solve_async(400_000, 1_000_000, s) == 0
+for s in streams[1:]: hip.hipStreamSynchronize(s)      # the first stream's free is still pending
+idle = hip.fake_idle()
+assert idle > 1024 * MB and idle == hip.fake_used()
+"""
+
+
+@pytest.mark.parametrize("call", [
+    "solve_async(4_000_000, 40_000_000, streams[0])",                        # past the pool's largest block
+    "solve_async(1_000_000, 10_000_000, streams[0])",                        # from the pool, in a larger block than any idle
+    "lz.lib().lz_ortho_loss(D, 4096, 4096, 8, 0, None, ctypes.byref(ctypes.c_double()))",
+    "lz._server_lib().lz_server_create(0, 900 * MB, 1, 0, ctypes.byref(ctypes.c_void_p()))",
+])
+def test_idle_pool_memory_is_given_back_before_an_allocation_fails(fake, call):
+    # The call's memory is there only together with what the pool keeps idle.
+    need = int(run(fake, f"""
+streams = [stream()]
+assert {call} == 0
+print(hip.fake_used(), flush=True)
+os._exit(0)
+"""))
+    run(fake, FILL + f"""
+hip.fake_capacity(max(idle, {need}) + 8 * MB)
+assert {call} == 0
+os._exit(0)
+""")
+
+
+def test_allocation_fails_cleanly_where_giving_back_is_not_enough(fake):
+    run(fake, FILL + """
+hip.fake_capacity(idle + 8 * MB)
+assert solve_async(40_000_000, 400_000_000, streams[0]) == -2     # LZ_ERR_OUT_OF_MEMORY
+assert solve_async(4000, 20000, streams[0]) == 0
+""")
+
+
+def test_no_wait_and_no_pool_inside_a_capture(fake):
+    # An allocation inside a capture is a graph node: it goes to the default pool,
+    # and one that fails is refused without waiting for the stream.
+    run(fake, """
+hip.fake_capturing(1)
+assert solve_async(4000, 20000, stream()) == 0 and hip.fake_idle() == hip.fake_used() > 0
+idle = hip.fake_idle()
+hip.fake_capacity(idle + 8 * MB)
+assert solve_async(4_000_000, 40_000_000, stream()) == -2 and hip.fake_idle() == idle
+""")
