@@ -203,7 +203,8 @@ const char* lz_status_string(int status);
  *             unit 2-norm, signed so its entry of largest modulus is positive.
  * Default options; the library allocates its workspace for the call,
  * stream-ordered on `stream` from a memory pool of its own that keeps at most
- * 2 GiB between calls (inside a stream capture: from the device's default pool).
+ * 2 GiB between calls (inside a stream capture: from the device's default pool;
+ * lz_release_memory gives it back).
  * Blocking: reads nnz = rowptr[n] back from the device and returns after the
  * results are in out_vals/out_vecs.  The finish is enqueued behind the m
  * iterations and does nothing unless all m steps completed; after a breakdown,
@@ -213,6 +214,15 @@ const char* lz_status_string(int status);
 int lanczos_topk(const int64_t* csr_rowptr, const int32_t* csr_col, const void* csr_val,
                  int64_t n, int32_t K, int32_t m, int32_t precision, void* stream,
                  double* out_vals, double* out_vecs);
+
+/*
+ * Gives the memory that the library's pools keep between calls back to the
+ * driver, on every device, for other allocators of the process (the library's
+ * own allocations do so before they fail).  What stream-ordered calls have yet
+ * to free stays until their streams have been waited for.  Does not wait;
+ * later calls fill the pools again.
+ */
+int lz_release_memory(void);
 
 /* Device bytes of workspace a solve of this shape needs (default options). */
 size_t lanczos_topk_workspace_size(int64_t n, int64_t nnz, int32_t K, int32_t m,

@@ -254,6 +254,14 @@ def topk_noalloc(rowptr, col, val, K: int, m: int, precision="fp64", **kw):
     return topk_async(rowptr, col, val, K, m, precision, _entry="lanczos_topk_noalloc", **kw)
 
 
+def release_memory() -> None:
+    """Gives the workspace memory that the library keeps between calls back to
+    the driver (lz_release_memory)."""
+    rc = lib().lz_release_memory()
+    if rc != 0:
+        raise LanczosError(rc, "lz_release_memory")
+
+
 def noalloc_max_bytes() -> int:
     return int(lib().lanczos_topk_noalloc_max_bytes())
 

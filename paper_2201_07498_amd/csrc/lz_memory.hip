@@ -9,10 +9,12 @@
 // 35 us per call whatever the size.  Larger blocks, and allocations inside a
 // stream capture (which become graph nodes), use the default pool.  The runtime
 // orders reuse between streams and threads.  Before an allocation of the
-// library fails, the pool's idle memory is given back and it is tried again.
+// library fails, the pool's idle memory is given back and it is tried again;
+// lz_release_memory() gives it back to other allocators of the process.
 #include <cstring>
 #include <mutex>
 
+#include "../../include/lanczos_topk.h"
 #include "lz_internal.h"
 
 namespace lz {
@@ -93,3 +95,14 @@ hipError_t device_alloc(void** p, size_t bytes) {
 }
 
 }  // namespace lz
+
+extern "C" int lz_release_memory(void) {
+    int rc = LZ_OK;
+    std::lock_guard<std::mutex> lk(lz::pool_mu);
+    for (hipMemPool_t pool : lz::pools)
+        if (pool && hipMemPoolTrimTo(pool, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            rc = LZ_ERR_HIP;
+        }
+    return rc;
+}

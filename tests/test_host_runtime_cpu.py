@@ -129,3 +129,15 @@ idle = hip.fake_idle()
 hip.fake_capacity(idle + 8 * MB)
 assert solve_async(4_000_000, 40_000_000, stream()) == -2 and hip.fake_idle() == idle
 """)
+
+
+def test_release_memory_gives_back_what_is_idle(fake):
+    run(fake, FILL + """
+lz.release_memory()
+pending = hip.fake_used()
+assert 0 < pending < idle // 4                       # the first stream has yet to free its block
+hip.hipStreamSynchronize(streams[0])
+lz.release_memory()
+assert hip.fake_used() == 0
+assert solve_async(4000, 20000, stream()) == 0 and hip.fake_used() > 0
+""")
