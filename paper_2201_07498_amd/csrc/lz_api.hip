@@ -156,15 +156,6 @@ Bufs resolve(const Plan& p, void* base) {
     return b;
 }
 
-// Pinned host copy of the state (one per host thread, kept for the process):
-// pageable copies are staged in many small blits.
-static State* pinned_state() {
-    static thread_local State* pinned = nullptr;
-    if (!pinned && hipHostMalloc((void**)&pinned, sizeof(State), hipHostMallocDefault) != hipSuccess)
-        pinned = nullptr;
-    return pinned;
-}
-
 }  // namespace lz
 
 using namespace lz;
@@ -232,6 +223,7 @@ int run_solve(Plan p, Csr a, const lz_options& o, hipStream_t s, double* out_val
     int rc = LZ_OK;
     void* ws = o.workspace;
     bool owned = false;
+    HostState host;
     State* hst = nullptr;
     // Profiling: phase events (start, after the start vector, after the
     // last Lanczos iteration, before and after the finish) and a pair around
@@ -258,7 +250,7 @@ int run_solve(Plan p, Csr a, const lz_options& o, hipStream_t s, double* out_val
             owned = true;
         }
         const Bufs b = resolve(p, ws);
-        hst = pinned_state();
+        hst = host.get();
         if (!hst) {
             rc = LZ_ERR_OUT_OF_MEMORY;
             goto done;
@@ -389,7 +381,8 @@ int run_solve(Plan p, Csr a, const lz_options& o, hipStream_t s, double* out_val
         }
     }
 done:
-    if (owned || hc) (void)hipStreamSynchronize(s);
+    // (After a failed call, copies to the host may still be under way.)
+    if (owned || hc || rc == LZ_ERR_HIP) (void)hipStreamSynchronize(s);
     if (hc) {
         if (hc->ooc.ks && ooc_end(hc->ooc, user) != hipSuccess && rc == LZ_OK) rc = LZ_ERR_HIP;
         ooc_release(hc->ooc);
@@ -681,7 +674,8 @@ int lz_spmv(const int64_t* csr_rowptr, const int32_t* csr_col, const void* csr_v
                  o_head = align_up(o_tk + (size_t)p.n_tiles * 4, 256),
                  o_tail = align_up(o_head + (size_t)p.n_tiles * 8, 256), bytes = o_tail + (size_t)p.n_tiles * 8;
     hipStream_t s = (hipStream_t)stream;
-    State* hst = pinned_state();
+    HostState host;
+    State* hst = host.get();
     void* ws = nullptr;
     int rc = LZ_OK;
     if (!hst || workspace_alloc(&ws, bytes, s) != hipSuccess) return LZ_ERR_OUT_OF_MEMORY;
@@ -712,7 +706,8 @@ int lz_tridiag_eig(const double* alpha, const double* offdiag, int32_t m, double
     void* d = nullptr;
     const hipStream_t s = nullptr;
     const size_t so = align_up(sizeof(State), 256);
-    State* hst = pinned_state();
+    HostState host;
+    State* hst = host.get();
     if (!hst || workspace_alloc(&d, so + 2 * 64 * 8, s) != hipSuccess) return LZ_ERR_OUT_OF_MEMORY;
     {
         State* st = (State*)d;

@@ -241,6 +241,22 @@ Bufs resolve(const Plan& p, void* base);
 hipError_t workspace_alloc(void** p, size_t bytes, hipStream_t s);
 hipError_t device_alloc(void** p, size_t bytes);
 
+// Pinned host copy of a solve's state, for the length of a call (pageable
+// copies are staged in many small blits).  Returned buffers serve later calls
+// of any thread, so there are as many as calls have run at once.  A copy into
+// it must have ended before it goes out of scope.
+class HostState {
+   public:
+    HostState() = default;
+    ~HostState();
+    HostState(const HostState&) = delete;
+    HostState& operator=(const HostState&) = delete;
+    State* get();          // null if there is no memory
+
+   private:
+    State* st_ = nullptr;
+};
+
 // Matrix pointers.
 struct Csr {
     const int64_t* rowptr;

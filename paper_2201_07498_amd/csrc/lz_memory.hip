@@ -61,7 +61,34 @@ bool give_back(int dev) {
     return pools[dev] && hipMemPoolTrimTo(pools[dev], 0) == hipSuccess;
 }
 
+// Pinned state buffers not in use, linked through their first word.
+std::mutex host_mu;
+void* host_free = nullptr;
+
 }  // namespace
+
+State* HostState::get() {
+    if (st_) return st_;
+    {
+        std::lock_guard<std::mutex> lk(host_mu);
+        if (host_free) {
+            st_ = (State*)host_free;
+            host_free = *(void**)st_;
+        }
+    }
+    if (!st_ && hipHostMalloc((void**)&st_, sizeof(State), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        st_ = nullptr;
+    }
+    return st_;
+}
+
+HostState::~HostState() {
+    if (!st_) return;
+    std::lock_guard<std::mutex> lk(host_mu);
+    *(void**)st_ = host_free;
+    host_free = st_;
+}
 
 // An allocation that failed for good: reported by its status alone, not by the
 // next launch's error check too.

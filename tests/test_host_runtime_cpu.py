@@ -141,3 +141,25 @@ lz.release_memory()
 assert hip.fake_used() == 0
 assert solve_async(4000, 20000, stream()) == 0 and hip.fake_used() > 0
 """)
+
+
+def test_pinned_buffers_do_not_pile_up_with_threads(fake):
+    # One buffer serves calls in any number of threads that do not overlap, and
+    # overlapping ones take no more than one each.
+    run(fake, """
+import threading
+def work():
+    assert spmv(s=stream()) == 0
+    lz.tridiag_eig(np.ones(4), np.ones(3))
+    L.lanczos_topk_ex(D, D, D, 1000, 5000, 2, 8, 0, stream(), D, D, None, None)
+for _ in range(20):
+    t = threading.Thread(target=work); t.start(); t.join()
+assert hip.fake_count(1) == 1, hip.fake_count(1)
+ts = [threading.Thread(target=work) for _ in range(40)]
+for t in ts: t.start()
+for t in ts: t.join()
+assert hip.fake_count(1) <= 40
+n = hip.fake_count(0)
+work()
+assert hip.fake_count(0) == n
+""")
