@@ -225,7 +225,7 @@ __device__ __forceinline__ int jacobi_core(int m, const double* diag, const doub
         // start of a sweep is the identity.
         bool pending = false;
         if (is_rot) {
-            pending = live && rot;
+            pending = live && rot && m > 1;      // (m = 1: the only pair is with the dummy row, which a NaN would rotate)
         } else if (is_blk && live) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
