@@ -235,6 +235,13 @@ size_t lanczos_topk_workspace_size(int64_t n, int64_t nnz, int32_t K, int32_t m,
 size_t lanczos_topk_workspace_size_opt(int64_t n, int64_t nnz, int32_t K, int32_t m,
                                        int32_t precision, const lz_options* opt);
 
+/* Panels of x (128 KiB each, past its first 4 MiB) whose gathers the sweep-block
+ * SpMV of such a solve has laid out ahead of it; 0 where there are none, no
+ * sweep blocks or no room for their tables in the workspace (and for invalid
+ * arguments). */
+int32_t lanczos_topk_sweep_panels(int64_t n, int64_t nnz, int32_t K, int32_t m, int32_t precision,
+                                  const lz_options* opt);
+
 /*
  * lanczos_topk with options and a report.  nnz must equal rowptr[n].
  * opt may be NULL (defaults); report may be NULL.  With a caller workspace

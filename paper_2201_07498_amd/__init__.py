@@ -85,6 +85,8 @@ def lib() -> ctypes.CDLL:
         L.lanczos_topk_workspace_size.argtypes = [i64, i64, i32, i32, i32]
         L.lanczos_topk_workspace_size_opt.restype = ctypes.c_size_t
         L.lanczos_topk_workspace_size_opt.argtypes = [i64, i64, i32, i32, i32, ctypes.POINTER(Options)]
+        L.lanczos_topk_sweep_panels.restype = ctypes.c_int32
+        L.lanczos_topk_sweep_panels.argtypes = [i64, i64, i32, i32, i32, ctypes.POINTER(Options)]
         L.lanczos_topk_ex.restype = ctypes.c_int
         L.lanczos_topk_ex.argtypes = [P, P, P, i64, i64, i32, i32, i32, P, P, P,
                                       ctypes.POINTER(Options), ctypes.POINTER(Report)]
@@ -157,6 +159,12 @@ def workspace_size(n: int, nnz: int, K: int, m: int, precision="fp64", sweep=Non
         return int(lib().lanczos_topk_workspace_size(n, nnz, K, m, _prec(precision)))
     opt = _options(0, "twice", True, False, reorder, "mixed", None, sweep=sweep)
     return int(lib().lanczos_topk_workspace_size_opt(n, nnz, K, m, _prec(precision), ctypes.byref(opt)))
+
+
+def sweep_panels(n: int, nnz: int, K: int, m: int, precision="fp64", sweep=None, reorder="auto") -> int:
+    """Panels of x whose gathers the sweep-block SpMV has laid out ahead (0: none)."""
+    opt = _options(0, "twice", True, False, reorder, "mixed", None, sweep=sweep)
+    return int(lib().lanczos_topk_sweep_panels(n, nnz, K, m, _prec(precision), ctypes.byref(opt)))
 
 
 def topk(rowptr, col, val, K: int, m: int, precision="fp64", seed: int = 0, reorth="twice",

@@ -508,6 +508,14 @@ size_t lanczos_topk_workspace_size_opt(int64_t n, int64_t nnz, int32_t K, int32_
     return plan_for(n, nnz, K, m, precision, o).bytes;
 }
 
+int32_t lanczos_topk_sweep_panels(int64_t n, int64_t nnz, int32_t K, int32_t m, int32_t precision,
+                                  const lz_options* opt) {
+    if (n < 1 || nnz < 0 || K < 1 || m < K || m > LZ_MAX_STEPS || precision < 0 || precision > 2) return 0;
+    lz_options o;
+    if (check_options(opt, precision, &o) != LZ_OK) return 0;
+    return plan_for(n, nnz, K, m, precision, o).sw_np;
+}
+
 int lanczos_topk_ex(const int64_t* csr_rowptr, const int32_t* csr_col, const void* csr_val, int64_t n, int64_t nnz,
                     int32_t K, int32_t m, int32_t precision, void* stream, double* out_vals, double* out_vecs,
                     const lz_options* opt, lz_report* report) {
