@@ -61,16 +61,28 @@ constexpr int sweep_rows(int prec) { return prec == 0 ? 4096 : 2048; }
 constexpr int SW_POSBITS = 18;
 static_assert((int64_t)SW_W * 4096 <= (int64_t(1) << SW_POSBITS) && (4096 << SW_POSBITS) > 0, "sweep payload");
 // Automatic choice: relabelled matrices whose x takes at least 64 MiB.
-// Measured on MI355X, whole solve (K = 8, m = 32) of R-MAT with edge factor
-// 16, tiles -> sweep blocks: scale 24 FP32 149 -> 135 ms, FP64 196 -> 180,
-// BF16 (x 32 MiB) 118 -> 120; scale 25 FP32 337 -> 280, BF16 249 -> 242,
-// FP64 444 -> 366; scale 26 FP32 769 -> 634, BF16 578 -> 520.  At scale 23
-// in FP32 (x 32 MiB) the step SpMV was slower in sweep blocks.
+// Measured on MI355X with the tail pass, R-MAT with edge factor 16, tiles ->
+// sweep blocks, step SpMV and setup in ms:
+//   x 64 MiB up:  scale 23 FP64 1.91 -> 1.06, 4.4 -> 11.3; scale 24 FP32 3.07 ->
+//                 1.60, 8.4 -> 20.2, FP64 4.27 -> 2.08, 9.0 -> 22.8; scale 25 FP32
+//                 7.57 -> 3.29, 17.9 -> 41.3, BF16 5.69 -> 2.86, 17.0 -> 39.6,
+//                 FP64 10.2 -> 4.50, 19.1 -> 48.6
+//   x 32 MiB:     scale 22 FP64 0.93 -> 0.80, 2.2 -> 6.0; scale 23 FP32 1.37 ->
+//                 1.23, 4.2 -> 10.3; scale 24 BF16 2.54 -> 1.40, 8.1 -> 19.2
+//   x 16 MiB:     scale 22 FP32 0.63 -> 0.99; scale 23 BF16 1.13 -> 1.23
+// From 64 MiB the setup pays within 5 to 9 steps in every precision.  At 32 MiB
+// it takes 10 (BF16) to 43 steps (FP32) and the copy's memory, at 16 MiB the
+// SpMV itself is slower.
 constexpr int64_t SWEEP_AUTO_MIN_N = int64_t(1) << 22;
 constexpr uint64_t SWEEP_AUTO_MIN_X_BYTES = uint64_t(1) << 26;
 
 // Tail columns of the sweep blocks: x past its first SW_HEAD_BYTES, cut into at
-// most SW_PANELS_MAX panels that fit the LDS of a CU (see k_sweep_tail).
+// most SW_PANELS_MAX panels that fit the LDS of a CU (see k_sweep_tail).  The cap
+// bounds the panels' offsets in LDS (4 KiB) and the tables; x past the last
+// panel (68 MiB) owns too few entries of a relabelled matrix to matter.  Caps
+// of 512 / 1024 / 2048, step SpMV: R-MAT 25 FP32 3.28 / 3.28 / 3.29 ms, BF16 2.89
+// / 2.89 / 2.87 ms; R-MAT 26 FP32 (x 256 MiB) 6.62 / 6.62 / 6.61 ms with 1 and 2 ms
+// more setup.
 constexpr int64_t SW_HEAD_BYTES = int64_t(4) << 20;
 constexpr int SW_PANEL_BYTES = 128 << 10;
 constexpr int SW_PANELS_MAX = 512;
@@ -285,10 +297,13 @@ hipError_t launch_spmv_step(const Plan& p, const Bufs& b, const Csr& a, hipStrea
 // Column checks 0 <= col[e] < n of entries [e0, e1) (col indexed by matrix
 // entry); a failure sets the solve status to LZ_ERR_INVALID_ARG.
 void launch_validate_cols(State* st, const int32_t* col, int64_t e0, int64_t e1, int64_t n, hipStream_t s);
-// The LDS copy of the head of x pays off for relabelled (power-law)
+// The LDS copy of the head of x pays off for large relabelled (power-law)
 // matrices in the mixed modes and costs occupancy elsewhere.  Measured on
-// MI355X: R-MAT scale 23 FP32 1.79 -> 1.59 ms, BF16 1.63 -> 1.25 ms; scale
-// 20 BF16 90 -> 80 us but FP32 102 -> 105 us; banded FP32 0.77 -> 1.15 ms.
+// MI355X, step SpMV without -> with it: R-MAT scale 23 FP32 1.71 -> 1.37 ms, BF16
+// 1.51 -> 1.14 ms; scale 22 FP32 0.80 -> 0.63 ms; scale 20 FP32 65 -> 88 us;
+// banded 2^23 rows FP32 0.34 -> 0.38 ms.  The BF16 line at 2^20 rows dates from
+// before the wide tile loads (scale 20 90 -> 80 us); there the group-sorted
+// tiles alone now take 57 us against 78.
 inline bool want_xcache(const Plan& p, bool relabelled) {
     if (!relabelled) return false;
     if (p.prec == 2) return p.n >= (int64_t(1) << 20);

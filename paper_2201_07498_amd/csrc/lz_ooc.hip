@@ -10,8 +10,13 @@ namespace lz {
 
 // A slab's column indices and values from pinned host memory to a staging buffer.
 // The host link bounds it (57.5 GB/s for one large copy): 16 workgroups keep
-// 512 KiB in flight, several times what the link's latency asks for, and leave the
-// chip to the slab before.  Loads are aligned to 16 bytes of the source, which
+// 512 KiB in flight, several times what the link's latency asks for.  The kernels
+// beside it run slower while it does, since they share 16 CUs with loads of host
+// latency and their grids wait for the last workgroup: R-MAT 20 FP32 in one slab,
+// step SpMV 138 -> 232 us, orthogonalisation kernels of 48 columns 41 -> 105 and
+// 124 us against copies by the runtime, out of 2.3 ms of copy a step.  Whole solves
+// took 0.64 to 0.94 of the time with those copies in every mix measured (1.4M to
+// 16M entries, slabs of 2^18 to 2^24, none to 95 % resident).  Loads are aligned to 16 bytes of the source, which
 // starts anywhere; the stores take what alignment that leaves.  Copies by the
 // runtime cost the host thread 70 to 450 us inside a call about once per slab,
 // while the copy stream idled.  16.1M FP32 entries, 16 steps, slabs of 2^18 / 2^20 /

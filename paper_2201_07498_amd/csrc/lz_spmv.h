@@ -552,11 +552,11 @@ struct TailArgs {
 // wavefronts per SIMD, so registers cost nothing).
 constexpr int SW_U = 12;
 // Rows per block and wavefronts per workgroup (their row sums fill the LDS, so
-// one workgroup per CU), per storage precision.  Measured on MI355X, R-MAT
-// scale 26 step SpMV without the tail pass (rows/wavefronts/grid): FP64
-// 4096/4/1024 14.3 ms, 2048/8/512 16.5; FP32 2048/8/512 12.4 ms, 4096/4/1024
-// 12.6, 2048/4/512 13.2; BF16 2048/8/512 9.7 ms, 2048/4/512 10.3, 4096/4/1024
-// 11.7.
+// one workgroup per CU), per storage precision.  Measured on MI355X, step SpMV
+// (rows/wavefronts): R-MAT 25 with the tail pass FP64 4096/4 4.46 ms, 2048/8
+// 4.75; FP32 2048/8 3.28-3.36 ms, 2048/4 3.34, 4096/4 3.16; BF16 2048/8 2.93 ms,
+// 2048/4 2.90, 4096/4 3.08.  R-MAT 26 without it, where the shapes were chosen:
+// FP64 14.3 and 16.5 ms; FP32 12.4, 13.2, 12.6; BF16 9.7, 10.3, 11.7.
 template <int P> struct SweepShape { static constexpr int ROWS = 2048, WAVES = 8; };
 template <> struct SweepShape<0> { static constexpr int ROWS = 4096, WAVES = 4; };
 constexpr int SWEEP_GRID_MAX = 16384;
