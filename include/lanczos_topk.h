@@ -219,8 +219,9 @@ int lanczos_topk(const int64_t* csr_rowptr, const int32_t* csr_col, const void* 
  * Gives the memory that the library's pools keep between calls back to the
  * driver, on every device, for other allocators of the process (the library's
  * own allocations do so before they fail).  What stream-ordered calls have yet
- * to free stays until their streams have been waited for.  Does not wait;
- * later calls fill the pools again.
+ * to free stays until their streams have been waited for.  Does not wait (the
+ * driver has the memory about a millisecond later); later calls fill the pools
+ * again.
  */
 int lz_release_memory(void);
 

@@ -11,8 +11,10 @@
 // orders reuse between streams and threads.  Before an allocation of the
 // library fails, the pool's idle memory is given back and it is tried again;
 // lz_release_memory() gives it back to other allocators of the process.
+#include <chrono>
 #include <cstring>
 #include <mutex>
+#include <thread>
 
 #include "../../include/lanczos_topk.h"
 #include "lz_internal.h"
@@ -53,12 +55,34 @@ hipMemPool_t workspace_pool(int dev) {
     return pools[dev];
 }
 
-// Gives the idle memory of a device's pool back to the driver; false if the
-// device has no pool.
-bool give_back(int dev) {
-    if (dev < 0 || dev >= POOL_MAX_DEVICES) return false;
-    std::lock_guard<std::mutex> lk(pool_mu);
-    return pools[dev] && hipMemPoolTrimTo(pools[dev], 0) == hipSuccess;
+// Gives the idle memory of a pool back to the driver; false if it had none.
+bool trim(hipMemPool_t pool) {
+    uint64_t before = 0, after = 0;
+    if (hipMemPoolGetAttribute(pool, hipMemPoolAttrReservedMemCurrent, &before) == hipSuccess &&
+        hipMemPoolTrimTo(pool, 0) == hipSuccess &&
+        hipMemPoolGetAttribute(pool, hipMemPoolAttrReservedMemCurrent, &after) == hipSuccess)
+        return after < before;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Runs alloc again after a failure, first giving the idle memory of the
+// device's pool back.  The runtime drops its last references to a block on a
+// thread of its own: the driver had it 0.6 ms after the trim, so the
+// allocation is tried for 20 times that.
+template <class Alloc> hipError_t retry(int dev, Alloc&& alloc) {
+    bool freed = false;
+    if (dev >= 0 && dev < POOL_MAX_DEVICES) {
+        std::lock_guard<std::mutex> lk(pool_mu);
+        freed = pools[dev] && trim(pools[dev]);
+    }
+    hipError_t e = alloc();
+    for (int i = 0; freed && e != hipSuccess && i < 12; ++i) {
+        (void)hipGetLastError();
+        std::this_thread::sleep_for(std::chrono::milliseconds(1));
+        e = alloc();
+    }
+    return e;
 }
 
 // Pinned state buffers not in use, linked through their first word.
@@ -109,16 +133,15 @@ hipError_t workspace_alloc(void** p, size_t bytes, hipStream_t s) {
     (void)hipGetLastError();
     // Blocks that the stream has yet to free are idle once it has been waited for.
     (void)hipStreamSynchronize(s);
-    (void)give_back(dev);
-    return settle(hipMallocAsync(p, bytes, s));
+    return settle(retry(dev, [&] { return hipMallocAsync(p, bytes, s); }));
 }
 
 // hipMalloc on the current device.
 hipError_t device_alloc(void** p, size_t bytes) {
     const hipError_t e = settle(hipMalloc(p, bytes));
     int dev = -1;
-    if (e == hipSuccess || hipGetDevice(&dev) != hipSuccess || !give_back(dev)) return e;
-    return settle(hipMalloc(p, bytes));
+    if (e == hipSuccess || hipGetDevice(&dev) != hipSuccess) return e;
+    return settle(retry(dev, [&] { return hipMalloc(p, bytes); }));
 }
 
 }  // namespace lz

@@ -23,12 +23,15 @@ static pthread_mutex_t mu = PTHREAD_MUTEX_INITIALIZER;
 static Block blocks[BLOCKS];
 static Pool pools[POOLS];
 static int npools, current_device, last_error, capturing;
-static size_t capacity = (size_t)1 << 40, used;
+static size_t capacity = (size_t)1 << 40, used, lagging;
+static int lag, lag_left;
 static struct { char* base; size_t bytes; } pinned[RANGES];
 static int npinned;
 static long count_host_malloc, count_host_live, count_h2d_pinned, count_launch, count_pool_alloc_other_device;
 
 void fake_capacity(size_t bytes) { capacity = bytes; }
+/* Trimmed memory comes free only after this many further failed allocations. */
+void fake_lag(int attempts) { lag = attempts; }
 size_t fake_used(void) { return used; }
 size_t fake_idle(void) {
     size_t s = 0;
@@ -71,7 +74,9 @@ static int take(void** out, size_t bytes, int pool, void* stream) {
         if (!b->p && !slot) slot = b;
     }
     int rc = OK;
-    if (!slot || used + bytes > capacity) {
+    if (lagging && lag_left == 0) lagging = 0;
+    if (!slot || used + lagging + bytes > capacity) {
+        if (lagging) --lag_left;
         rc = fail(NOMEM);
     } else {
         used += bytes;
@@ -110,6 +115,15 @@ int hipMemPoolCreate(void** pool, const int* props) {      /* props: type, handl
     return OK;
 }
 int hipMemPoolSetAttribute(void* pool, int attr, void* value) { (void)pool; (void)attr; (void)value; return OK; }
+int hipMemPoolGetAttribute(void* pool, int attr, void* value) {
+    uint64_t s = 0;
+    pthread_mutex_lock(&mu);
+    for (int i = 0; i < BLOCKS; ++i)
+        if (blocks[i].p && blocks[i].pool == (int)((Pool*)pool - pools)) s += blocks[i].bytes;
+    pthread_mutex_unlock(&mu);
+    *(uint64_t*)value = s;
+    return attr == 5 ? OK : fail(INVALID);                 /* hipMemPoolAttrReservedMemCurrent */
+}
 int hipMemPoolDestroy(void* pool) { (void)pool; return OK; }
 int hipMallocFromPoolAsync(void** p, size_t bytes, void* pool, void* s) {
     if (((Pool*)pool)->device != stream_device(s)) ++count_pool_alloc_other_device;
@@ -141,7 +155,12 @@ int hipMemPoolTrimTo(void* pool, size_t keep) {
     pthread_mutex_lock(&mu);
     for (int i = 0; i < BLOCKS; ++i) {
         Block* b = &blocks[i];
-        if (b->p && b->idle && !b->pending && b->pool == (int)((Pool*)pool - pools)) drop(b);
+        if (!b->p || !b->idle || b->pending || b->pool != (int)((Pool*)pool - pools)) continue;
+        if (lag) {
+            lagging += b->bytes;
+            lag_left = lag;
+        }
+        drop(b);
     }
     pthread_mutex_unlock(&mu);
     return OK;

@@ -1,4 +1,6 @@
 """Device memory that the library keeps between calls is bounded and can be given back."""
+import time
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -19,15 +21,24 @@ def test_release_memory():
         torch.cuda.synchronize()
         return torch.cuda.mem_get_info()[0]
 
+    def release(target=None):
+        # The driver has the memory when the runtime has dropped its last references,
+        # on a thread of its own.
+        lz.release_memory()
+        end = time.monotonic() + 2.0
+        while True:
+            time.sleep(0.05)
+            free = torch.cuda.mem_get_info()[0]
+            if target is None or free >= target or time.monotonic() > end:
+                return free
+
     solve()                                   # code objects, streams and scratch of the first call
-    lz.release_memory()
-    before = torch.cuda.mem_get_info()[0]
+    before = release()
     kept = before - solve()
     vals = out[0].clone()
     need = lz.workspace_size(200_000, csr[1].numel(), 8, 24, "fp64")
     print(f"workspace {need} bytes, kept {kept}", flush=True)
-    assert 0 < kept <= 2 << 30
-    lz.release_memory()
-    assert torch.cuda.mem_get_info()[0] == before
+    assert need // 2 < kept <= 2 << 30
+    assert release(before) >= before
     solve()
     assert torch.equal(out[0], vals)

@@ -104,7 +104,9 @@ assert {call} == 0
 print(hip.fake_used(), flush=True)
 os._exit(0)
 """))
-    run(fake, FILL + f"""
+    for lag in (0, 3):             # the driver may have given-back memory a little later
+        run(fake, FILL + f"""
+hip.fake_lag({lag})
 hip.fake_capacity(max(idle, {need}) + 8 * MB)
 assert {call} == 0
 os._exit(0)
