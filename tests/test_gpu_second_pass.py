@@ -78,6 +78,17 @@ def test_server_equals_blocking(reorth, use_graphs):
             assert np.array_equal(res["resid"], a[2]["resid"])
 
 
+@pytest.mark.parametrize("reorth", ["selective", "twice"])
+@pytest.mark.parametrize("name", ["clusters12", "repeated4"])
+def test_host_resident_equals_blocking(name, reorth):
+    (rp, c, v), K, m = MATRICES[name]
+    a = lz.topk(*device_csr(rp, c, v, "fp64"), K, m, "fp64", seed=3, reorth=reorth, reorder="off")
+    b = lz.topk_host(torch.from_numpy(rp), torch.from_numpy(c).pin_memory(), torch.from_numpy(v).pin_memory(), K, m,
+                     "fp64", slab_nnz=4096, seed=3, reorth=reorth)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    assert a[2]["restarts"] == b[2]["restarts"] and np.array_equal(a[2]["alpha"], b[2]["alpha"])
+
+
 def test_profile_of_a_held_solve():
     csr, K, m = MATRICES["clusters12"]
     a = lz.topk(*device_csr(*csr, "fp64"), K, m, "fp64", seed=3)
