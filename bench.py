@@ -104,13 +104,19 @@ def generate(name: str):
     raise SystemExit(f"unknown workload {name}")
 
 
+# Roundings of the values that generate() makes, as the stored solves name
+# them (that of R-MAT 20 belongs to the BF16-rounded matrix, not to this one).
+GOLDEN_VALUES = {"rmat20": "round fp32, normalize_sym, round fp32", "rmat23": "round bf16", "rmat26": "round fp32"}
+
+
 def golden(name: str):
     """The FP64 oracle's stored solve of the workload (tests/golden), if any."""
     path = os.path.join(ROOT, "tests", "golden", f"{name}.json")
     if not os.path.exists(path):
         return None
     with open(path) as fh:
-        return json.load(fh)
+        G = json.load(fh)
+    return G if G["recipe"]["values"] == GOLDEN_VALUES.get(name) else None
 
 
 LAYOUTS = {0: "caller's rows", 1: "hub-first rows", 2: "hub-first rows, tiles in column order",
