@@ -30,6 +30,15 @@ std::mutex pool_mu;
 hipMemPool_t pools[POOL_MAX_DEVICES] = {};
 bool tried[POOL_MAX_DEVICES] = {};
 
+// The device a stream belongs to, -1 if it cannot be told.  The default streams
+// are the current device's (hipGetStreamDeviceId takes no such handle but null:
+// it follows the others).
+int stream_device(hipStream_t s) {
+    if (s != nullptr && s != hipStreamLegacy && s != hipStreamPerThread) return hipGetStreamDeviceId(s);
+    int dev = -1;
+    return hipGetDevice(&dev) == hipSuccess ? dev : -1;
+}
+
 // Pool of a device; null if it has none.
 hipMemPool_t workspace_pool(int dev) {
     if (dev < 0 || dev >= POOL_MAX_DEVICES) return nullptr;
@@ -126,7 +135,7 @@ hipError_t workspace_alloc(void** p, size_t bytes, hipStream_t s) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
         return settle(hipMallocAsync(p, bytes, s));
-    const int dev = hipGetStreamDeviceId(s);
+    const int dev = stream_device(s);
     const hipMemPool_t pool = bytes <= POOL_BLOCK_MAX ? workspace_pool(dev) : nullptr;
     if ((pool ? hipMallocFromPoolAsync(p, bytes, pool, s) : hipMallocAsync(p, bytes, s)) == hipSuccess)
         return hipSuccess;

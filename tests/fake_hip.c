@@ -50,8 +50,9 @@ long fake_count(int what) {
                        : count_pool_alloc_other_device;
 }
 
-/* A stream is null (the current device's) or 1 + its device in the low byte. */
-static int stream_device(void* s) { return s ? (int)((uintptr_t)s & 255) - 1 : current_device; }
+/* A stream is null, hipStreamLegacy (1) or hipStreamPerThread (2), the current
+ * device's, or has 1 + its device in the low byte. */
+static int stream_device(void* s) { return (uintptr_t)s > 2 ? (int)((uintptr_t)s & 255) - 1 : current_device; }
 static int fail(int e) { return last_error = e; }
 static void drop(Block* b) {
     used -= b->bytes;
@@ -97,7 +98,10 @@ static Block* find(void* p) {
 
 int hipGetDevice(int* d) { *d = current_device; return OK; }
 int hipSetDevice(int d) { current_device = d; return OK; }
-int hipGetStreamDeviceId(void* s) { return stream_device(s); }
+int hipGetStreamDeviceId(void* s) {
+    if ((uintptr_t)s == 1 || (uintptr_t)s == 2) abort();   /* as the runtime, which follows the handle */
+    return stream_device(s);
+}
 int hipGetLastError(void) { int e = last_error; last_error = OK; return e; }
 int hipStreamIsCapturing(void* s, int* status) { (void)s; *status = capturing; return OK; }
 int hipMalloc(void** p, size_t bytes) { return take(p, bytes, -2, NULL); }

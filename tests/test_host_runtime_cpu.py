@@ -71,9 +71,10 @@ def test_host_arrays_past_their_pinned_allocation_go_through_the_runtime(fake, s
 
 
 def test_workspace_comes_from_the_device_of_the_stream(fake):
-    # The current device is 0, the streams belong to devices 0, 1 and (null) 0.
+    # The current device is 0; the streams belong to devices 0 and 1 and, the default
+    # ones (null, legacy, per thread), to the current device.
     out = run(fake, """
-for s in (stream(0), stream(1), None):
+for s in (stream(0), stream(1), None, ctypes.c_void_p(1), ctypes.c_void_p(2)):
     assert spmv(s=s) == 0 and solve_async(4000, 20000, s) == 0
 print(hip.fake_count(4))
 """)
